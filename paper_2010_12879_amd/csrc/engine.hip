@@ -152,6 +152,7 @@ struct Ctx {
     int fg_m = 0;
     // quantile selection
     uint8_t *d_sel_work = nullptr;
+    unsigned long long *d_sel_cand = nullptr;
     double *d_sel_out = nullptr;
     double *d_part = nullptr;
     int pstride = 0;          // partial sums per right side
@@ -2284,6 +2285,7 @@ spfd_status set_geometry(spfd_handle h, int nx, int ny, int nz, double hx, doubl
         h->d_adj_b = h->d_adj_c = h->d_adj_lam = h->d_adj_labpart = h->d_adj_labout = nullptr;
         h->d_adj_scal = nullptr;
         h->d_sel_work = nullptr;
+        h->d_sel_cand = nullptr;
         h->d_sel_out = nullptr;
         h->d_fgV = nullptr;
         h->d_fgZ = nullptr;
@@ -2780,19 +2782,30 @@ spfd_status spfd_percentile(spfd_handle h, const double *emag, double q, double 
         enter(h);
         const int nlab = h->voxel_mode ? MAX_LABELS : h->nlab;
         const int ng = 1 + nlab;
-        if (!h->d_sel_work) {
-            h->d_sel_work = dalloc<uint8_t>(h, h->geo_allocs, sel_work_bytes(1 + MAX_LABELS));
-            h->d_sel_out = dalloc<double>(h, h->geo_allocs, 1 + MAX_LABELS);
-        }
         const long long nvox = (long long)h->g.nx * h->g.ny * h->g.nz;
-        {
-            TScope ts(h, SPFD_K_EFIELD, 8.0 * nvox * 9.0);
-            HIPCHK(launch_quantiles(h->d_labels, h->d_table64, h->voxel_mode ? h->d_sigvox : nullptr, nvox, emag, ng, q,
-                                    h->d_sel_work, h->d_sel_out, h->stream));
+        if (!h->d_sel_work) {
+            h->d_sel_cand = dalloc<unsigned long long>(h, h->geo_allocs, (size_t)bin_candidates(nvox));
+            h->d_sel_out = dalloc<double>(h, h->geo_allocs, 2 + MAX_LABELS);
+            h->d_sel_work = dalloc<uint8_t>(h, h->geo_allocs, std::max(bin_state_bytes(), sel_work_bytes(1 + MAX_LABELS)));
         }
-        double out[1 + MAX_LABELS];
-        HIPCHK(hipMemcpyAsync(out, h->d_sel_out, ng * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
+        const double *sv = h->voxel_mode ? h->d_sigvox : nullptr;
+        double out[2 + MAX_LABELS];
+        auto fetch = [&](int n) {
+            HIPCHK(hipMemcpyAsync(out, h->d_sel_out, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+            HIPCHK(hipStreamSynchronize(h->stream));
+        };
+        {
+            TScope ts(h, SPFD_K_EFIELD, 18.0 * nvox);
+            HIPCHK(launch_quantiles_bins(h->d_labels, h->d_table64, sv, nvox, emag, nlab, q, h->d_sel_work,
+                                         h->d_sel_cand, h->d_sel_out, h->stream));
+        }
+        fetch(ng + 1);
+        if (out[ng] != 0.0) {   // more candidates than the buffer holds: the radix form
+            TScope ts(h, SPFD_K_EFIELD, 8.0 * nvox * 9.0);
+            HIPCHK(launch_quantiles(h->d_labels, h->d_table64, sv, nvox, emag, ng, q, h->d_sel_work, h->d_sel_out,
+                                    h->stream));
+            fetch(ng);
+        }
         *out_body = out[0];
         if (out_labels)
             for (int l = 0; l < nlab; ++l) out_labels[l] = out[1 + l];

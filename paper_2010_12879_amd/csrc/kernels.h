@@ -351,6 +351,15 @@ size_t sel_work_bytes(int ngroups);
 hipError_t launch_quantiles(const uint8_t *labels, const double *table, const double *sig_vox, long long nvox,
                             const double *emag, int ngroups, double q, void *work, double *out, hipStream_t s);
 
+// the same for labels < nlab in two scans of the voxels.  work: bin_state_bytes(); cand: a buffer of
+// bin_candidates(nvox) keys; out: nlab + 2 doubles, the last one nonzero when the candidates did not fit it
+// (then the others are not written and launch_quantiles has to do it)
+size_t bin_state_bytes();
+long long bin_candidates(long long nvox);
+hipError_t launch_quantiles_bins(const uint8_t *labels, const double *table, const double *sig_vox, long long nvox,
+                                 const double *emag, int nlab, double q, void *work, unsigned long long *cand,
+                                 double *out, hipStream_t s);
+
 // ---------------------------------------------------------------- adjoint gradient
 hipError_t launch_adj_voxel(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
                             const double h[3], double omega, const double *a, const double *psi,
