@@ -171,8 +171,10 @@ constexpr int FIN_T = 1024;           // threads of a final selection
 constexpr int FIN_BINS = 2048;        // its 11-bit digits
 constexpr int FIN_LIST = 4096;        // keys it keeps in LDS
 
+constexpr int SAMPLE_WG = 1 + (HIST_WORDS + SCAN_T - 1) / SCAN_T;   // workgroups of k_bin_start
+
 struct BinState {
-    unsigned long long base;          // lowest key of the window
+    unsigned long long top[SAMPLE_WG];// largest sampled keys (finite), one per workgroup of k_bin_start
     unsigned present[MAX_LABELS / 32];// labels that occur (only read when the labels exceed LAB_FULL)
     int bin[SEL_GROUPS];              // the bin that holds rank k of a group (-1: no voxels)
     long long k[SEL_GROUPS];          // the rank to find inside that bin
@@ -219,8 +221,11 @@ __device__ __forceinline__ LabelMap label_map(const BinState *st, int nlab, unsi
     return m;
 }
 
-// clears the histograms, the presence mask and the cursors; the first workgroup samples the largest finite |E|
-// (4,096 spread voxels: each is a line of its own from memory, 32,768 of them took 70 us)
+// Clears the histograms, the presence mask and the cursors, and samples the largest finite |E|: every thread
+// reads SAMPLES voxels, each somewhere in a stretch of its own (a plain stride can stay in one column of the
+// grid).  One workgroup with 32,768 samples took 70 us, each being a line of its own from memory.
+constexpr int SAMPLES = 4;
+
 __global__ __launch_bounds__(SCAN_T) void k_bin_start(const double *__restrict__ emag, long long nvox, BinState *st,
                                                       unsigned *__restrict__ hist)
 {
@@ -228,22 +233,23 @@ __global__ __launch_bounds__(SCAN_T) void k_bin_start(const double *__restrict__
     if (blockIdx.x > 0) {
         const int i = ((int)blockIdx.x - 1) * SCAN_T + t;
         if (i < HIST_WORDS) hist[i] = 0u;
-        return;
+    } else {
+        if (t < MAX_LABELS / 32) st->present[t] = 0u;
+        for (int g = t; g < SEL_GROUPS; g += SCAN_T) st->cursor[g] = 0u;
     }
-    if (t < MAX_LABELS / 32) st->present[t] = 0u;
-    for (int g = t; g < SEL_GROUPS; g += SCAN_T) st->cursor[g] = 0u;
     __shared__ unsigned long long sm[SCAN_T / 64];
-    constexpr int NS = 4;
     const unsigned long long INF = 0x7ff0000000000000ull;
-    unsigned long long v[NS], m = 0ull;
-    const long long step = (nvox + (long long)SCAN_T * NS - 1) / ((long long)SCAN_T * NS);
+    const unsigned long long n = (unsigned long long)nvox, ns = (unsigned long long)SAMPLE_WG * SCAN_T * SAMPLES;
+    const unsigned long long step = (n + ns - 1) / ns;
+    unsigned long long v[SAMPLES], m = 0ull;
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        const long long i = ((long long)j * SCAN_T + t) * step;
-        v[j] = (unsigned long long)__double_as_longlong(emag[i < nvox ? i : 0]);
+    for (int j = 0; j < SAMPLES; ++j) {
+        const unsigned long long k = ((unsigned long long)j * SAMPLE_WG + blockIdx.x) * SCAN_T + t;
+        const unsigned long long i = k * step + (k * 2654435761ull >> 8) % step;
+        v[j] = (unsigned long long)__double_as_longlong(emag[i < n ? i : i % n]);
     }
 #pragma unroll
-    for (int j = 0; j < NS; ++j) m = v[j] < INF && v[j] > m ? v[j] : m;
+    for (int j = 0; j < SAMPLES; ++j) m = v[j] < INF && v[j] > m ? v[j] : m;
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned long long o = __shfl_down(m, off, 64);
         m = o > m ? o : m;
@@ -252,9 +258,22 @@ __global__ __launch_bounds__(SCAN_T) void k_bin_start(const double *__restrict__
     __syncthreads();
     if (t == 0) {
         for (int w = 1; w < SCAN_T / 64; ++w) m = sm[w] > m ? sm[w] : m;
-        const unsigned long long top = (m >> 52) + 2ull;
-        st->base = (top > OCT ? top - OCT : 0ull) << 52;
+        st->top[blockIdx.x] = m;
     }
+}
+
+// lowest key of the window (all lanes of a wave call this)
+__device__ __forceinline__ unsigned long long bin_base(const BinState *st)
+{
+    static_assert(SAMPLE_WG <= 64, "one wave reads them");
+    const int lane = threadIdx.x & 63;
+    unsigned long long m = lane < SAMPLE_WG ? st->top[lane] : 0ull;
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(m, off, 64);
+        m = o > m ? o : m;
+    }
+    const unsigned long long top = (m >> 52) + 2ull;
+    return (top > OCT ? top - OCT : 0ull) << 52;
 }
 
 // which labels occur (only for tables longer than LAB_FULL + 1)
@@ -324,7 +343,7 @@ __global__ __launch_bounds__(SCAN_T) void k_bin_hist(const uint8_t *__restrict__
     const int words = BODY_BINS + m.n * m.bins;
     for (int i = t; i < words; i += SCAN_T) lh[i] = 0u;
     for (int l = t; l < MAX_LABELS; l += SCAN_T) cond[l] = !sig_vox && l < nlab && table[l] > 0.0;
-    const unsigned long long base = st->base;
+    const unsigned long long base = bin_base(st);
     __syncthreads();
     const long long stride = (long long)SCAN_T * SCAN_U;
     for (long long c = (long long)blockIdx.x * stride; c < nvox; c += (long long)gridDim.x * stride) {
@@ -440,7 +459,7 @@ __global__ __launch_bounds__(SCAN_T) void k_bin_gather(const uint8_t *__restrict
     }
     for (int l = t; l < MAX_LABELS; l += SCAN_T) cond[l] = !sig_vox && l < nlab && table[l] > 0.0;
     if (t == 0) fill = 0u;
-    const unsigned long long base = st->base;
+    const unsigned long long base = bin_base(st);
     __syncthreads();
     // a key of group g: into the LDS list, or straight to its stretch when the list is full
     auto put = [&](int g, unsigned long long key) {
@@ -614,7 +633,7 @@ hipError_t launch_quantiles_bins(const uint8_t *labels, const double *table, con
     const long long chunk = (long long)SCAN_T * SCAN_U;
     long long blocks = (nvox + chunk - 1) / chunk;
     if (blocks > 256) blocks = 256;   // one workgroup per CU: its histograms fill the LDS
-    SPFD_LAUNCH(k_bin_start, dim3(1 + (HIST_WORDS + SCAN_T - 1) / SCAN_T), dim3(SCAN_T), 0, s, emag, nvox, st, hist);
+    SPFD_LAUNCH(k_bin_start, dim3(SAMPLE_WG), dim3(SCAN_T), 0, s, emag, nvox, st, hist);
     if (nlab > LAB_FULL + 1) {
         long long lb = (nvox + 4095) / 4096;
         if (lb > 2048) lb = 2048;
