@@ -64,6 +64,7 @@ struct Level {
     unsigned long long *d_cmask = nullptr;  // node columns with unknowns, per brick (structured levels)
     double *d_dinv64 = nullptr;             // inverse diagonal (0 where it vanishes), FP64 and FP32
     float *d_dinv32 = nullptr;
+    int *d_nbr27 = nullptr;                 // the 27 bricks around each brick (levels that run one-launch legs)
     int seg = 0;                            // column segment (nodes per lane) of an FP32 cycle on this level:
                                             // 4 or 8 when tuned at build, 0 = by the brick-count threshold
     Topo topo() const { return Topo{nb, d_nbr, d_cmask}; }
@@ -625,6 +626,7 @@ const float *dinv_of<float>(const Level &L) { return L.d_dinv32; }
 struct CycleDots {
     const double *q = nullptr;
     double *part = nullptr;
+    mutable int quads = 0;   // set by the cycle: the partials are this many single sums, four to a group
 };
 
 // dmode (structured levels): where the step takes the previous update from (CHEB_D_*); the ELL levels
@@ -734,14 +736,16 @@ const double *stored_w<double>(const Level &L) { return L.d_w64; }
 template <>
 const float *stored_w<float>(const Level &L) { return L.d_w32; }
 
+bool leg_level(const Ctx *c, int l, int nb);
+
 template <typename T, typename TB>
 void restrict_level(Ctx *c, int l, const TB *b, const T *x, const Scal *sc, int nb, bool fuse_first)
 {
-    // fuse_first: also the first Chebyshev step of level l+1 into its x2 (where its smoothing starts)
+    // fuse_first: also the first Chebyshev step of level l+1, into the buffer where its smoothing starts
     Level &L = c->lv[l];
     Level &C = c->lv[l + 1];
     const Batch bt = level_batch(c, l, nb);
-    T *xc = fuse_first ? (T *)C.x2 : nullptr;
+    T *xc = fuse_first ? (T *)(leg_level(c, l + 1, nb) ? C.x : C.x2) : nullptr;
     const T *dc = fuse_first ? dinv_of<T>(C) : nullptr;
     const T c0 = (T)c->cheb_c0;
     const double fb = fuse_first ? nb * (double)C.dofs * 2.0 * sizeof(T) : 0.0;
@@ -794,6 +798,96 @@ void coarse_solve(Ctx *c, const TB *b, T *x, const Scal *sc, int nb)
     HIPCHK(launch_coarse_apply<T, TB>(b, x, c->d_Ainv, c->d_cdof_node, c->ncoarse, sc, bt, c->stream));
 }
 
+// Levels of at most this many workgroups (bricks times right sides) run a leg of the cycle in one launch
+// (kernels_brick.hip); on larger ones the nodes smoothed again around each brick cost more than the launches
+// saved.  Measured on bodies of 12 to 2 mm voxels, 1 and 4 right sides, gain per cycle of both legs (mixed /
+// FP64): coarse level of degree 4: 172 workgroups 12 / 21 us, 310: 0 / 7, 620: -16 / 1; degree 2 on a coarse
+// level: 226: 5 / 7, 304: 5 / 3, 490: 2 / 0, 904: -6 / -6; finest level: 223: 10 / 7, 332: 8 / -1, 621: 2 / -5,
+// 944: -7 / -14.
+constexpr int LEG_MOST = 512;   // the largest of them (levels up to here get the table of 27 neighbours)
+
+int leg_max(bool fine, int degree, bool mixed)
+{
+    if (fine) return mixed ? LEG_MOST : 256;
+    return degree == 4 && mixed ? 256 : LEG_MOST;
+}
+
+bool leg_level(const Ctx *c, int l, int nb)
+{
+    const Level &L = c->lv[l];
+    if (L.ell || !L.d_nbr27 || l + 1 >= (int)c->lv.size()) return false;
+    const int m = level_degree(c, l);
+    if (m != 2 && !(m == 4 && l > 0)) return false;
+    if ((long long)L.nb * nb > leg_max(l == 0, m, c->opt.precision == SPFD_MIXED)) return false;
+    const Level &C = c->lv[l + 1];
+    // (an ELL coarser level: pieces of at most eight nodes; its restriction reads the FP32 weights, so not below FP16
+    // ones, and not from the finest level)
+    if (C.ell && (!C.d_memb || !L.d_agg || l == 0 || (l == 1 && L.d_w16))) return false;
+    return true;
+}
+
+// one leg of level l: down (x from its first iterate, residual restricted to level l+1) or up (correction from
+// level l+1, post-smoothing into xout; on the finest level the CG's partials)
+template <typename T>
+void brick_leg(Ctx *c, int l, bool up, const T *b, const T *xin, T *xout, const Scal *sc, int nb, double *part)
+{
+    Level &L = c->lv[l];
+    Level &C = c->lv[l + 1];
+    const bool fine = l == 0;
+    const OpArgs<T> op = level_op<T>(c, l);
+    const Batch bt = level_batch(c, l, nb);
+    BrickLeg<T> A{};
+    A.nb = L.nb;
+    A.nbr27 = L.d_nbr27;
+    A.coord = L.d_coord;
+    A.cmask = L.d_cmask;
+    A.sc = sc;
+    A.w = op.w;
+    A.stride = op.stride;
+    A.wh = op.wh;
+    A.whs = op.whs;
+    if (!op.w) {
+        A.labels = c->d_labels;
+        A.g = c->g;
+        A.table = op.table;
+        A.nlab = op.nlab;
+        for (int d = 0; d < 3; ++d) A.geo4[d] = op.geo4[d];
+    }
+    A.bscale = op.bscale;
+    A.b = b;
+    A.xin = xin;
+    A.dinv = dinv_of<T>(L);
+    A.xout = xout;
+    A.vs = bt.vs;
+    A.vsc = bt.vsc;
+    A.c0 = (T)c->cheb_c0;
+    for (int k = 0; k < 8; ++k) {
+        A.c1[k] = (T)c->cheb_c1[k];
+        A.c2[k] = (T)c->cheb_c2[k];
+    }
+    if (C.ell) {
+        A.agg = L.d_agg;
+        A.memb = C.d_memb;
+    } else {
+        A.parent_slot = L.d_parent_slot;
+    }
+    A.xc = (const T *)C.x;
+    A.scale = (T)c->opt.coarse_scale;
+    if (!up) {
+        const bool first = l + 2 < (int)c->lv.size();   // the coarser level is smoothed
+        A.bc = (T *)C.b;
+        A.xcout = first ? (T *)(leg_level(c, l + 1, nb) ? C.x : C.x2) : nullptr;
+        A.dinv_c = first ? dinv_of<T>(C) : nullptr;
+    }
+    A.part = part;
+    A.ps = bt.ps;
+    // the leg's vectors once: right side, iterates, operator, the coarser level's vectors
+    const double per = (fine && !up ? 2.0 : 3.0) * sizeof(T) + op_bytes<T>(c, l);
+    TScope ts(c, fine ? (up ? SPFD_K_DOTS : SPFD_K_SMOOTH0) : SPFD_K_COARSE,
+              nb * ((double)L.dofs * per + (double)C.dofs * (up ? 1.0 : 2.0) * sizeof(T)));
+    HIPCHK(launch_brick_leg<T>(A, level_degree(c, l), fine, up, nb, c->stream));
+}
+
 // z = B r for a batch of nb right sides: one V-cycle (T = arithmetic of the
 // cycle); r is the outer residual (FP64, or its FP32 copy for an FP32 cycle)
 // dots (optional): the finest post-smoothing step also writes the partials of
@@ -821,6 +915,10 @@ bool vcycle(Ctx *c, const TR *r, T *z, const Scal *sc, int nb, const CycleDots *
         coarse_solve<T, TR>(c, r, z, sc, nb);  // single level: the dense solve is exact
         return false;
     }
+    // levels that run each leg in one launch (the finest reads r in the cycle's type and forms no z.q)
+    auto leg = [&](int l) {
+        return leg_level(c, l, nb) && (l > 0 || (std::is_same<T, TR>::value && !(dots && dots->q)));
+    };
     // downward: pre-smooth, restrict the residual.  The smoother ping-pongs
     // between two buffers; starting in x2 makes the (2m-1) swaps of a level end
     // in the level's output buffer (z on the finest level, x below).
@@ -828,6 +926,12 @@ bool vcycle(Ctx *c, const TR *r, T *z, const Scal *sc, int nb, const CycleDots *
         Level &L = c->lv[l];
         T *cur = (T *)L.x2;
         T *other = l == 0 ? z : (T *)L.x;
+        if (leg(l)) {
+            // one launch: the first iterate (in L.x, stored by the finer level's restriction) -> L.x2
+            brick_leg<T>(c, l, false, l == 0 ? (const T *)r : (const T *)L.b, (const T *)L.x, (T *)L.x2, sc, nb, nullptr);
+            res[l] = (T *)L.x2;
+            continue;
+        }
         // the restriction stores the next level's first Chebyshev step unless that level is the coarsest
         const bool fuse = l + 2 < nl;
         if (l == 0) {
@@ -846,6 +950,12 @@ bool vcycle(Ctx *c, const TR *r, T *z, const Scal *sc, int nb, const CycleDots *
     // upward: prolongate and correct, post-smooth
     for (int l = nl - 2; l >= 0; --l) {
         Level &L = c->lv[l];
+        if (leg(l)) {
+            brick_leg<T>(c, l, true, l == 0 ? (const T *)r : (const T *)L.b, res[l], l == 0 ? z : (T *)L.x, sc, nb,
+                         l == 0 && dots ? dots->part : nullptr);
+            if (l == 0 && dots) dots->quads = brick_dot_parts<T>(L.nb);
+            continue;
+        }
         T *cur = res[l];
         T *other = (cur == (T *)L.x2) ? (l == 0 ? z : (T *)L.x) : (T *)L.x2;
         // between two structured or two ELL levels the prolongation rides on the first post-smoothing step
@@ -866,7 +976,8 @@ bool vcycle(Ctx *c, const TR *r, T *z, const Scal *sc, int nb, const CycleDots *
 // own count (bricks, or groups of the CG step), and the finisher sums just those.
 enum { ROWS_BRICKS = 1, ROWS_CG_GROUPS = 2, ROWS_RU_GROUPS = 3 };
 
-void finish(Ctx *c, int n, int mode, Scal *sc, int max_iter, int nb = 1, Scal *mirror = nullptr, int rows = 0)
+void finish(Ctx *c, int n, int mode, Scal *sc, int max_iter, int nb = 1, Scal *mirror = nullptr, int rows = 0,
+            int quads = 0)
 {
     TScope ts(c, SPFD_K_FINISH, nb * (double)n * 8.0 * (mode == FIN_BETA ? 2 : 1));
     FinRows fr{};
@@ -878,7 +989,7 @@ void finish(Ctx *c, int n, int mode, Scal *sc, int max_iter, int nb = 1, Scal *m
                                                : cg_step_parts(c->mcount[m]);
     }
     HIPCHK(launch_finish(c->d_part, n, mode, sc, max_iter, c->stream, nullptr, nullptr, 0, nb, c->pstride, mirror,
-                         fr.used ? &fr : nullptr));
+                         fr.used ? &fr : nullptr, quads));
 }
 
 // The finest level as the CG kernels see it: all bricks, or one launch row per packed model (its bricks,
@@ -1381,6 +1492,10 @@ spfd_status do_build(Ctx *c)
         if (L.ell) {
             HIPCHK(launch_dinv_ell(L.nrow, L.K, L.d_col, L.d_val64, L.d_dinv64, L.d_dinv32, c->side));
         } else if (L.nb > 0) {
+            if (L.nb <= LEG_MOST) {
+                L.d_nbr27 = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 27);
+                HIPCHK(launch_nbr27(L.d_slot_of, L.d_coord, L.nb, L.G, L.d_nbr27, c->side));
+            }
             L.d_cmask = dalloc<unsigned long long>(c, c->hier_allocs, L.nb);
             HIPCHK(launch_col_masks(L.d_w64, L.nodes(), L.topo(), L.d_cmask, c->side));
             HIPCHK(launch_dinv_struct(L.d_w64, L.nodes(), Topo{L.nb, L.d_nbr}, L.d_dinv64, L.d_dinv32, c->side));
@@ -1526,7 +1641,7 @@ void pcg_begin(Ctx *c, Scal *sc, int nb)
             vcycle<T, double>(c, c->d_r, z, nullptr, 1, nullptr);
     } else if (r32 ? vcycle<T, float>(c, c->d_r32, z, sc, nb, &dots, bs)
                    : vcycle<T, double>(c, c->d_r, z, sc, nb, &dots)) {
-        finish(c, cheb_dot_parts<T>(topo.nb), FIN_BETA0, sc, 0, nb);
+        finish(c, cheb_dot_parts<T>(topo.nb), FIN_BETA0, sc, 0, nb, nullptr, 0, dots.quads);
         return;
     }
     {
@@ -1574,7 +1689,7 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
                         : vcycle<T, double>(c, c->d_r, z, sc, nb, &dots);
         }
         if (fused) {
-            finish(c, cheb_dot_parts<T>(topo.nb), bmode, sc, 0, nb);
+            finish(c, cheb_dot_parts<T>(topo.nb), bmode, sc, 0, nb, nullptr, 0, dots.quads);
         } else {
             {
                 TScope ts(c, SPFD_K_DOTS, n0 * (wz + (flex ? 16.0 : 8.0)));

@@ -121,13 +121,15 @@ enum {
 // had already stopped: the host reads them after the stream has passed here.
 // rows (nullable, used != 0): row r sums only its first n[r] partials (packed models: each model's own
 // count of bricks or groups); the z.q partials of FIN_BETA start at part + n in every row
+// quads != 0: the partials are 4 n single sums, quads of them given (the rest count as 0), each four added in
+// order to one of the n sums first (not with FIN_BETA)
 struct FinRows {
     int used;
     int n[MAX_MODELS];
 };
 hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_iter, hipStream_t s,
                          double *means = nullptr, const int *counts = nullptr, int comp = 0, int nbatch = 1,
-                         int ps = 0, Scal *mirror = nullptr, const FinRows *rows = nullptr);
+                         int ps = 0, Scal *mirror = nullptr, const FinRows *rows = nullptr, int quads = 0);
 
 template <typename T>
 hipError_t launch_fill(T *x, long long n, T v, hipStream_t s);
@@ -247,6 +249,50 @@ hipError_t launch_prolong(Topo topo, T *x, const T *xc, const int *parent_slot, 
 template <typename T, typename TB>
 hipError_t launch_coarse_apply(const TB *bc, T *xc, const double *Ainv, const int *node_of_dof, int n,
                                const Scal *sc, const Batch &bt, hipStream_t s);
+
+// ---------------------------------------------------------------- one leg of the cycle per launch (small levels)
+// Operands of launch_brick_leg, on a structured level of nb bricks (vectors [nrhs][vs], the coarser level's
+// [nrhs][vsc]).
+template <typename T>
+struct BrickLeg {
+    int nb;
+    const int *nbr27;                  // launch_nbr27
+    const int4 *coord;
+    const unsigned long long *cmask;
+    const Scal *sc;
+    // operator: stored weights (w, or FP16 bits wh times whs) or (labels given) the label form
+    const T *w;
+    long long stride;
+    const uint16_t *wh;
+    float whs;
+    const uint8_t *labels;
+    Grid g;
+    const T *table;
+    int nlab;
+    T geo4[3];
+    int bscale;                        // b is held as D^-1 b (finest level)
+    // vectors: right side, iterate in and out (different buffers); the finest level's downward leg starts
+    // from c0 D^-1 b and reads dinv (not with bscale) in place of xin
+    const T *b, *xin, *dinv;
+    T *xout;
+    long long vs, vsc;
+    T c0, c1[8], c2[8];                // step coefficients (OpArgs' smoothers)
+    // coarser level: structured (parent_slot) or ELL (agg, and for the downward leg memb)
+    const int *parent_slot, *agg, *memb;
+    const T *xc;                       // up: x += scale P xc
+    T scale;
+    T *bc, *xcout;                     // down: P^T (b - A x); its first iterate c0 dinv_c bc (nullable)
+    const T *dinv_c;
+    // up on the finest level (nullable): partials of x.b per column segment, brick_dot_parts<T>(nb) of them in
+    // groups of four, the column kernels' partials
+    double *part;
+    int ps;
+};
+template <typename T>
+constexpr int brick_dot_parts(int nb) { return nb * (sizeof(T) == 4 ? 1 : 2); }
+template <typename T>
+hipError_t launch_brick_leg(const BrickLeg<T> &A, int degree, int fine, int up, int nrhs, hipStream_t s);
+hipError_t launch_nbr27(const int *slot_of, const int4 *coord, int nb, const int G[3], int *out, hipStream_t s);
 
 // ---------------------------------------------------------------- several voxel models in one handle
 // model boxes in the packed grid: model m has nx x ny x nz voxels from voxel layer zoff on

@@ -920,7 +920,7 @@ __device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc)
 // the second set of partials (z.q) starts at part + n in every row
 __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part, int n, int mode, Scal *sc,
                                                  int max_iter, double *means, const int *counts, int comp, int ps,
-                                                 Scal *mirror, FinRows rows)
+                                                 Scal *mirror, FinRows rows, int quads)
 {
     __shared__ double red[16];
     part += (long long)blockIdx.x * ps;
@@ -940,6 +940,14 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = i0 + u * nt;
+            if (quads) {
+                double p[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) p[k] = 4 * i + k < quads ? part[4 * i + k] : 0.0;
+                v[u] = ((p[0] + p[1]) + p[2]) + p[3];
+                w[u] = 0.0;
+                continue;
+            }
             v[u] = i < nr ? part[i] : 0.0;
             w[u] = mode == FIN_BETA && i < nr ? part[n + i] : 0.0;
         }
@@ -1013,13 +1021,14 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
 }
 
 hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_iter, hipStream_t s, double *means,
-                         const int *counts, int comp, int nbatch, int ps, Scal *mirror, const FinRows *rows)
+                         const int *counts, int comp, int nbatch, int ps, Scal *mirror, const FinRows *rows, int quads)
 {
     if (mirror && !sc) return hipErrorInvalidValue;
+    if (quads && (mode == FIN_BETA || quads > 4 * n || (rows && rows->used))) return hipErrorInvalidValue;
     if (rows && rows->used && nbatch > MAX_MODELS) return hipErrorInvalidValue;
     const FinRows fr = rows ? *rows : FinRows{};
     SPFD_LAUNCH(k_finish, dim3(nbatch), dim3(1024), 0, s, part, n, mode, sc, max_iter, means, counts, comp, ps,
-                mirror, fr);
+                mirror, fr, quads);
     return hipGetLastError();
 }
 

@@ -1,0 +1,49 @@
+"""One launch per leg of the cycle (small levels) against one launch per smoothing step: a source solved alone
+(few workgroups: legs) and in a batch large enough that every level takes the separate kernels must give the
+same bits, on every kind of operator, degree, coarser level and precision the legs have."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2010_12879_amd as P  # noqa: E402
+
+DEV = torch.device("cuda:0")
+MOST = 512   # workgroups (bricks x right sides) above which no level runs legs
+
+
+def _dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("opts", [{}, {"voxel": True}, {"level1_degree": 2}, {"level1_fp32": True}, {"split": False},
+                                  {"smooth_degree": 4, "coarsest_max": 48}, {"coarsest_max": 48},
+                                  {"split_level": 1, "coarsest_max": 48}, {"smoother": "chebyshev4"},
+                                  {"smoother": "l1jacobi", "voxel": True}], ids=str)
+def test_legs_equal_separate_kernels(opts, prec):
+    print(f"case legs {opts} {prec}", flush=True)
+    opts = dict(opts)
+    voxel = opts.pop("voxel", False)
+    w = W.random_ellipsoid_phantom(45, 38, 52, seed=47, n_ell=10, semi_range=(3.0, 10.0))
+    sig = _dev(w.sigma_voxel() * np.random.default_rng(3).uniform(0.8, 1.2, w.labels.shape)) if voxel else w.sigma_table
+    s = P.Solver(_dev(w.labels), sig, w.h, precision=prec, **opts)
+    bricks = [s_["slots"] // 512 for s_ in (P.spfd_level_info(s.handle, k) for k in range(s.info()["n_levels"]))
+              if s_["kind"] == "structured"]
+    assert bricks[0] <= 256, bricks               # alone, every structured level runs legs
+    n = MOST // bricks[-1] + 1 if len(bricks) == 1 else MOST // min(bricks) + 1
+    n = min(n, 80)
+    assert n * bricks[min(1, len(bricks) - 1)] > MOST, (n, bricks)   # the batch: not the finest nor the first coarse one
+    a = _dev(w.a)
+    srcs = torch.stack([a * (1.0 + 0.01 * k) for k in range(n)])
+    one, info = s.solve(srcs[1].contiguous(), tol=1e-10, max_iter=300)
+    many, infos = s.solve(srcs, tol=1e-10, max_iter=300)
+    s.close()
+    assert info["status"] == "OK" and infos[1]["iterations"] == info["iterations"]
+    assert torch.equal(one, many[1])
