@@ -38,6 +38,8 @@ struct Scal {
     int hcount;      // CG steps of the current window of kept search directions (the next one's slot)
     int happlied;    // of these, the directions already added to x (an update of x before the window is full)
     int pad;
+    double rzn;      // r.z of the step under way, where the CG kernels finish the sums themselves: the CG step reads
+                     // rz and leaves the new value here, the residual update reads it here and moves it to rz
 };
 
 constexpr int MAX_MODELS = 16;     // voxel models packed into one handle

@@ -156,6 +156,7 @@ struct Ctx {
     unsigned long long *d_sel_cand = nullptr;
     double *d_sel_out = nullptr;
     double *d_part = nullptr;
+    double *d_part2 = nullptr;   // p.q partials where the residual update adds them up itself
     int pstride = 0;          // partial sums per right side
     int *d_again = nullptr;   // per right side: restart from the true residual
     int nbat = 0;             // right sides the solve buffers hold
@@ -1269,6 +1270,7 @@ void alloc_cycle_buffers(Ctx *c, int nb)
     c->pstride = 2 * c->lv[0].nb + 64;
     c->d_part = dalloc<double>(c, c->rhs_allocs, (size_t)c->pstride * nb);
     zero_add(c, zl, c->d_part, (size_t)c->pstride * nb * sizeof(double));
+    c->d_part2 = dalloc<double>(c, c->rhs_allocs, (size_t)FIN_SMALL * nb);
     c->d_nostop = dalloc<Scal>(c, c->rhs_allocs, nb);
     zero_add(c, zl, c->d_nostop, (size_t)nb * sizeof(Scal));
     zero_flush(c, zl);
@@ -1651,6 +1653,12 @@ void pcg_begin(Ctx *c, Scal *sc, int nb)
     finish(c, topo_count(topo), FIN_BETA0, sc, 0, nb, nullptr, ROWS_BRICKS);
 }
 
+// Workgroups of a CG kernel (groups of two bricks times launch rows) up to which the kernels add up the partial sums
+// before them themselves: every workgroup reads them all.  Measured per iteration on bodies of 30 to 8 mm voxels:
+// 15 workgroups 47 -> 44 us, 112: 71 -> 69, 166: 75 -> 73, 448: 86 -> 85, 664: 106 -> 106; with up to 1,024 partials per
+// row (5 mm, 891 of them) 125 -> 141.
+constexpr int OWN_SUMS_MOST = 512;
+
 // CG step `it`: for it >= 1 first z = B r (the cycle, which also forms z.r and, for the flexible beta,
 // z.q) and beta; then p = z + beta p, the deferred x update and q = A p, alpha, and the residual update
 // with its norm, which decides the stop.  The step ends at the stop decision, so the step that converges
@@ -1672,6 +1680,10 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
     // in the cycle's precision
     const int nh = c->phist_len;
     T *ph = (T *)c->d_phist;
+    // few partial sums and workgroups: the CG step and the residual update add the sums up themselves (no finisher
+    // in between)
+    const bool own_sums = !c->cg_flexible && cg_step_parts(nmax) <= FIN_SMALL && cg_step_parts(nmax) * nb <= OWN_SUMS_MOST;
+    FinIn beta_in{}, alpha_in{};
     if (it > 0) {
         const bool flex = c->cg_flexible;
         const int bmode = flex ? FIN_BETA : FIN_BETA_STD;
@@ -1688,15 +1700,17 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
             fused = r32 ? vcycle<T, float>(c, r32, z, sc, nb, &dots, bs)
                         : vcycle<T, double>(c, c->d_r, z, sc, nb, &dots);
         }
-        if (fused) {
-            finish(c, cheb_dot_parts<T>(topo.nb), bmode, sc, 0, nb, nullptr, 0, dots.quads);
-        } else {
-            {
-                TScope ts(c, SPFD_K_DOTS, n0 * (wz + (flex ? 16.0 : 8.0)));
-                HIPCHK(launch_dots<T>(topo, z, c->d_r, c->d_q, c->d_part, sc, flex ? 0 : 1, bt, c->stream));
-            }
-            finish(c, nmax, bmode, sc, 0, nb, nullptr, ROWS_BRICKS);
+        int nbeta = cheb_dot_parts<T>(topo.nb), brows = 0;
+        if (!fused) {
+            TScope ts(c, SPFD_K_DOTS, n0 * (wz + (flex ? 16.0 : 8.0)));
+            HIPCHK(launch_dots<T>(topo, z, c->d_r, c->d_q, c->d_part, sc, flex ? 0 : 1, bt, c->stream));
+            nbeta = nmax;
+            brows = ROWS_BRICKS;
         }
+        if (own_sums && nbeta <= (dots.quads ? FIN_QUADS : FIN_SMALL))
+            beta_in = FinIn{c->d_part, nbeta, dots.quads, c->np ? 1 : 0, c->pstride};
+        else
+            finish(c, nbeta, bmode, sc, 0, nb, nullptr, brows, dots.quads);
     }
     // p_k = z_k + beta p_{k-1}, q_k = A p_k.  Only the flexible beta reads q_k later (z.q); with the
     // standard beta the residual update forms A p_k again from p_k instead.  x is updated at the end of
@@ -1705,10 +1719,15 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
     {
         // z, p_{k-1}, p_k in the cycle's precision; q in FP64
         TScope ts(c, SPFD_K_SPMV, n0 * (wz + (it ? 2.0 * wz : wz) + (keep_q ? 8.0 : 0.0) + op_bytes<double>(c, 0)));
-        HIPCHK(launch_cg_step<T>(op, topo, z, ph, c->phist_stride, nh, keep_q ? c->d_q : nullptr, c->d_part, sc,
-                                 it == 0, bt, c->stream));
+        Batch bq = bt;
+        if (own_sums) bq.ps = FIN_SMALL;
+        HIPCHK(launch_cg_step<T>(op, topo, z, ph, c->phist_stride, nh, keep_q ? c->d_q : nullptr,
+                                 own_sums ? c->d_part2 : c->d_part, sc, it == 0, bq, c->stream, beta_in));
     }
-    finish(c, cg_step_parts(nmax), FIN_ALPHA, sc, 0, nb, nullptr, ROWS_CG_GROUPS);
+    if (own_sums)
+        alpha_in = FinIn{c->d_part2, cg_step_parts(nmax), 0, c->np ? 2 : 0, FIN_SMALL};
+    else
+        finish(c, cg_step_parts(nmax), FIN_ALPHA, sc, 0, nb, nullptr, ROWS_CG_GROUPS);
     if (keep_q) {
         {
             TScope ts(c, SPFD_K_UPDATE, n0 * (24.0 + (r32 ? 4.0 : 0.0)));
@@ -1720,7 +1739,7 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
             // r (read and written), p_k and the operator; the FP32 copy of r
             TScope ts(c, SPFD_K_UPDATE, n0 * (16.0 + wz + op_bytes<double>(c, 0) + (r32 ? 4.0 : 0.0)));
             HIPCHK(launch_col_rupdate<T>(op, topo, ph, c->phist_stride, nh, c->d_r, r32, c->d_part, sc, bt, c->stream,
-                                         r32 && r32_scaled(c), c->d_ahist));
+                                         r32 && r32_scaled(c), c->d_ahist, alpha_in, beta_in.n > 0));
         }
         finish(c, rupdate_parts(nmax), FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_RU_GROUPS);
     }

@@ -176,6 +176,16 @@ hipError_t launch_fg_xupdate(double *x, const TZ *Z, long long ldz, long long n,
 template <typename TZ>
 hipError_t launch_spmv(const OpArgs<double> &op, Topo topo, const TZ *z, double *w, const Scal *sc, const Batch &bt,
                        hipStream_t s);
+// Partial sums that a CG kernel adds up itself (every workgroup, in launch_finish's order) in place of a
+// launch_finish before it: n (0: none) per launch row, or with quads 4 n single sums as in launch_finish; with
+// packed models each row's own count (rows: 1 bricks, 2 groups of the CG step).  part must not be the array the
+// kernel writes its own partials to.
+constexpr int FIN_SMALL = 256;    // most partials per row that are added up this way
+constexpr int FIN_QUADS = 128;    // ... in groups of four single sums
+struct FinIn {
+    const double *part = nullptr;
+    int n = 0, quads = 0, rows = 0, ps = 0;
+};
 // number of partial sums launch_cg_step (launch_col_rupdate) writes per right side (nb: bricks per launch
 // row, topo_count)
 int cg_step_parts(int nb);
@@ -185,7 +195,8 @@ int rupdate_parts(int nb);
 // p = z + beta p_prev into the current slot, q = A p (q nullable: not stored), p.q partials
 template <typename TZ>
 hipError_t launch_cg_step(const OpArgs<double> &op, Topo topo, const TZ *z, TZ *ph, long long hs, int nh, double *q,
-                          double *part, Scal *sc, int first, const Batch &bt, hipStream_t s);
+                          double *part, Scal *sc, int first, const Batch &bt, hipStream_t s,
+                          const FinIn &fin = FinIn{});   // fin: r.z, for beta
 // x += sum_j alpha_j p_j over the window's slots happlied .. hcount-1, in step order; then (full) an empty
 // window, else happlied = hcount
 template <typename TP>
@@ -199,8 +210,9 @@ hipError_t launch_rupdate(Topo topo, double *r, const double *q, double *part, S
 // into that slot
 template <typename TZ>
 hipError_t launch_col_rupdate(const OpArgs<double> &op, Topo topo, const TZ *ph, long long hs, int nh, double *r,
-                              float *r32, double *part, const Scal *sc, const Batch &bt, hipStream_t s, int r32_scaled,
-                              double *ahist);
+                              float *r32, double *part, Scal *sc, const Batch &bt, hipStream_t s, int r32_scaled,
+                              double *ahist, const FinIn &fin = FinIn{}, int rz_next = 0);   // fin: p.q, for alpha
+                              // (rz_next: r.z is in Scal::rzn)
 // r = b - A x (r nullable) and the partials of ||r||^2 (cg_step_parts(nb) per right side).  b has its own
 // batch stride bvs (the right sides may live apart from the solve vectors).
 hipError_t launch_resid(const OpArgs<double> &op, Topo topo, const double *b, const double *x, double *r,

@@ -880,7 +880,7 @@ __global__ void k_scal_init(Scal *sc, double tol, int use_x0)
         sc->rr = bb;
         sc->tol2 = tol * tol * bb;
         sc->done = bb > 0.0 ? 0 : 1;
-        sc->iters = 0; sc->status = 0; sc->hcount = 0; sc->happlied = 0; sc->pad = 0;
+        sc->iters = 0; sc->status = 0; sc->hcount = 0; sc->happlied = 0; sc->pad = 0; sc->rzn = 0.0;
     }
 }
 

@@ -825,10 +825,62 @@ __device__ __forceinline__ float fma_t<float>(float a, float b, float c) { retur
 template <>
 __device__ __forceinline__ double fma_t<double>(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-template <typename TZ, int ZPL, bool LABEL, bool FIRST>
+// The sum k_finish forms of a row's partials, for up to 64 NC of them (one per thread there): the sums of 64
+// consecutive partials, added in order.  Where a model's sums are that few, the kernel that needs them adds them
+// up itself, every wave alike and without a barrier, its loads in flight with the wave's own: a finisher kernel
+// between two kernels costs 4 to 5 us with its gap.  All lanes of the wave call both.
+template <int NC>
+struct RowSum {
+    double v[NC];
+
+    __device__ __forceinline__ void load(const FinIn &fin, const Topo &topo, int zpl)
+    {
+        int n = fin.n;
+        if (fin.rows) {   // packed models: the row's own bricks, or groups of the CG step
+            const int cnt = topo.prange[blockIdx.y].y, per = CWAVES * zpl / 8;
+            n = fin.rows == 1 ? cnt : (cnt + per - 1) / per;
+        }
+        const double *part = fin.part + (long long)blockIdx.y * fin.ps;
+        const int lane = threadIdx.x & 63;
+        if (fin.quads) {   // (FIN_QUADS sums at most)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) v[k] = 0.0;
+#pragma unroll
+            for (int k = 0; k < FIN_QUADS / 64; ++k) {
+                double p[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int i = 4 * (64 * k + lane) + m;
+                    p[m] = i < fin.quads ? part[i] : 0.0;
+                }
+                v[k] = ((p[0] + p[1]) + p[2]) + p[3];
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < NC; ++k) v[k] = part[64 * k + lane < n ? 64 * k + lane : 0];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) v[k] = 64 * k + lane < n ? v[k] : 0.0;
+        }
+    }
+
+    __device__ __forceinline__ double total()
+    {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) v[k] = wave_sum(v[k]);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) t += __shfl(v[k], 0, 64);
+        return t;
+    }
+};
+template <>
+struct RowSum<0> {};
+
+// FIN > 0: beta from the partials of r.z (fin), up to 64 FIN of them (RowSum)
+template <typename TZ, int ZPL, bool LABEL, bool FIRST, int FIN>
 __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Topo topo, const TZ *__restrict__ zv,
                                                           TZ *ph, long long hs, int nh, double *__restrict__ q,
-                                                          double *part, Scal *sc, long long vs, int ps)
+                                                          double *part, Scal *sc, long long vs, int ps, FinIn fin)
 {
     constexpr bool WIDE = std::is_same<TZ, double>::value;
     double *lds = col_lds<double, ZPL, LABEL>();
@@ -843,6 +895,12 @@ __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Top
     TZ *__restrict__ pout = ph + (long long)s.hc * hs + blockIdx.y * vs;
     if (q) q += blockIdx.y * vs;
     part += (long long)blockIdx.y * ps;
+    RowSum<FIN> rs;
+    double rz = 0.0;
+    if constexpr (FIN > 0) {
+        rs.load(fin, topo, ZPL);
+        rz = sc->rz;
+    }
     double dot = 0.0;
     if (s.bk >= 0) {
         SegOp<double, ZPL, LABEL> A;
@@ -851,7 +909,24 @@ __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Top
         Z.template load<WIDE>(zv, s);
         SegVals<TZ, ZPL> Pi;
         if constexpr (!FIRST) Pi.template load<WIDE>(pin, s);
-        const TZ beta = FIRST ? TZ(0) : (TZ)sc->beta;
+        TZ beta = TZ(0);
+        if constexpr (FIN > 0) {
+            const double rzn = rs.total(), beta64 = rzn / rz;
+            const bool bad = !(rzn > 0.0) || !isfinite(beta64);
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                if (bad) {
+                    sc->status = 6;
+                    sc->done = 1;
+                }
+                sc->zq = 0.0;
+                sc->rzn = rzn;
+                sc->beta = bad ? 0.0 : beta64;
+            }
+            beta = (TZ)beta64;
+            if (bad) return;   // (every wave of the row returns here or has no brick; the partials are not read)
+        } else if constexpr (!FIRST) {
+            beta = (TZ)sc->beta;
+        }
         // p_k on the segment, the face columns and the z ends
         SegVals<TZ, ZPL> P;
 #pragma unroll
@@ -901,20 +976,30 @@ __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Top
 // and order of operations, so it equals the q_k that step formed for p.q bit
 // for bit; reading p_k in the cycle's precision and the labels costs fewer
 // bytes than storing q_k in FP64 and reading it back.
-template <typename TZ, int ZPL, bool LABEL>
+// FIN > 0: alpha from the partials of p.q (fin), up to 64 FIN of them (RowSum); r.z in Scal::rzn when rz_next
+template <typename TZ, int ZPL, bool LABEL, int FIN>
 __global__ __launch_bounds__(CTHREADS) void k_col_rupdate(OpArgs<double> op, Topo topo, const TZ *ph, long long hs,
                                                           int nh, double *__restrict__ r, float *__restrict__ r32,
-                                                          double *part, const Scal *sc, long long vs, int ps,
-                                                          int r32_scaled, double *ahist)
+                                                          double *part, Scal *sc, long long vs, int ps,
+                                                          int r32_scaled, double *ahist, FinIn fin, int rz_next)
 {
     constexpr bool WIDE = std::is_same<TZ, double>::value;
     double *lds = col_lds<double, ZPL, LABEL>();
     __shared__ double red[CWAVES];
     const Seg<ZPL> s = make_seg<ZPL>(topo, sc);
     if (s.stop || s.hc < 0 || s.hc >= nh) return;
-    const double alpha = sc[blockIdx.y].alpha;
+    double alpha = 0.0, rz = 0.0;
+    RowSum<FIN> rs;
+    Scal *row = sc + blockIdx.y;
+    if constexpr (FIN > 0) {
+        if (s.grp < 0) return;
+        rs.load(fin, topo, ZPL);
+        rz = rz_next ? row->rzn : row->rz;
+    } else {
+        alpha = row->alpha;
+    }
     // the step size of this search direction, for the update of x at the end of the window
-    if (blockIdx.x == 0 && threadIdx.x == 0) ahist[blockIdx.y * nh + s.hc] = alpha;
+    if (FIN == 0 && blockIdx.x == 0 && threadIdx.x == 0) ahist[blockIdx.y * nh + s.hc] = alpha;
     if (s.grp < 0) return;
     const TZ *__restrict__ pv = ph + (long long)s.hc * hs + blockIdx.y * vs;
     r += blockIdx.y * vs;
@@ -931,6 +1016,23 @@ __global__ __launch_bounds__(CTHREADS) void k_col_rupdate(OpArgs<double> op, Top
         if (s.active)
 #pragma unroll
             for (int z = 0; z < ZPL; ++z) rv[z] = r[s.self + 64 * z];
+        if constexpr (FIN > 0) {
+            const double pq = rs.total();
+            alpha = rz / pq;
+            const bool bad = !(pq > 0.0) || !isfinite(alpha);
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                if (bad) {
+                    row->status = 6;
+                    row->done = 1;
+                } else {
+                    ahist[blockIdx.y * nh + s.hc] = alpha;
+                }
+                row->pq = pq;
+                row->alpha = bad ? 0.0 : alpha;
+                if (rz_next) row->rz = rz;
+            }
+            if (bad) return;   // (as in the CG step)
+        }
         A.stage(op, s);
 #pragma unroll
         for (int z = 0; z < ZPL; ++z) {
@@ -1217,20 +1319,24 @@ hipError_t launch_resid_restrict(const OpArgs<T> &op, Topo topo, const TB *b, co
 
 template <typename TZ>
 hipError_t launch_cg_step(const OpArgs<double> &op, Topo topo, const TZ *z, TZ *ph, long long hs, int nh, double *q,
-                          double *part, Scal *sc, int first, const Batch &bt, hipStream_t s)
+                          double *part, Scal *sc, int first, const Batch &bt, hipStream_t s, const FinIn &fin)
 {
     if (topo.nb <= 0) return hipSuccess;
     if (!col_args_ok(topo, sc)) return hipErrorInvalidValue;
     if (!ph || nh < 2 || nh > MAX_PHIST) return hipErrorInvalidValue;
     const dim3 g = col_grid<ZPL_CG>(topo_count(topo), bt.n);
-#define SPFD_CG(LB, F) SPFD_LAUNCH((k_col_cg_step<TZ, ZPL_CG, LB, F>), g, dim3(CTHREADS), 0, s, op, topo, z, ph, hs, \
-                                   nh, q, part, sc, bt.vs, bt.ps)
+    if (fin.n > FIN_SMALL || (fin.quads && fin.n > FIN_QUADS) || (fin.n > 0 && (first || q || fin.part == part)))
+        return hipErrorInvalidValue;
+#define SPFD_CG(LB, F, FN) SPFD_LAUNCH((k_col_cg_step<TZ, ZPL_CG, LB, F, FN>), g, dim3(CTHREADS), 0, s, op, topo, z, \
+                                       ph, hs, nh, q, part, sc, bt.vs, bt.ps, fin)
     if (op.w) {
-        if (first) SPFD_CG(false, true);
-        else SPFD_CG(false, false);
+        if (first) SPFD_CG(false, true, 0);
+        else if (fin.n > 0) SPFD_CG(false, false, FIN_SMALL / 64);
+        else SPFD_CG(false, false, 0);
     } else {
-        if (first) SPFD_CG(true, true);
-        else SPFD_CG(true, false);
+        if (first) SPFD_CG(true, true, 0);
+        else if (fin.n > 0) SPFD_CG(true, false, FIN_SMALL / 64);
+        else SPFD_CG(true, false, 0);
     }
 #undef SPFD_CG
     return hipGetLastError();
@@ -1238,28 +1344,33 @@ hipError_t launch_cg_step(const OpArgs<double> &op, Topo topo, const TZ *z, TZ *
 
 template <typename TZ>
 hipError_t launch_col_rupdate(const OpArgs<double> &op, Topo topo, const TZ *ph, long long hs, int nh, double *r,
-                              float *r32, double *part, const Scal *sc, const Batch &bt, hipStream_t s, int r32_scaled,
-                              double *ahist)
+                              float *r32, double *part, Scal *sc, const Batch &bt, hipStream_t s, int r32_scaled,
+                              double *ahist, const FinIn &fin, int rz_next)
 {
     if (topo.nb <= 0) return hipSuccess;
     if (!col_args_ok(topo, sc)) return hipErrorInvalidValue;
     if (r32_scaled && !r32) return hipErrorInvalidValue;
     if (!ph || !ahist || nh < 2 || nh > MAX_PHIST) return hipErrorInvalidValue;
+    if (fin.n > FIN_SMALL || fin.quads || (fin.n > 0 && fin.part == part)) return hipErrorInvalidValue;
     const dim3 g = col_grid<ZPL_RU>(topo_count(topo), bt.n);
-    if (op.w)
-        SPFD_LAUNCH((k_col_rupdate<TZ, ZPL_RU, false>), g, dim3(CTHREADS), 0, s, op, topo, ph, hs, nh, r, r32, part,
-                    sc, bt.vs, bt.ps, r32_scaled, ahist);
-    else
-        SPFD_LAUNCH((k_col_rupdate<TZ, ZPL_RU, true>), g, dim3(CTHREADS), 0, s, op, topo, ph, hs, nh, r, r32, part,
-                    sc, bt.vs, bt.ps, r32_scaled, ahist);
+#define SPFD_RU(LB, FN) SPFD_LAUNCH((k_col_rupdate<TZ, ZPL_RU, LB, FN>), g, dim3(CTHREADS), 0, s, op, topo, ph, hs, nh, \
+                                    r, r32, part, sc, bt.vs, bt.ps, r32_scaled, ahist, fin, rz_next)
+    if (op.w) {
+        if (fin.n > 0) SPFD_RU(false, FIN_SMALL / 64);
+        else SPFD_RU(false, 0);
+    } else {
+        if (fin.n > 0) SPFD_RU(true, FIN_SMALL / 64);
+        else SPFD_RU(true, 0);
+    }
+#undef SPFD_RU
     return hipGetLastError();
 }
 template hipError_t launch_col_rupdate<double>(const OpArgs<double> &, Topo, const double *, long long, int, double *,
-                                               float *, double *, const Scal *, const Batch &, hipStream_t, int,
-                                               double *);
+                                               float *, double *, Scal *, const Batch &, hipStream_t, int, double *,
+                                               const FinIn &, int);
 template hipError_t launch_col_rupdate<float>(const OpArgs<double> &, Topo, const float *, long long, int, double *,
-                                              float *, double *, const Scal *, const Batch &, hipStream_t, int,
-                                              double *);
+                                              float *, double *, Scal *, const Batch &, hipStream_t, int, double *,
+                                              const FinIn &, int);
 
 hipError_t launch_resid(const OpArgs<double> &op, Topo topo, const double *b, const double *x, double *r,
                         double *part, long long bvs, const Batch &bt, hipStream_t s)
@@ -1308,8 +1419,8 @@ SPFD_INST_COL(float, float)
 SPFD_INST_COL(float, double)
 
 template hipError_t launch_cg_step<double>(const OpArgs<double> &, Topo, const double *, double *, long long, int,
-                                           double *, double *, Scal *, int, const Batch &, hipStream_t);
+                                           double *, double *, Scal *, int, const Batch &, hipStream_t, const FinIn &);
 template hipError_t launch_cg_step<float>(const OpArgs<double> &, Topo, const float *, float *, long long, int,
-                                          double *, double *, Scal *, int, const Batch &, hipStream_t);
+                                          double *, double *, Scal *, int, const Batch &, hipStream_t, const FinIn &);
 
 }  // namespace spfd
