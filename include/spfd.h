@@ -105,8 +105,9 @@ typedef struct {
     double rel_tol;       /* stop when ||b - A Psi||_2 <= rel_tol * ||b||_2 (true residual at exit); default 1e-8 */
     int max_iter;         /* default 500 */
     int use_x0;           /* nonzero: psi holds the start iterate on entry */
-    int eager;            /* nonzero: launch every kernel from the host instead of replaying the
-                             captured HIP graph of a CG iteration (same kernels, same results) */
+    int eager;            /* nonzero: spfd_solve_many launches every kernel from the host instead of
+                             replaying the captured HIP graph of a CG iteration (same kernels, same
+                             results); spfd_solve and spfd_adjoint always launch from the host */
     int method;           /* SPFD_CG (default): preconditioned CG (see flexible); SPFD_FGMRES: flexible GMRES
                              (the paper's Krylov method, Sec. III), one right side per handle only */
     int restart;          /* FGMRES basis vectors per cycle, 1..32, default 30 */

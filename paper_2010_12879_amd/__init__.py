@@ -480,7 +480,8 @@ class Solver:
 
     def solve(self, a=None, tol=1e-8, max_iter=500, x0=None, check=True, eager=False, method="cg", restart=30,
               flexible=False):
-        """Psi (nrhs or none, Nz, Ny, Nx) and the per-source info dicts (eager: no graph replay;
+        """Psi (nrhs or none, Nz, Ny, Nx) and the per-source info dicts (eager: no graph replay, which
+        only solves of several handles use;
         method "cg" or "fgmres" with `restart` basis vectors per cycle; flexible: the CG's
         Polak-Ribiere beta instead of the standard one)."""
         import torch

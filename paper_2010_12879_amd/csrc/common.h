@@ -37,7 +37,7 @@ struct Scal {
     int status;      // 0 ok, 5 not converged, 6 breakdown
     int hcount;      // CG steps of the current window of kept search directions (the next one's slot)
     int happlied;    // of these, the directions already added to x (an update of x before the window is full)
-    int pad;
+    int stamp;       // host copies only: number of the launch that wrote the copy, stored after the rest of it
     double rzn;      // r.z of the step under way, where the CG kernels finish the sums themselves: the CG step reads
                      // rz and leaves the new value here, the residual update reads it here and moves it to rz
 };

@@ -137,6 +137,8 @@ struct Ctx {
     int h_cap = 0;                // right sides h_scal and h_ring hold (plus one each)
     Scal *d_nostop = nullptr;     // zeroed scalars (never stopped) for cycles run outside a CG step
     Scal *step_mirror = nullptr;  // where the CG step being enqueued leaves its scalars
+    int step_stamp = 0;           // and the stamp it leaves with them (0: none)
+    int stamps = 0;               // stamps given so far
     hipEvent_t ev_it[2] = {nullptr, nullptr};
     // adjoint solve
     double *d_adj_b = nullptr;
@@ -978,7 +980,7 @@ bool vcycle(Ctx *c, const TR *r, T *z, const Scal *sc, int nb, const CycleDots *
 enum { ROWS_BRICKS = 1, ROWS_CG_GROUPS = 2, ROWS_RU_GROUPS = 3 };
 
 void finish(Ctx *c, int n, int mode, Scal *sc, int max_iter, int nb = 1, Scal *mirror = nullptr, int rows = 0,
-            int quads = 0)
+            int quads = 0, int stamp = 0)
 {
     TScope ts(c, SPFD_K_FINISH, nb * (double)n * 8.0 * (mode == FIN_BETA ? 2 : 1));
     FinRows fr{};
@@ -990,7 +992,7 @@ void finish(Ctx *c, int n, int mode, Scal *sc, int max_iter, int nb = 1, Scal *m
                                                : cg_step_parts(c->mcount[m]);
     }
     HIPCHK(launch_finish(c->d_part, n, mode, sc, max_iter, c->stream, nullptr, nullptr, 0, nb, c->pstride, mirror,
-                         fr.used ? &fr : nullptr, quads));
+                         fr.used ? &fr : nullptr, quads, stamp));
 }
 
 // The finest level as the CG kernels see it: all bricks, or one launch row per packed model (its bricks,
@@ -1733,7 +1735,7 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
             TScope ts(c, SPFD_K_UPDATE, n0 * (24.0 + (r32 ? 4.0 : 0.0)));
             HIPCHK(launch_rupdate(topo, c->d_r, c->d_q, c->d_part, sc, bt, r32, c->stream, c->d_ahist, nh));
         }
-        finish(c, nmax, FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_BRICKS);
+        finish(c, nmax, FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_BRICKS, 0, c->step_stamp);
     } else {
         {
             // r (read and written), p_k and the operator; the FP32 copy of r
@@ -1741,7 +1743,7 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
             HIPCHK(launch_col_rupdate<T>(op, topo, ph, c->phist_stride, nh, c->d_r, r32, c->d_part, sc, bt, c->stream,
                                          r32 && r32_scaled(c), c->d_ahist, alpha_in, beta_in.n > 0));
         }
-        finish(c, rupdate_parts(nmax), FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_RU_GROUPS);
+        finish(c, rupdate_parts(nmax), FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_RU_GROUPS, 0, c->step_stamp);
     }
 }
 
@@ -1793,27 +1795,65 @@ void drop_graphs(Ctx *c)
     c->sg_max_iter = -1;
 }
 
+int next_stamp(Ctx *c)
+{
+    c->stamps = c->stamps == 0x7fffffff ? 1 : c->stamps + 1;
+    return c->stamps;
+}
+
+// Waits until the finisher launched with `stamp` has stored the scalars of nb right sides in hs (the pinned
+// ring).  Watching the stored stamp costs the stream nothing; an event recorded between two kernels holds the
+// second back by 3 to 4 us.  The stream is looked at now and then: an error ends the wait, and so does a
+// stream that has run dry without the stamp.
+void wait_stamp(Ctx *c, const Scal *hs, int nb, int stamp)
+{
+    auto there = [&]() {
+        for (int i = 0; i < nb; ++i)
+            if (__atomic_load_n(&hs[i].stamp, __ATOMIC_ACQUIRE) != stamp) return false;
+        return true;
+    };
+    for (;;) {
+        for (int spin = 0; spin < 4096; ++spin) {
+            if (there()) return;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();   // (not an error of the next launch)
+            continue;
+        }
+        HIPCHK(e);
+        if (there()) return;
+        throw HipFail{hipErrorUnknown, "scalars of a finished stream"};
+    }
+}
+
 // Enqueue CG step `it`; its last kernel also stores the scalars into hsc (a
-// slot of the pinned ring).  Steps after the first have fixed kernel
-// arguments per buffer parity, so they are captured once into a HIP graph and
-// replayed: one host call instead of some fifty launches, which keeps the
-// short coarse-level kernels back to back.  The first step, eager solves and
-// the step sampled by the launch timing run eagerly.  The graphs hold no
-// memset nodes.
-void pcg_step_enqueue(Ctx *c, Scal *sc, Scal *hsc, int nb, int it, int max_iter, bool eager)
+// slot of the pinned ring), with a stamp when one is given.  The kernels are
+// launched one by one (direct), or, from the second step on, replayed from a
+// HIP graph captured once per buffer parity: one host call instead of up to
+// fifty.  A solve of one handle launches directly: the host is a step ahead
+// and its calls take less time than the kernels, and graph replay held the
+// kernels of a step further apart (mixed solves: 31^3 590 -> 567 us,
+// 128x96x256 1,044 -> 993, 250x150x900 body 8,496 -> 8,335).  The lockstep of
+// several handles, whose host feeds all their streams, replays.  The step
+// sampled by the launch timing is always launched directly.  The graphs hold
+// no memset nodes.
+void pcg_step_enqueue(Ctx *c, Scal *sc, Scal *hsc, int nb, int it, int max_iter, bool direct, int stamp = 0)
 {
     if (!c->h_ring || hsc < c->h_ring || hsc + nb > c->h_ring + 2 * (c->nrhs + 1))
         throw HipFail{hipErrorInvalidValue, "CG step scalars outside the pinned ring"};
     Scal *mirror = c->h_ring_dev + (hsc - c->h_ring);
     struct MirrorScope {
         Ctx *c;
-        MirrorScope(Ctx *c_, Scal *m) : c(c_) { c->step_mirror = m; }
-        ~MirrorScope() { c->step_mirror = nullptr; }
-    } ms(c, mirror);
+        MirrorScope(Ctx *c_, Scal *m, int stamp) : c(c_) { c->step_mirror = m; c->step_stamp = stamp; }
+        ~MirrorScope() { c->step_mirror = nullptr; c->step_stamp = 0; }
+    } ms(c, mirror, stamp);
     const bool timed_sample = c->tmask != 0 && it == 1;
     // a full window of search directions updates x before the next step overwrites its first slot
     const bool flush = (it + 1) % c->phist_len == 0;
-    if (eager || it == 0 || timed_sample) {
+    if (stamp > 0 && !direct) throw HipFail{hipErrorInvalidValue, "a stamp in a replayed step"};
+    if (direct || it == 0 || timed_sample) {
         c->step_ctx = timed_sample ? 2 : 1;
         pcg_step_any(c, sc, nb, it, max_iter);
         c->step_ctx = 0;
@@ -1873,14 +1913,14 @@ constexpr double HOLD_MARGIN = 4.0;
 void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
 {
     Scal *ring[2] = {c->h_ring, c->h_ring + nb};
-    const bool eager = so.eager != 0;
+    int stamp[2] = {0, 0};
     c->cg_flexible = so.flexible != 0;
     c->step_ctx = 1;
     pcg_begin_any(c, sc, nb);
     c->step_ctx = 0;
     auto enqueue = [&](int k) {
-        pcg_step_enqueue(c, sc, ring[k & 1], nb, k, so.max_iter, eager);
-        HIPCHK(hipEventRecord(c->ev_it[k & 1], c->stream));
+        stamp[k & 1] = next_stamp(c);
+        pcg_step_enqueue(c, sc, ring[k & 1], nb, k, so.max_iter, true, stamp[k & 1]);
     };
     // ||r||^2 after the last two steps seen by the host (< 0: not seen yet)
     std::vector<double> rr1(nb, -1.0), rr2(nb, -1.0), tol2(nb, 0.0);
@@ -1911,7 +1951,7 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
             // kept so far now (the window goes on: they are only marked as added)
             x_flush(c, sc, nb, (it + 1) % c->phist_len, false);
         }
-        HIPCHK(hipEventSynchronize(c->ev_it[it & 1]));
+        wait_stamp(c, ring[it & 1], nb, stamp[it & 1]);
         const Scal *hs = ring[it & 1];
         bool all = true;
         for (int i = 0; i < nb; ++i) {
@@ -1927,7 +1967,7 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
     pcg_end(c, sc, nb, queued + 1);
 }
 
-void resid_b(Ctx *c, const double *b, long long bvs, Scal *sc, double *r, int mode, int nb);
+void resid_b(Ctx *c, const double *b, long long bvs, Scal *sc, double *r, int mode, int nb, Scal *mirror = nullptr);
 
 // Flexible GMRES (one right side): from x and its residual r in c->d_r, cycles
 // of up to m columns with the same multigrid cycle as the CG, each column
@@ -2073,7 +2113,7 @@ void krylov_iterations(Ctx *c, const double *b, long long bvs, Scal *sc, int nb,
 
 // r = b - A x for the batch and ||r||^2 (mode 0: start of a warm-started solve,
 // mode 1: true residual kept in zq)
-void resid_b(Ctx *c, const double *b, long long bvs, Scal *sc, double *r, int mode, int nb)
+void resid_b(Ctx *c, const double *b, long long bvs, Scal *sc, double *r, int mode, int nb, Scal *mirror)
 {
     Level &L0 = c->lv[0];
     const Topo topo = cg_topo(c);
@@ -2082,7 +2122,7 @@ void resid_b(Ctx *c, const double *b, long long bvs, Scal *sc, double *r, int mo
         HIPCHK(launch_resid(level_op<double>(c, 0), topo, b, c->d_x, r, c->d_part, c->np ? 0 : bvs, cg_batch(c, nb),
                             c->stream));
     }
-    finish(c, cg_step_parts(topo_count(topo)), mode == 0 ? FIN_RESID0 : FIN_RESID1, sc, 0, nb, nullptr, ROWS_CG_GROUPS);
+    finish(c, cg_step_parts(topo_count(topo)), mode == 0 ? FIN_RESID0 : FIN_RESID1, sc, 0, nb, mirror, ROWS_CG_GROUPS);
 }
 
 
@@ -2100,12 +2140,13 @@ __global__ void k_rearm_if(Scal *sc, double tol, int nb, const int *again)
 // FP64) whose scalars (with ||b||^2 from the right-side kernel) live in sc[i];
 // write the gauged solutions as dense node arrays psi + i*nn (also the start
 // iterates when use_x0).  Uses the handle's solve buffers (nb <= nbat).
-spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, Scal *hsc, int nb,
+spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, int nb,
                         const spfd_solve_options &so, double *psi, spfd_rhs_info *info)
 {
     Level &L0 = c->lv[0];
     const Topo topo = L0.topo();
     const long long n0 = L0.nodes();
+    const Scal *hsc = c->h_ring;
     const long long nn = (long long)c->g.Nx * c->g.Ny * c->g.Nz;
     // packed models share one vector of each kind
     const int nvec = c->np ? 1 : nb;
@@ -2153,8 +2194,8 @@ spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, Scal *
         krylov_iterations(c, b, bvs, sc, nb, so);
         // true residual of every iterate (also of those that converged in an earlier pass); r itself is
         // only needed for a restart and is formed again then
-        resid_b(c, b, bvs, sc, nullptr, 1, nb);
-        HIPCHK(hipMemcpyAsync(hsc, sc, nb * sizeof(Scal), hipMemcpyDeviceToHost, c->stream));
+        // (the scalars come back through the pinned ring, which the iterations have left)
+        resid_b(c, b, bvs, sc, nullptr, 1, nb, c->h_ring_dev);
         // the output is formed before the host has seen the residuals (no idle GPU during that round
         // trip); a restart forms it again
         emit();
@@ -2196,7 +2237,7 @@ spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, Scal *
 spfd_status do_solve(Ctx *c, const spfd_solve_options &so, double *psi, spfd_rhs_info *info)
 {
     const long long n0 = c->lv[0].nodes();
-    spfd_status worst = solve_batch(c, c->d_bs, n0, c->d_scal, c->h_scal, c->nrhs, so, psi, info);
+    spfd_status worst = solve_batch(c, c->d_bs, n0, c->d_scal, c->nrhs, so, psi, info);
     if (worst != SPFD_OK)
         c->err = worst == SPFD_BREAKDOWN ? "breakdown in CG (non-positive curvature or non-finite value)"
                                          : "maximum iteration count reached";
@@ -2287,7 +2328,7 @@ spfd_status solve_many(Ctx **hs, int n, const spfd_solve_options &so, double **p
         }
         spfd_status st;
         if (redo) {
-            st = solve_batch(c, c->d_bs, n0, c->d_scal, c->h_scal, nb, so, psi[k], info ? info + off[k] : nullptr);
+            st = solve_batch(c, c->d_bs, n0, c->d_scal, nb, so, psi[k], info ? info + off[k] : nullptr);
         } else {
             st = SPFD_OK;
             const Level &L0 = c->lv[0];
@@ -2694,7 +2735,7 @@ spfd_status spfd_set_source(spfd_handle h, int rhs, const double *a)
         HIPCHK(hipSetDevice(h->device));
         enter(h);
         Level &L0 = h->lv[0];
-        HIPCHK(hipMemsetAsync(h->d_scal + rhs, 0, sizeof(Scal), h->stream));
+        const int stamp = next_stamp(h);
         if (h->np) {
             // model rhs: its bricks of the shared vector, its dense a, ||b||^2 from its own row of partials
             Topo t = L0.topo();
@@ -2707,18 +2748,19 @@ spfd_status spfd_set_source(spfd_handle h, int rhs, const double *a)
                 HIPCHK(launch_rhs(level_op<double>(h, 0), t, L0.d_coord, h->mgrid[rhs], a, h->d_bs, part,
                                   h->d_scal + rhs, h->stream, h->mbox.zoff[rhs]));
             }
-            HIPCHK(launch_finish(part, t.pmax, FIN_BB, h->d_scal + rhs, 0, h->stream));
+            HIPCHK(launch_finish(part, t.pmax, FIN_BB, h->d_scal + rhs, 0, h->stream, nullptr, nullptr, 0, 1, 0,
+                                 h->h_ring_dev, nullptr, 0, stamp));
         } else {
             {
                 TScope ts(h, SPFD_K_RHS, (double)L0.dofs * (24.0 + 8.0 + op_bytes<double>(h, 0)));
                 HIPCHK(launch_rhs(level_op<double>(h, 0), L0.topo(), L0.d_coord, h->g, a, h->d_bs + rhs * L0.nodes(),
                                   h->d_part, h->d_scal + rhs, h->stream));
             }
-            finish(h, L0.nb, FIN_BB, h->d_scal + rhs, 0);
+            finish(h, L0.nb, FIN_BB, h->d_scal + rhs, 0, 1, h->h_ring_dev, 0, 0, stamp);
         }
-        HIPCHK(hipMemcpyAsync(h->h_scal + rhs, h->d_scal + rhs, sizeof(Scal), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        if (!isfinite(h->h_scal[rhs].bb)) return fail(h, SPFD_INVALID_ARG, "source potentials must be finite");
+        // ||b||^2 has arrived once the kernels that read a have ended
+        wait_stamp(h, h->h_ring, 1, stamp);
+        if (!isfinite(h->h_ring[0].bb)) return fail(h, SPFD_INVALID_ARG, "source potentials must be finite");
         h->has_source[rhs] = 1;
         h->state = 4;
         return SPFD_OK;
@@ -2832,7 +2874,7 @@ spfd_status spfd_adjoint(spfd_handle h, double omega, const double *a, const dou
         }
         finish(h, L0.nb, FIN_BB, h->d_adj_scal, 0);
         spfd_rhs_info inf{};
-        spfd_status st = solve_batch(h, h->d_adj_b, 0, h->d_adj_scal, h->h_scal + h->nrhs, 1, so, h->d_adj_lam, &inf);
+        spfd_status st = solve_batch(h, h->d_adj_b, 0, h->d_adj_scal, 1, so, h->d_adj_lam, &inf);
         {
             TScope ts(h, SPFD_K_EFIELD, (double)nvox * (1.0 + 8.0) + (double)L0.dofs * (8.0 + 8.0 + 24.0));
             HIPCHK(launch_adj_grad(h->d_labels, h->d_table64, sv, g, h->geo4, a, psi, h->d_adj_lam, grad_sigma_voxel,

@@ -106,7 +106,7 @@ hipError_t launch_dense_inverse(int n, double *A, double *work, hipStream_t s);
 // workgroup, then launch_finish (one workgroup) sums them in a fixed order and
 // updates the solve's scalars according to `mode`.
 enum {
-    FIN_BB = 0,       // ||b||^2 of a new right side
+    FIN_BB = 0,       // ||b||^2 of a new right side; its other scalars are cleared
     FIN_ALPHA = 1,    // alpha = r.z / p.q
     FIN_RR = 2,       // ||r||^2, iteration count and stop test
     FIN_BETA0 = 3,    // r.z of the first preconditioned residual
@@ -118,7 +118,8 @@ enum {
 };
 // mirror != nullptr: the scalars of right side i are also written to
 // mirror[i] (host-visible memory) when the kernel ends, also when the solve
-// had already stopped: the host reads them after the stream has passed here.
+// had already stopped: the host reads them after the stream has passed here,
+// or, with stamp > 0, once mirror[i].stamp holds it (stored after the rest).
 // rows (nullable, used != 0): row r sums only its first n[r] partials (packed models: each model's own
 // count of bricks or groups); the z.q partials of FIN_BETA start at part + n in every row
 // quads != 0: the partials are 4 n single sums, quads of them given (the rest count as 0), each four added in
@@ -129,7 +130,8 @@ struct FinRows {
 };
 hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_iter, hipStream_t s,
                          double *means = nullptr, const int *counts = nullptr, int comp = 0, int nbatch = 1,
-                         int ps = 0, Scal *mirror = nullptr, const FinRows *rows = nullptr, int quads = 0);
+                         int ps = 0, Scal *mirror = nullptr, const FinRows *rows = nullptr, int quads = 0,
+                         int stamp = 0);
 
 template <typename T>
 hipError_t launch_fill(T *x, long long n, T v, hipStream_t s);

@@ -880,7 +880,7 @@ __global__ void k_scal_init(Scal *sc, double tol, int use_x0)
         sc->rr = bb;
         sc->tol2 = tol * tol * bb;
         sc->done = bb > 0.0 ? 0 : 1;
-        sc->iters = 0; sc->status = 0; sc->hcount = 0; sc->happlied = 0; sc->pad = 0; sc->rzn = 0.0;
+        sc->iters = 0; sc->status = 0; sc->hcount = 0; sc->happlied = 0; sc->stamp = 0; sc->rzn = 0.0;
     }
 }
 
@@ -911,16 +911,23 @@ __device__ __forceinline__ double block_sum_any(double v, double *lds)
     return s;
 }
 
-__device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc)
+// the scalars into host memory; with a stamp (> 0) the host may poll for them: it sees the stamp after the rest
+__device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc, int stamp)
 {
-    if (mirror) mirror[blockIdx.x] = *sc;
+    if (!mirror) return;
+    Scal *m = mirror + blockIdx.x;
+    *m = *sc;   // (the device's stamp is 0)
+    if (stamp > 0) {
+        __threadfence_system();
+        __hip_atomic_store(&m->stamp, stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // rows.used: row r sums its first rows.n[r] partials (packed models: each model's own count), else n;
 // the second set of partials (z.q) starts at part + n in every row
 __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part, int n, int mode, Scal *sc,
                                                  int max_iter, double *means, const int *counts, int comp, int ps,
-                                                 Scal *mirror, FinRows rows, int quads)
+                                                 Scal *mirror, FinRows rows, int quads, int stamp)
 {
     __shared__ double red[16];
     part += (long long)blockIdx.x * ps;
@@ -955,7 +962,7 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
         b += ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
     }
     if (stopped) {
-        if (threadIdx.x == 0) store_mirror(mirror, sc);
+        if (threadIdx.x == 0) store_mirror(mirror, sc, stamp);
         return;
     }
     a = block_sum_any(a, red);
@@ -963,6 +970,7 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
     if (threadIdx.x != 0) return;
     switch (mode) {
     case FIN_BB:
+        *sc = Scal{};   // a new right side
         sc->bb = a;
         break;
     case FIN_ALPHA: {
@@ -1017,18 +1025,19 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
         means[comp] = counts[comp] > 0 ? a / (double)counts[comp] : 0.0;
         break;
     }
-    if (sc) store_mirror(mirror, sc);
+    if (sc) store_mirror(mirror, sc, stamp);
 }
 
 hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_iter, hipStream_t s, double *means,
-                         const int *counts, int comp, int nbatch, int ps, Scal *mirror, const FinRows *rows, int quads)
+                         const int *counts, int comp, int nbatch, int ps, Scal *mirror, const FinRows *rows, int quads,
+                         int stamp)
 {
     if (mirror && !sc) return hipErrorInvalidValue;
     if (quads && (mode == FIN_BETA || quads > 4 * n || (rows && rows->used))) return hipErrorInvalidValue;
     if (rows && rows->used && nbatch > MAX_MODELS) return hipErrorInvalidValue;
     const FinRows fr = rows ? *rows : FinRows{};
     SPFD_LAUNCH(k_finish, dim3(nbatch), dim3(1024), 0, s, part, n, mode, sc, max_iter, means, counts, comp, ps,
-                mirror, fr, quads);
+                mirror, fr, quads, stamp);
     return hipGetLastError();
 }
 
