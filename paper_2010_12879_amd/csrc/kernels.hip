@@ -620,32 +620,32 @@ hipError_t launch_coarse_setup(const double *w64, long long stride, Topo topo, i
     return hipGetLastError();
 }
 
-// Dense matrix of the coarsest structured level over its unknowns (row-major n x n).
-__global__ void k_coarse_assemble_brick(const double *__restrict__ w, long long stride, Topo topo,
-                                        const int *__restrict__ node_of_dof, const int *__restrict__ adj, int n,
-                                        double *A)
+// Dense matrix of the coarsest structured level over its unknowns (row-major n x n), one wave per row.
+__global__ __launch_bounds__(256) void k_coarse_assemble_brick(const double *__restrict__ w, long long stride, Topo topo,
+                                                               const int *__restrict__ node_of_dof,
+                                                               const int *__restrict__ adj, int n, double *A)
 {
-    const int t = threadIdx.x, nt = blockDim.x;
-    for (long long e = t; e < (long long)n * n; e += nt) A[e] = 0.0;
-    __syncthreads();
-    for (int q = t; q < n; q += nt) {
-        const int i = node_of_dof[q];
-        const int b = i / BS, tt = i % BS;
-        int tx, ty, tz;
-        brick_xyz(tt, tx, ty, tz);
-        double W[6];
-        long long I[6];
-        nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * 6, I);
-        stored_weights(w, stride, (long long)b * BS, tt, I, W);
-        double d = 0.0;
-        for (int k = 0; k < 6; ++k) {
-            const int m = adj[q * 6 + k];
-            if (m >= 0) {
-                A[(long long)q * n + m] -= W[k];
-                d += W[k];
-            }
-        }
-        A[(long long)q * n + q] += d;
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (q >= n) return;
+    const int i = node_of_dof[q];
+    const int b = i / BS, tt = i % BS;
+    int tx, ty, tz;
+    brick_xyz(tt, tx, ty, tz);
+    double W[6];
+    long long I[6];
+    nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * 6, I);
+    stored_weights(w, stride, (long long)b * BS, tt, I, W);
+    int m[6];
+    double d = 0.0;
+    for (int k = 0; k < 6; ++k) {
+        m[k] = adj[q * 6 + k];
+        if (m[k] >= 0) d += W[k];
+    }
+    for (int c = lane; c < n; c += 64) {
+        double v = c == q ? d : 0.0;
+        for (int k = 0; k < 6; ++k)
+            if (m[k] == c) v -= W[k];
+        A[(long long)q * n + c] = v;
     }
 }
 
@@ -764,49 +764,73 @@ __global__ __launch_bounds__(256) void k_creg_pattern(int n, const double *__res
     if (lane == 0) w.deg[q] = d;
 }
 
+// One thread per unknown (n <= 1024), labels in LDS, the row's first CREG_NB neighbours in registers: a round of
+// the propagation is a few LDS reads (labels and neighbours in global memory, and one thread adding up the
+// diagonals, took 103 us on 641 unknowns; this form 52 us).
+constexpr int CREG_NB = 16;
+
 __global__ __launch_bounds__(1024) void k_creg_components(int n, const double *__restrict__ A, int *work)
 {
     const CoarseWork w = coarse_work(n, work);
-    const int t = threadIdx.x, nt = blockDim.x;
+    const int q = threadIdx.x;
+    const bool in = q < n;
     __shared__ int changed;
+    __shared__ int label[1024], size[1024];
+    __shared__ double sdiag[1024];
+    int nb[CREG_NB];
+    const int d = in ? w.deg[q] : 0;   // -1: a row with more than CMAXADJ nonzeros
+#pragma unroll
+    for (int k = 0; k < CREG_NB; ++k) nb[k] = k < d ? w.adj[(long long)q * CMAXADJ + k] : q;
+    sdiag[q] = in ? A[(long long)q * n + q] : 0.0;
+    label[q] = q;
+    size[q] = 0;
+    auto get = [&](int m) { return __hip_atomic_load(label + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
     // minimum label over each component: neighbour minima plus pointer jumping
     do {
         __syncthreads();
-        if (t == 0) changed = 0;
+        if (q == 0) changed = 0;
         __syncthreads();
-        for (int q = t; q < n; q += nt) {
-            int c = __hip_atomic_load(w.comp + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const int d = w.deg[q];
-            const int cnt = d >= 0 ? d : n;
-            for (int k = 0; k < cnt; ++k) {
-                const int m = d >= 0 ? w.adj[(long long)q * CMAXADJ + k] : k;
-                if (d < 0 && (m == q || A[(long long)q * n + m] == 0.0)) continue;
-                const int cm = __hip_atomic_load(w.comp + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (cm < c) c = cm;
+        if (in) {
+            const int c0 = get(q);
+            int c = c0;
+#pragma unroll
+            for (int k = 0; k < CREG_NB; ++k) {
+                const int cm = get(nb[k]);
+                c = cm < c ? cm : c;
             }
-            const int cc = __hip_atomic_load(w.comp + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (cc < c) c = cc;
-            if (c < __hip_atomic_load(w.comp + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                __hip_atomic_store(w.comp + q, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            for (int k = CREG_NB; k < d; ++k) {
+                const int cm = get(w.adj[(long long)q * CMAXADJ + k]);
+                c = cm < c ? cm : c;
+            }
+            if (d < 0)
+                for (int m = 0; m < n; ++m)
+                    if (m != q && A[(long long)q * n + m] != 0.0) {
+                        const int cm = get(m);
+                        c = cm < c ? cm : c;
+                    }
+            const int cc = get(c);
+            c = cc < c ? cc : c;
+            if (c < c0) {
+                __hip_atomic_store(label + q, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 changed = 1;
             }
         }
         __syncthreads();
     } while (changed);
-    for (int q = t; q < n; q += nt) atomicAdd(w.csize + w.comp[q], 1);
-    // per-component diagonal sums in a fixed order (deterministic): diagonal and labels staged in LDS
-    __shared__ double sdiag[1024], ssum[1024];
-    __shared__ int scomp[1024];
-    for (int q = t; q < n; q += nt) {
-        sdiag[q] = A[(long long)q * n + q];
-        scomp[q] = w.comp[q];
-        ssum[q] = 0.0;
+    if (in) {
+        w.comp[q] = label[q];
+        atomicAdd(size + label[q], 1);
     }
     __syncthreads();
-    if (t == 0)
-        for (int q = 0; q < n; ++q) ssum[scomp[q]] += sdiag[q];
-    __syncthreads();
-    for (int q = t; q < n; q += nt) w.cdiag[q] = ssum[q];
+    if (!in) return;
+    w.csize[q] = size[q];
+    // diagonal sum of each component, in the order of the unknowns, by the unknown that gives it its label
+    double sum = 0.0;
+    if (label[q] == q) {
+#pragma unroll 16
+        for (int m = 0; m < n; ++m) sum += label[m] == q ? sdiag[m] : 0.0;
+    }
+    w.cdiag[q] = sum;
 }
 
 __global__ __launch_bounds__(256) void k_creg_update(int n, double *A, const int *work)
@@ -827,7 +851,7 @@ hipError_t launch_coarse_assemble_brick(const double *w64, long long stride, Top
                                         const int *adj, int n, double *A, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_coarse_assemble_brick, dim3(1), dim3(1024), 0, s, w64, stride, topo, node_of_dof, adj, n, A);
+    SPFD_LAUNCH(k_coarse_assemble_brick, dim3((n + 3) / 4), dim3(256), 0, s, w64, stride, topo, node_of_dof, adj, n, A);
     return hipGetLastError();
 }
 
@@ -836,6 +860,7 @@ size_t coarse_factor_work_ints(int n) { return (size_t)(5 + CMAXADJ) * n + 8; }
 hipError_t launch_coarse_factor(int n, double *A, int *work, double *dwork, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
+    if (n > 1024) return hipErrorInvalidValue;
     SPFD_LAUNCH(k_creg_pattern, dim3((n + 3) / 4), dim3(256), 0, s, n, A, work);
     SPFD_LAUNCH(k_creg_components, dim3(1), dim3(1024), 0, s, n, A, work);
     const long long nn = (long long)n * n;
@@ -843,7 +868,6 @@ hipError_t launch_coarse_factor(int n, double *A, int *work, double *dwork, hipS
                 n, A, work);
     HIP_RETURN_IF(hipGetLastError());
     return launch_dense_inverse(n, A, dwork, s);
-    return hipGetLastError();
 }
 
 // ============================================================================
