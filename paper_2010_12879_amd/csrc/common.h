@@ -206,4 +206,16 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
     return s;
 }
 
+// the scalars into host memory; with a stamp (> 0) the host may poll for them: it sees the stamp after the rest
+__device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc, int stamp, int row = 0)
+{
+    if (!mirror) return;
+    Scal *m = mirror + row;
+    *m = *sc;   // (the device's stamp is 0)
+    if (stamp > 0) {
+        __threadfence_system();
+        __hip_atomic_store(&m->stamp, stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 }  // namespace spfd

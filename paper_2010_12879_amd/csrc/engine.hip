@@ -2011,18 +2011,21 @@ void fgmres_iterations(Ctx *c, const double *b, long long bvs, Scal *sc, const s
         TScope ts(c, SPFD_K_DOTS, nd * 8.0);
         HIPCHK(launch_mdot(c->d_r, n0, c->d_r, n0, 1, part, sc, c->stream));
     }
-    HIPCHK(launch_finish(part, ng, FIN_RESID0, sc, 0, c->stream, nullptr, nullptr, 0, 1, 0));
+    int start_stamp = next_stamp(c);   // (in the ring's third slot; the columns use the first two)
+    HIPCHK(launch_finish(part, ng, FIN_RESID0, sc, 0, c->stream, nullptr, nullptr, 0, 1, 0, c->h_ring_dev + 2, nullptr, 0,
+                         start_stamp));
     HIPCHK(launch_fg_start(st, sc, c->stream));
     {
         TScope ts(c, SPFD_K_UPDATE, nd * (16.0 + (mixed ? 4.0 : 0.0)));
         HIPCHK(launch_fg_scale(c->d_r, V, v32, n0, st, sc, c->stream));
     }
-    if (poll()) return;
     // Columns run one ahead of the host's check, as the CG steps do: column j+1
     // is enqueued before the host reads the stop test of column j (a column
     // after the last one finds the stop flag and stores nothing), unless the
     // residual estimates predict that column j ends the solve, or j ends the cycle.
     Scal *ring[2] = {c->h_ring, c->h_ring + 1};
+    Scal *ring_dev[2] = {c->h_ring_dev, c->h_ring_dev + 1};
+    int stamp[2] = {0, 0};
     auto enqueue_column = [&](int j) {
         T *zj = Z + (long long)j * n0;
         if (mixed)
@@ -2048,14 +2051,12 @@ void fgmres_iterations(Ctx *c, const double *b, long long bvs, Scal *sc, const s
             TScope ts(c, SPFD_K_DOTS, nd * 8.0 * (nv + 2));
             HIPCHK(launch_mupdate(V, n0, w, n0, nv, st->h2, 1, part, sc, c->stream));
         }
-        HIPCHK(launch_msum(part, ng, 1, &st->hnext, sc, c->stream));
-        HIPCHK(launch_fg_column(st, sc, j, so.max_iter, c->stream));
+        stamp[j & 1] = next_stamp(c);
+        HIPCHK(launch_fg_column(st, sc, j, so.max_iter, part, ng, ring_dev[j & 1], stamp[j & 1], c->stream));
         {
             TScope ts(c, SPFD_K_UPDATE, nd * (16.0 + (mixed ? 4.0 : 0.0)));
             HIPCHK(launch_fg_scale(w, V + (long long)nv * n0, v32, n0, st, sc, c->stream));
         }
-        HIPCHK(hipMemcpyAsync(ring[j & 1], sc, sizeof(Scal), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipEventRecord(c->ev_it[j & 1], c->stream));
     };
     double rr1 = -1.0, rr2 = -1.0;  // residual estimates of the last two columns seen
     int j = 0, queued = -1;
@@ -2064,12 +2065,17 @@ void fgmres_iterations(Ctx *c, const double *b, long long bvs, Scal *sc, const s
             enqueue_column(j);
             queued = j;
         }
+        if (start_stamp) {   // a start that is already done: its first column found the stop flag
+            wait_stamp(c, c->h_ring + 2, 1, start_stamp);
+            start_stamp = 0;
+            if (c->h_ring[2].done) return;
+        }
         const bool likely_last = rr1 > 0.0 && rr2 > 0.0 && rr1 * (rr1 / rr2) <= HOLD_MARGIN * ring[0]->tol2;
         if (j + 1 < m && !likely_last) {
             enqueue_column(j + 1);
             queued = j + 1;
         }
-        HIPCHK(hipEventSynchronize(c->ev_it[j & 1]));
+        wait_stamp(c, ring[j & 1], 1, stamp[j & 1]);
         const bool done = ring[j & 1]->done != 0;
         rr2 = rr1;
         rr1 = ring[j & 1]->rr;

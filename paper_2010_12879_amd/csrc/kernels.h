@@ -166,7 +166,8 @@ hipError_t launch_mupdate(const double *V, long long ldv, double *w, long long n
                           double *part, const Scal *sc, hipStream_t s);
 hipError_t launch_msum(const double *part, int ng, int nv, double *out, const Scal *sc, hipStream_t s);
 hipError_t launch_fg_start(FGState *st, const Scal *sc, hipStream_t s);
-hipError_t launch_fg_column(FGState *st, Scal *sc, int j, int max_iter, hipStream_t s);
+hipError_t launch_fg_column(FGState *st, Scal *sc, int j, int max_iter, const double *part, int ng, Scal *mirror,
+                            int stamp, hipStream_t s);
 hipError_t launch_fg_ysolve(FGState *st, int k, hipStream_t s);
 hipError_t launch_fg_scale(const double *src, double *v, float *v32, long long n, const FGState *st, const Scal *sc,
                            hipStream_t s);

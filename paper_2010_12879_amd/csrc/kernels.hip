@@ -935,18 +935,6 @@ __device__ __forceinline__ double block_sum_any(double v, double *lds)
     return s;
 }
 
-// the scalars into host memory; with a stamp (> 0) the host may poll for them: it sees the stamp after the rest
-__device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc, int stamp)
-{
-    if (!mirror) return;
-    Scal *m = mirror + blockIdx.x;
-    *m = *sc;   // (the device's stamp is 0)
-    if (stamp > 0) {
-        __threadfence_system();
-        __hip_atomic_store(&m->stamp, stamp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-}
-
 // rows.used: row r sums its first rows.n[r] partials (packed models: each model's own count), else n;
 // the second set of partials (z.q) starts at part + n in every row
 __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part, int n, int mode, Scal *sc,
@@ -986,7 +974,7 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
         b += ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
     }
     if (stopped) {
-        if (threadIdx.x == 0) store_mirror(mirror, sc, stamp);
+        if (threadIdx.x == 0) store_mirror(mirror, sc, stamp, blockIdx.x);
         return;
     }
     a = block_sum_any(a, red);
@@ -1049,7 +1037,7 @@ __global__ __launch_bounds__(1024) void k_finish(const double *__restrict__ part
         means[comp] = counts[comp] > 0 ? a / (double)counts[comp] : 0.0;
         break;
     }
-    if (sc) store_mirror(mirror, sc, stamp);
+    if (sc) store_mirror(mirror, sc, stamp, blockIdx.x);
 }
 
 hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_iter, hipStream_t s, double *means,

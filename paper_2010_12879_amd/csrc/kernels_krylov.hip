@@ -9,7 +9,7 @@
 // At convergence or after m columns: y = R^-1 g and x += Z y (restart from
 // the true residual).  Vectors are the finest level's slot arrays (zero at
 // slots without an unknown); the small least-squares problem lives in device
-// memory and is updated by one thread per column.
+// memory and is updated by one workgroup per column.
 #include <math.h>
 
 #include "kernels.h"
@@ -31,17 +31,29 @@ __device__ __forceinline__ double block_reduce(double v, double *lds)
     return s;
 }
 
-// partials of NV rows at once: row i of the workgroup into part[i*gridDim.x + blockIdx.x], i < nv
+// partials of NV rows at once: row i of the workgroup into part[i*gridDim.x + blockIdx.x], i < nv.  Each step of a
+// wave's sums over half the distance also halves the rows a lane keeps (lanes l and l ^ off keep one half each), so
+// 16 rows take 17 cross-lane adds instead of 96, in the order of wave_sum.  (205 k slots, 9 to 13 rows: k_mdot 14.0 ->
+// 6.5 us, k_mupdate, whose coefficients were also loaded one by one, 14.2 -> 7.4 us.)
 template <int NV>
 __device__ __forceinline__ void rows_reduce(double (&acc)[NV], int nv, double *__restrict__ part)
 {
     __shared__ double lds[NV][KT / 64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int off = 32;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const double t = wave_sum(acc[i]);
-        if (lane == 0) lds[i][wv] = t;
+    for (int m = NV / 2; m > 0; m /= 2, off /= 2) {
+        const long long up = lane & off ? -1LL : 0LL;   // (a mask: a choice of elements becomes a search by index)
+#pragma unroll
+        for (int i = 0; i < m; ++i) {
+            const long long lo = __double_as_longlong(acc[i]), hi = __double_as_longlong(acc[i + m]);
+            const double give = __longlong_as_double((lo & up) | (hi & ~up));
+            const double keep = __longlong_as_double((hi & up) | (lo & ~up));
+            acc[i] = keep + __shfl_xor(give, off, 64);
+        }
     }
+    for (; off > 0; off >>= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+    if (lane % (64 / NV) == 0) lds[lane / (64 / NV)][wv] = acc[0];
     __syncthreads();
     if (threadIdx.x < nv) {
         double t = 0.0;
@@ -87,8 +99,10 @@ __global__ __launch_bounds__(KT) void k_mupdate(const double *__restrict__ V, lo
     if (sc->done) return;
     double hv[NV], acc[NV];
 #pragma unroll
+    for (int i = 0; i < NV; ++i) hv[i] = h[i < nv ? i : nv - 1];   // (h[i] under the condition: one wait per row)
+#pragma unroll
     for (int i = 0; i < NV; ++i) {
-        hv[i] = i < nv ? h[i] : 0.0;
+        if (i >= nv) hv[i] = 0.0;
         acc[i] = 0.0;
     }
     double nrm = 0.0;
@@ -139,52 +153,84 @@ __global__ void k_fg_start(FGState *st, const Scal *sc)
     st->scale = beta > 0.0 ? 1.0 / beta : 0.0;
 }
 
-// column j of H from the two Gram-Schmidt passes and ||w||; rotations; stop test
-__global__ void k_fg_column(FGState *st, Scal *sc, int j, int max_iter)
+// ||w||^2 from its partials, column j of H from the two Gram-Schmidt passes and ||w||; rotations; stop test; the
+// scalars to the host.  One workgroup: all operands are loaded at once into LDS, where the first thread goes
+// through the rotations (a sum, a one-thread column and a copy of the scalars with an event were four entries
+// of the stream: 3.2 + 4.1 + 2 us and the gaps between them; this one 5.2 us).
+__global__ __launch_bounds__(KT) void k_fg_column(FGState *st, Scal *sc, int j, int max_iter,
+                                                  const double *__restrict__ part, int ng, Scal *mirror, int stamp)
 {
-    if (sc->done) return;
+    __shared__ double lds[KT / 64];
+    __shared__ double h[FG_MAXM + 1], cs[FG_MAXM], sn[FG_MAXM];
+    const int t = threadIdx.x;
+    const int stopped = sc->done;
     double *H = st->H + (long long)j * (FG_MAXM + 1);
-    for (int i = 0; i <= j; ++i) H[i] = st->h1[i] + st->h2[i];
-    const double hn = sqrt(st->hnext);
-    H[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-        const double t = st->cs[i] * H[i] + st->sn[i] * H[i + 1];
-        H[i + 1] = -st->sn[i] * H[i] + st->cs[i] * H[i + 1];
-        H[i] = t;
+    double nrm = 0.0;
+    for (int g = t; g < ng; g += KT) nrm += part[g];
+    if (t <= j) h[t] = st->h1[t] + st->h2[t];
+    if (t < j) {
+        cs[t] = st->cs[t];
+        sn[t] = st->sn[t];
     }
-    const double a = H[j], b = H[j + 1];
-    const double r = hypot(a, b);
-    const double c = r > 0.0 ? a / r : 1.0, s = r > 0.0 ? b / r : 0.0;
-    st->cs[j] = c;
-    st->sn[j] = s;
-    H[j] = r;
-    H[j + 1] = 0.0;
-    st->g[j + 1] = -s * st->g[j];
-    st->g[j] = c * st->g[j];
-    st->scale = hn > 0.0 ? 1.0 / hn : 0.0;
-    const double res2 = st->g[j + 1] * st->g[j + 1];
-    sc->rr = res2;
-    sc->iters += 1;
-    if (!isfinite(res2) || !(r > 0.0)) {
-        sc->status = 6;
-        sc->done = 1;
-    } else if (res2 <= sc->tol2 || !(hn > 0.0)) {
-        sc->done = 1;   // converged (hn = 0: the Krylov space holds the solution)
-    } else if (sc->iters >= max_iter) {
-        sc->status = 5;
-        sc->done = 1;
+    const double gj = st->g[j];
+    if (stopped) {
+        if (t == 0) store_mirror(mirror, sc, stamp);
+        return;
+    }
+    nrm = block_reduce(nrm, lds);   // (its barriers also order h, cs and sn)
+    if (t == 0) {
+        st->hnext = nrm;
+        const double hn = sqrt(nrm);
+        double a = h[0];
+        for (int i = 0; i < j; ++i) {
+            const double next = h[i + 1];
+            const double r = -sn[i] * a + cs[i] * next;
+            H[i] = cs[i] * a + sn[i] * next;
+            a = r;
+        }
+        const double b = hn;
+        const double r = hypot(a, b);
+        const double c = r > 0.0 ? a / r : 1.0, s = r > 0.0 ? b / r : 0.0;
+        st->cs[j] = c;
+        st->sn[j] = s;
+        H[j] = r;
+        H[j + 1] = 0.0;
+        const double gn = -s * gj;
+        st->g[j + 1] = gn;
+        st->g[j] = c * gj;
+        st->scale = hn > 0.0 ? 1.0 / hn : 0.0;
+        const double res2 = gn * gn;
+        sc->rr = res2;
+        sc->iters += 1;
+        if (!isfinite(res2) || !(r > 0.0)) {
+            sc->status = 6;
+            sc->done = 1;
+        } else if (res2 <= sc->tol2 || !(hn > 0.0)) {
+            sc->done = 1;   // converged (hn = 0: the Krylov space holds the solution)
+        } else if (sc->iters >= max_iter) {
+            sc->status = 5;
+            sc->done = 1;
+        }
+        store_mirror(mirror, sc, stamp);
     }
 }
 
-// y = R^-1 g over the first k columns (back substitution); runs also after the stop flag is set
-__global__ void k_fg_ysolve(FGState *st, int k)
+// y = R^-1 g over the first k columns (back substitution, in LDS); runs also after the stop flag is set
+__global__ __launch_bounds__(KT) void k_fg_ysolve(FGState *st, int k)
 {
-    for (int i = k - 1; i >= 0; --i) {
-        double t = st->g[i];
-        for (int l = i + 1; l < k; ++l) t -= st->H[(long long)l * (FG_MAXM + 1) + i] * st->y[l];
-        const double d = st->H[(long long)i * (FG_MAXM + 1) + i];
-        st->y[i] = d != 0.0 ? t / d : 0.0;
-    }
+    __shared__ double H[FG_MAXM * (FG_MAXM + 1)], g[FG_MAXM], y[FG_MAXM];
+    for (int e = threadIdx.x; e < k * (FG_MAXM + 1); e += KT) H[e] = st->H[e];
+    if (threadIdx.x < k) g[threadIdx.x] = st->g[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = k - 1; i >= 0; --i) {
+            double t = g[i];
+            for (int l = i + 1; l < k; ++l) t -= H[l * (FG_MAXM + 1) + i] * y[l];
+            const double d = H[i * (FG_MAXM + 1) + i];
+            y[i] = d != 0.0 ? t / d : 0.0;
+        }
+    __syncthreads();
+    if (threadIdx.x < k) st->y[threadIdx.x] = y[threadIdx.x];
 }
 
 // v = src * st->scale (and its FP32 copy for an FP32 cycle)
@@ -208,7 +254,10 @@ __global__ __launch_bounds__(KT) void k_fg_xupdate(double *__restrict__ x, const
 {
     double y[NV];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) y[i] = i < k ? st->y[i] : 0.0;
+    for (int i = 0; i < NV; ++i) y[i] = st->y[i < k ? i : k - 1];
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+        if (i >= k) y[i] = 0.0;
     for (long long e = (long long)blockIdx.x * KT + threadIdx.x; e < n; e += (long long)gridDim.x * KT) {
         double t = x[e];
         TZ zv[NV];
@@ -273,17 +322,18 @@ hipError_t launch_fg_start(FGState *st, const Scal *sc, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fg_column(FGState *st, Scal *sc, int j, int max_iter, hipStream_t s)
+hipError_t launch_fg_column(FGState *st, Scal *sc, int j, int max_iter, const double *part, int ng, Scal *mirror,
+                            int stamp, hipStream_t s)
 {
     if (j < 0 || j >= FG_MAXM) return hipErrorInvalidValue;
-    SPFD_LAUNCH(k_fg_column, dim3(1), dim3(1), 0, s, st, sc, j, max_iter);
+    SPFD_LAUNCH(k_fg_column, dim3(1), dim3(KT), 0, s, st, sc, j, max_iter, part, ng, mirror, stamp);
     return hipGetLastError();
 }
 
 hipError_t launch_fg_ysolve(FGState *st, int k, hipStream_t s)
 {
     if (k < 0 || k > FG_MAXM) return hipErrorInvalidValue;
-    SPFD_LAUNCH(k_fg_ysolve, dim3(1), dim3(1), 0, s, st, k);
+    SPFD_LAUNCH(k_fg_ysolve, dim3(1), dim3(KT), 0, s, st, k);
     return hipGetLastError();
 }
 
