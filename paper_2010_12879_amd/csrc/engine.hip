@@ -62,7 +62,7 @@ struct Level {
     int *d_memb = nullptr;          // the same as a direct table of 8 per row (null: an aggregate has more)
     int *d_agg = nullptr;           // this level's unknown -> row of the next (split) level, -1 if none
     unsigned long long *d_cmask = nullptr;  // node columns with unknowns, per brick (structured levels)
-    double *d_dinv64 = nullptr;             // inverse diagonal (0 where it vanishes), FP64 and FP32
+    double *d_dinv64 = nullptr;             // inverse diagonal (0 where it vanishes), of the cycle's precision
     float *d_dinv32 = nullptr;
     int *d_nbr27 = nullptr;                 // the 27 bricks around each brick (levels that run one-launch legs)
     int seg = 0;                            // column segment (nodes per lane) of an FP32 cycle on this level:
@@ -71,6 +71,8 @@ struct Level {
     long long nodes() const { return ell ? (long long)nrow : (long long)nb * BS; }
 };
 
+constexpr int H_NCOMP = LEVEL_STATS * (int)(sizeof(LevelStat) / sizeof(int));   // its place in Ctx::h_ints
+
 struct Ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -78,7 +80,7 @@ struct Ctx {
     // inverse diagonals, run there beside the coarsening and the coarsest inverse; joined before the build
     // returns
     hipStream_t side = nullptr;
-    hipEvent_t ev_side[2] = {nullptr, nullptr};   // [0] main -> side (inputs ready), [1] side -> main (work done)
+    hipEvent_t ev_side[1] = {nullptr};   // main -> side (inputs ready)
     std::string err;
     // geometry
     int state = 0;  // 0 created, 1 geometry, 2 sigma, 3 built, 4 sources
@@ -165,7 +167,7 @@ struct Ctx {
     int nbat_vec = 0;         // vectors of each kind the solve buffers hold (1 for packed models)
     std::vector<std::pair<int, int>> seg_cache;   // per level: bricks and the tuned segment (4 or 8)
     int *d_ints = nullptr;    // small scratch ints
-    int *h_ints = nullptr;    // pinned
+    int *h_ints = nullptr;    // pinned: scratch (LEVEL_STATS entries), then the number of components
     uint8_t *h_stage = nullptr;   // pinned staging for the host-built tables of the hierarchy
     size_t stage_cap = 0;
     // the library's own stream (all work) and the caller's stream it follows
@@ -467,25 +469,6 @@ void build_topology(Ctx *c, Level &L, const std::vector<uint8_t> &flags, std::ve
     HIPCHK(hipStreamSynchronize(c->stream));
 }
 
-__global__ void k_count_dofs(const double *w, long long stride, Topo topo, int *count)
-{
-    __shared__ int nb[6];
-    __shared__ int cnt;
-    const int b = blockIdx.x, t = threadIdx.x;
-    if (t < 6) nb[t] = topo.nbr[b * 6 + t];
-    if (t == 0) cnt = 0;
-    __syncthreads();
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    double W[6];
-    long long I[6];
-    nbr_index((long long)b * BS, t, tx, ty, tz, nb, I);
-    stored_weights(w, stride, (long long)b * BS, t, I, W);
-    if (diag_of(W) > 0.0) atomicAdd(&cnt, 1);
-    __syncthreads();
-    if (t == 0 && cnt) atomicAdd(count, cnt);
-}
-
 // rows of an ELL level with a positive diagonal (the sum of the row's stored entries, in the order the
 // enumeration of the coarsest level uses), counted by many workgroups
 __global__ __launch_bounds__(256) void k_count_ell_dofs(int n, int K, const int *__restrict__ col,
@@ -505,14 +488,21 @@ __global__ __launch_bounds__(256) void k_count_ell_dofs(int n, int K, const int 
     if (threadIdx.x == 0 && cnt) atomicAdd(count, cnt);
 }
 
-long long count_dofs(Ctx *c, const Level &L)
+constexpr int MAX_LEVELS = 20;
+
+// the statistics of a structured level whose setup kernel is queued (waits for it)
+LevelStat level_stat(Ctx *c, const LevelStat *d_stat)
 {
-    HIPCHK(hipMemsetAsync(c->d_ints, 0, sizeof(int), c->stream));
-    if (L.nb > 0) hipLaunchKernelGGL(k_count_dofs, dim3(L.nb), dim3(NT), 0, c->stream, L.d_w64, L.nodes(), L.topo(), c->d_ints);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    LevelStat *h = (LevelStat *)c->h_ints;
+    HIPCHK(hipMemcpyAsync(h, d_stat, LEVEL_STATS * sizeof(LevelStat), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    return c->h_ints[0];
+    LevelStat a{};
+    for (int i = 0; i < LEVEL_STATS; ++i) {
+        a.count += h[i].count;
+        a.wmax = std::max(a.wmax, h[i].wmax);
+        a.wmin_not = std::max(a.wmin_not, h[i].wmin_not);
+    }
+    return a;
 }
 
 template <typename T>
@@ -1279,6 +1269,16 @@ void alloc_cycle_buffers(Ctx *c, int nb)
     c->nbat = nb;
 }
 
+// inverse diagonals of a level, in the cycle's precision, and, for a structured one, its column masks
+void alloc_dinv(Ctx *c, Level &L)
+{
+    if (c->opt.precision == SPFD_MIXED)
+        L.d_dinv32 = dalloc<float>(c, c->hier_allocs, L.nodes());
+    else
+        L.d_dinv64 = dalloc<double>(c, c->hier_allocs, L.nodes());
+    if (!L.ell) L.d_cmask = dalloc<unsigned long long>(c, c->hier_allocs, L.nb);
+}
+
 // Coarse level whose unknowns are the connected pieces of the 2x2x2
 // aggregates of F (F structured or ELL), with its ELL Galerkin operator.
 Level split_level(Ctx *c, Level &F)
@@ -1360,6 +1360,8 @@ Level split_level(Ctx *c, Level &F)
     HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     C.dofs = c->h_ints[0];
+    alloc_dinv(c, C);
+    HIPCHK(launch_dinv_ell(C.nrow, C.K, C.d_col, C.d_val64, C.d_dinv64, C.d_dinv32, c->stream));
     return C;
 }
 
@@ -1378,18 +1380,22 @@ spfd_status do_build(Ctx *c)
     Grid &g = c->g;
     // 1. bricks of the finest level + input validation
     const size_t nbg = (size_t)g.Gx * g.Gy * g.Gz;
-    uint8_t *d_flags = dalloc<uint8_t>(c, c->hier_allocs, nbg);
-    HIPCHK(hipMemsetAsync(d_flags, 0, nbg, c->stream));
-    HIPCHK(hipMemsetAsync(c->d_ints, 0, 4 * sizeof(int), c->stream));
-    HIPCHK(launch_brick_flags(c->d_labels, c->d_table64, c->nlab, c->voxel_mode ? c->d_sigvox : nullptr, g, d_flags,
-                              c->d_ints, c->stream));
-    uint8_t *hflags = stage(c, nbg);
-    HIPCHK(hipMemcpyAsync(hflags, d_flags, nbg, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    // cleared at once: the levels' statistics, the error word and, right behind it, the brick flags
+    const size_t stat_bytes = MAX_LEVELS * LEVEL_STATS * sizeof(LevelStat);
+    uint8_t *d_head = dalloc<uint8_t>(c, c->hier_allocs, stat_bytes + sizeof(int) + nbg);
+    LevelStat *d_stat = (LevelStat *)d_head;
+    int *d_err = (int *)(d_head + stat_bytes);
+    HIPCHK(hipMemsetAsync(d_head, 0, stat_bytes + sizeof(int) + nbg, c->stream));
+    HIPCHK(launch_brick_flags(c->d_labels, c->d_table64, c->nlab, c->voxel_mode ? c->d_sigvox : nullptr, g,
+                              (uint8_t *)(d_err + 1), d_err, c->stream));
+    uint8_t *hflags = stage(c, sizeof(int) + nbg);
+    HIPCHK(hipMemcpyAsync(hflags, d_err, sizeof(int) + nbg, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    std::vector<uint8_t> flags(hflags, hflags + nbg);
-    if (c->h_ints[0] == 1) return fail(c, SPFD_INVALID_ARG, "a voxel label is not covered by the sigma table");
-    if (c->h_ints[0] == 2) return fail(c, SPFD_INVALID_ARG, "per-voxel sigma must be finite and >= 0");
+    int bad;
+    memcpy(&bad, hflags, sizeof(int));
+    std::vector<uint8_t> flags(hflags + sizeof(int), hflags + sizeof(int) + nbg);
+    if (bad == 1) return fail(c, SPFD_INVALID_ARG, "a voxel label is not covered by the sigma table");
+    if (bad == 2) return fail(c, SPFD_INVALID_ARG, "per-voxel sigma must be finite and >= 0");
     c->lv.emplace_back();
     Level &L0 = c->lv[0];
     L0.N[0] = g.Nx; L0.N[1] = g.Ny; L0.N[2] = g.Nz;
@@ -1397,34 +1403,37 @@ spfd_status do_build(Ctx *c)
     build_topology(c, L0, flags, c->hier_allocs);
     if (L0.nb == 0) return fail(c, SPFD_INVALID_ARG, "no conducting voxel");
     if ((long long)L0.nb * BS > 0x7fffffffLL) return fail(c, SPFD_INVALID_ARG, "grid too large");
-    // 2. finest-level conductances (stored FP64 for setup; label tiles for the solve)
-    L0.d_w64 = dalloc<double>(c, c->hier_allocs, (size_t)3 * L0.nodes());
-    L0.d_w32 = dalloc<float>(c, c->hier_allocs, (size_t)3 * L0.nodes());
-    HIPCHK(launch_weights0(c->d_labels, c->d_table64, c->voxel_mode ? c->d_sigvox : nullptr, g, c->geo4, L0.d_coord,
-                           L0.nb, L0.d_w64, L0.d_w32, c->stream));
-    if (!c->voxel_mode) {
+    // 2. finest-level conductances (stored FP64 for setup; label tiles for the solve) and what else follows from them
+    const long long n_fine = L0.nodes();
+    unsigned long long *emask = dalloc<unsigned long long>(c, c->hier_allocs, (size_t)L0.nb * EMASK);
+    L0.d_w64 = dalloc<double>(c, c->hier_allocs, (size_t)3 * n_fine);
+    if (c->voxel_mode)
+        L0.d_w32 = dalloc<float>(c, c->hier_allocs, (size_t)3 * n_fine);
+    else
         L0.d_tiles = dalloc<uint8_t>(c, c->hier_allocs, (size_t)L0.nb * TILE_BYTES);
-        HIPCHK(launch_label_tiles(c->d_labels, g, L0.d_coord, L0.nb, L0.d_tiles, c->stream));
-    }
+    alloc_dinv(c, L0);
+    HIPCHK(launch_finest_setup(c->d_labels, c->d_table64, c->voxel_mode ? c->d_sigvox : nullptr, g, c->geo4, L0.d_coord,
+                               L0.nb, FinestSetup{L0.d_tiles, L0.d_w64, L0.d_w32, L0.d_dinv64, L0.d_dinv32, L0.d_cmask,
+                                                  emask, d_stat},
+                               c->stream));
     // 3. connected components of the conductor (the gauge of Eq. (3)): on the side stream, beside the
-    //    coarsening, which needs only the number of unknowns (the nodes with a positive diagonal, counted
-    //    here); joined at the end of the build
+    //    coarsening, which needs only the number of unknowns; joined at the end of the build
     int *d_ncomp = dalloc<int>(c, c->hier_allocs, 1);
     {
-        const long long n = L0.nodes();
-        int *parent = dalloc<int>(c, c->hier_allocs, n);
-        int *flag = dalloc<int>(c, c->hier_allocs, n);
-        int *idx = dalloc<int>(c, c->hier_allocs, n);
-        int *tmp = dalloc<int>(c, c->hier_allocs, n / 2048 + 2);
-        c->d_comp = dalloc<int>(c, c->hier_allocs, n);
+        int *parent = dalloc<int>(c, c->hier_allocs, n_fine);
+        int *flag = dalloc<int>(c, c->hier_allocs, n_fine);
+        int *idx = dalloc<int>(c, c->hier_allocs, n_fine);
+        int *tmp = dalloc<int>(c, c->hier_allocs, n_fine / 2048 + 2);
+        c->d_comp = dalloc<int>(c, c->hier_allocs, n_fine);
         HIPCHK(hipEventRecord(c->ev_side[0], c->stream));
         HIPCHK(hipStreamWaitEvent(c->side, c->ev_side[0], 0));
-        HIPCHK(launch_components(L0.d_w64, n, L0.topo(), parent, flag, idx, tmp, c->d_comp, nullptr, d_ncomp, c->side));
-        L0.dofs = count_dofs(c, L0);
+        HIPCHK(launch_components(emask, L0.topo(), parent, flag, idx, tmp, c->d_comp, d_ncomp, c->side));
+        HIPCHK(hipMemcpyAsync(c->h_ints + H_NCOMP, d_ncomp, sizeof(int), hipMemcpyDeviceToHost, c->side));
+        L0.dofs = level_stat(c, d_stat).count;
     }
     // 4. coarsening: 2x2x2 aggregation until the level is small enough; from
     //    level split_level on, aggregates are split into their connected pieces
-    while (c->lv.back().dofs > c->opt.coarsest_max && c->lv.size() < 20) {
+    while (c->lv.back().dofs > c->opt.coarsest_max && c->lv.size() < MAX_LEVELS) {
         const int l = (int)c->lv.size() - 1;
         Level &F = c->lv[l];
         const bool split = !c->opt.no_split && (l >= c->opt.split_level || F.ell);
@@ -1460,52 +1469,36 @@ spfd_status do_build(Ctx *c)
         C.d_w32 = dalloc<float>(c, c->hier_allocs, (size_t)3 * C.nodes());
         HIPCHK(launch_galerkin(F.d_w64, F.nodes(), F.d_slot_of, F.G[0], F.G[1], F.G[2], F.N[0], F.N[1], F.N[2], C.d_coord,
                                C.nb, C.d_w64, C.d_w32, C.nodes(), c->stream));
+        // inverse diagonals (first Chebyshev steps folded into neighbouring kernels) and column masks (the stencil
+        // kernels skip columns without unknowns)
+        alloc_dinv(c, C);
+        LevelStat *st = d_stat + c->lv.size() * LEVEL_STATS;
+        HIPCHK(launch_struct_setup(C.d_w64, C.d_w32, C.nodes(), C.topo(), C.d_dinv64, C.d_dinv32, C.d_cmask, st,
+                                   c->stream));
+        const LevelStat a = level_stat(c, st);
+        C.dofs = a.count;
         // the first coarse level of an FP32 cycle is bandwidth-bound and smoothed hardest: its smoothing
         // and restriction read FP16 weights scaled so the largest is 2^15 (relative rounding 2^-11;
         // the Galerkin operators below it come from the FP64 weights).  If the smallest nonzero
         // weight would then fall below FP16's normal range (2^-14), the FP32 weights are kept.
         if (c->opt.precision == SPFD_MIXED && c->lv.size() == 1 && !c->opt.level1_fp32) {
-            unsigned *dm = dalloc<unsigned>(c, c->hier_allocs, 2);
-            const unsigned init[2] = {0u, 0x7f800000u};
-            memcpy(c->h_ints, init, sizeof(init));
-            HIPCHK(hipMemcpyAsync(dm, c->h_ints, sizeof(init), hipMemcpyHostToDevice, c->stream));
-            HIPCHK(launch_wmax(C.d_w32, 3LL * C.nodes(), dm, c->stream));
-            HIPCHK(hipMemcpyAsync(c->h_ints, dm, sizeof(init), hipMemcpyDeviceToHost, c->stream));
-            HIPCHK(hipStreamSynchronize(c->stream));
             float mw, mp;
-            memcpy(&mw, &c->h_ints[0], sizeof(float));
-            memcpy(&mp, &c->h_ints[1], sizeof(float));
+            const unsigned least = ~a.wmin_not;
+            memcpy(&mw, &a.wmax, sizeof(float));
+            memcpy(&mp, &least, sizeof(float));
             if (mw > 0.0f && (double)mp / mw * 32768.0 >= 0x1p-14) {
                 C.w16s = mw / 32768.0f;
                 C.d_w16 = dalloc<uint16_t>(c, c->hier_allocs, (size_t)3 * C.nodes());
                 HIPCHK(launch_w16(C.d_w32, 3LL * C.nodes(), 1.0f / C.w16s, C.d_w16, c->stream));
             }
         }
-        HIPCHK(hipStreamSynchronize(c->stream));
         c->lv.push_back(std::move(C));
-        c->lv.back().dofs = count_dofs(c, c->lv.back());
     }
-    // column masks of the structured levels (the stencil kernels skip columns without unknowns) and
-    // the inverse diagonals (first Chebyshev steps folded into neighbouring kernels): on the side stream,
-    // after the components, beside the coarsest inverse; joined with them
-    HIPCHK(hipEventRecord(c->ev_side[0], c->stream));
-    HIPCHK(hipStreamWaitEvent(c->side, c->ev_side[0], 0));
-    for (Level &L : c->lv) {
-        L.d_dinv64 = dalloc<double>(c, c->hier_allocs, L.nodes());
-        L.d_dinv32 = dalloc<float>(c, c->hier_allocs, L.nodes());
-        if (L.ell) {
-            HIPCHK(launch_dinv_ell(L.nrow, L.K, L.d_col, L.d_val64, L.d_dinv64, L.d_dinv32, c->side));
-        } else if (L.nb > 0) {
-            if (L.nb <= LEG_MOST) {
-                L.d_nbr27 = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 27);
-                HIPCHK(launch_nbr27(L.d_slot_of, L.d_coord, L.nb, L.G, L.d_nbr27, c->side));
-            }
-            L.d_cmask = dalloc<unsigned long long>(c, c->hier_allocs, L.nb);
-            HIPCHK(launch_col_masks(L.d_w64, L.nodes(), L.topo(), L.d_cmask, c->side));
-            HIPCHK(launch_dinv_struct(L.d_w64, L.nodes(), Topo{L.nb, L.d_nbr}, L.d_dinv64, L.d_dinv32, c->side));
+    for (Level &L : c->lv)
+        if (!L.ell && L.nb > 0 && L.nb <= LEG_MOST) {
+            L.d_nbr27 = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 27);
+            HIPCHK(launch_nbr27(L.d_slot_of, L.d_coord, L.nb, L.G, L.d_nbr27, c->stream));
         }
-    }
-    HIPCHK(hipEventRecord(c->ev_side[1], c->side));
     // 5. coarsest level: dense pseudo-inverse
     {
         Level &C = c->lv.back();
@@ -1513,17 +1506,16 @@ spfd_status do_build(Ctx *c)
         c->d_node_cdof = dalloc<int>(c, c->hier_allocs, C.nodes());
         c->d_cdof_node = dalloc<int>(c, c->hier_allocs, maxd);
         c->d_cadj = dalloc<int>(c, c->hier_allocs, (size_t)maxd * 6);
+        // (the enumeration counts the same unknowns)
+        if (C.dofs > maxd)
+            return fail(c, SPFD_INVALID_ARG, "coarsest level too large (grid cannot be coarsened further)");
+        c->ncoarse = (int)C.dofs;
         if (C.ell)
             HIPCHK(launch_coarse_enum_ell(C.nrow, C.K, C.d_col, C.d_val64, c->d_node_cdof, c->d_cdof_node, c->d_ints,
                                           maxd, c->stream));
         else
             HIPCHK(launch_coarse_setup(C.d_w64, C.nodes(), C.topo(), c->d_node_cdof, c->d_cdof_node, c->d_cadj,
                                        c->d_ints, maxd, c->stream));
-        HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        c->ncoarse = c->h_ints[0];
-        if (c->ncoarse > maxd)
-            return fail(c, SPFD_INVALID_ARG, "coarsest level too large (grid cannot be coarsened further)");
         c->d_Ainv = dalloc<double>(c, c->hier_allocs, (size_t)c->ncoarse * c->ncoarse + 1);
         c->d_cwork = dalloc<int>(c, c->hier_allocs, coarse_factor_work_ints(maxd));
         if (C.ell)
@@ -1535,20 +1527,16 @@ spfd_status do_build(Ctx *c)
         double *dwork = dalloc<double>(c, c->hier_allocs, dense_inverse_work_doubles(c->ncoarse));
         HIPCHK(launch_coarse_factor(c->ncoarse, c->d_Ainv, c->d_cwork, dwork, c->stream));
     }
-    // join the side stream (components, masks, inverse diagonals); the component count sizes the gauge's
-    // buffers
+    // join the side stream (its components are counted beside the inverse); their number sizes the gauge's buffers
     {
-        HIPCHK(hipStreamWaitEvent(c->stream, c->ev_side[1], 0));
-        HIPCHK(hipMemcpyAsync(c->h_ints, d_ncomp, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        c->ncomp = c->h_ints[0];
-        const Level &F0 = c->lv[0];   // (the coarsening above may have moved the level vector)
-        const long long n = F0.nodes();
+        HIPCHK(hipStreamSynchronize(c->side));
+        c->ncomp = c->h_ints[H_NCOMP];
         c->d_counts = dalloc<int>(c, c->hier_allocs, c->ncomp + 1);
         c->d_means = dalloc<double>(c, c->hier_allocs, c->ncomp + 1);
-        c->d_cpart = dalloc<double>(c, c->hier_allocs, comp_mean_parts(F0.nb));
-        HIPCHK(hipMemsetAsync(c->d_counts, 0, (c->ncomp + 1) * sizeof(int), c->stream));
-        HIPCHK(launch_comp_counts(c->d_comp, n, c->d_counts, c->stream));
+        c->d_cpart = dalloc<double>(c, c->hier_allocs, comp_mean_parts(c->lv[0].nb));
+        HIPCHK(hipMemsetAsync(c->d_counts, 0, (c->ncomp + 1) * sizeof(int), c->side));
+        HIPCHK(launch_comp_counts(c->d_comp, n_fine, c->d_counts, c->side));
+        HIPCHK(hipStreamSynchronize(c->side));
     }
     chebyshev_coefficients(c);
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -2406,7 +2394,7 @@ spfd_status spfd_create(int device, void *hip_stream, const spfd_allocator *allo
         HIPCHK(hipEventCreateWithFlags(&c->ev_user, hipEventDisableTiming));
         for (hipEvent_t &e : c->ev_it) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         c->d_ints = dalloc<int>(c, c->geo_allocs, 64);
-        HIPCHK(hipHostMalloc((void **)&c->h_ints, 64 * sizeof(int), hipHostMallocDefault));
+        HIPCHK(hipHostMalloc((void **)&c->h_ints, (H_NCOMP + 1) * sizeof(int), hipHostMallocDefault));
     } catch (const HipFail &f) {
         release_device(c);
         if (c->ev_user) (void)hipEventDestroy(c->ev_user);

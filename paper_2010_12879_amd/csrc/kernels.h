@@ -72,28 +72,40 @@ struct Grid {
 // ---------------------------------------------------------------- setup
 hipError_t launch_brick_flags(const uint8_t *labels, const double *table, int nlab, const double *sig_vox,
                               const Grid &g, uint8_t *flags, int *err, hipStream_t s);
-hipError_t launch_label_tiles(const uint8_t *labels, const Grid &g, const int4 *coord, int nb, uint8_t *tiles,
-                              hipStream_t s);
-hipError_t launch_weights0(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
-                           const double geo4[3], const int4 *coord, int nb, double *w64, float *w32, hipStream_t s);
-// largest and smallest positive of n non-negative weights (bits atomically maxed into out[0], which
-// starts at 0, and minned into out[1], which starts at the bits of +inf), and FP16 copies
-// h = w * inv rounded to nearest
-hipError_t launch_wmax(const float *w, long long n, unsigned *out, hipStream_t s);
+// What the build needs to know of a structured level, gathered by many workgroups: LEVEL_STATS entries, all zero at
+// the start, to be added up (count) and maximised (bits of the largest weight, complement of the bits of the
+// smallest positive one, 0x807fffff or more when there is none)
+constexpr int LEVEL_STATS = 64;
+struct LevelStat {
+    unsigned count, wmax, wmin_not, pad;
+};
+constexpr int EMASK = 32;   // words per brick: per node layer the edges to +x, +y, +z that conduct, and the unknowns
+struct FinestSetup {
+    uint8_t *tiles;   // label form
+    double *w64;
+    float *w32;       // conductivity per voxel
+    double *dinv64;   // one of the two
+    float *dinv32;
+    unsigned long long *cmask, *emask;
+    LevelStat *stat;
+};
+hipError_t launch_finest_setup(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
+                               const double geo4[3], const int4 *coord, int nb, const FinestSetup &out, hipStream_t s);
+hipError_t launch_struct_setup(const double *w64, const float *w32, long long stride, Topo topo, double *d64,
+                               float *d32, unsigned long long *cmask, LevelStat *stat, hipStream_t s);
+// FP16 copies h = w * inv rounded to nearest
 hipError_t launch_w16(const float *w, long long n, float inv, uint16_t *h, hipStream_t s);
 hipError_t launch_galerkin(const double *wf, long long fstride, const int *f_slot_of, int fGx, int fGy, int fGz,
                            int fNx, int fNy, int fNz, const int4 *ccoord, int cnb, double *wc64, float *wc32,
                            long long cstride, hipStream_t s);
-hipError_t launch_components(const double *w64, long long stride, Topo topo, int *parent, int *flag, int *idx,
-                             int *scan_tmp, int *comp, int *counts_or_null, int *ncomp_dev, hipStream_t s);
+hipError_t launch_components(const unsigned long long *emask, Topo topo, int *parent, int *flag, int *idx,
+                             int *scan_tmp, int *comp, int *ncomp_dev, hipStream_t s);
 hipError_t launch_comp_counts(const int *comp, long long n, int *counts, hipStream_t s);
 hipError_t launch_coarse_setup(const double *w64, long long stride, Topo topo, int *dof_of_node, int *node_of_dof,
                                int *adj, int *ndof_dev, int maxdof, hipStream_t s);
 hipError_t launch_coarse_assemble_brick(const double *w64, long long stride, Topo topo, const int *node_of_dof,
                                         const int *adj, int n, double *A, hipStream_t s);
 // dense pseudo-inverse in place; work: 2n ints + n doubles (+1 int of padding)
-// per brick, the node columns (tx,ty) that hold unknowns (bit tx + 8 ty)
-hipError_t launch_col_masks(const double *w64, long long stride, Topo topo, unsigned long long *mask, hipStream_t s);
 // A <- inverse of the regularised coarsest matrix (work: coarse_factor_work_ints(n)
 // ints; dwork: dense_inverse_work_doubles(n) doubles)
 size_t coarse_factor_work_ints(int n);
@@ -393,10 +405,8 @@ hipError_t launch_restrict_members(const FineLevelT<T> &f, long long nrows, cons
                                    const int *memb = nullptr);
 // direct member table memb[p*8 + j] of the restriction (*over = 1 if an aggregate has more than 8 members)
 hipError_t launch_members8(int nc, const int *mptr, const int *mem, int *memb, int *over, hipStream_t s);
-// inverse diagonals (0 where the diagonal vanishes): ELL level, structured level
+// inverse diagonals (0 where the diagonal vanishes), into d64 or d32 or both
 hipError_t launch_dinv_ell(int n, int K, const int *col, const double *val, double *d64, float *d32, hipStream_t s);
-hipError_t launch_dinv_struct(const double *w64, long long stride, Topo topo, double *d64, float *d32,
-                              hipStream_t s);
 template <typename T>
 hipError_t launch_prolong_agg(long long n, const int *agg, T *x, const T *xc, T scale, const Scal *sc,
                               const Batch &bt, hipStream_t s);

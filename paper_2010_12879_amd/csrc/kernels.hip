@@ -53,71 +53,96 @@ __device__ __forceinline__ void op_stage(const OpArgs<T> &op, int b, T *tile)
 // setup kernels
 // ============================================================================
 
-// Mark the finest-level bricks that contain a node of a conducting voxel and
-// validate labels / conductivities (err: 1 = label out of table, 2 = bad sigma).
-__global__ void k_brick_flags(const uint8_t *__restrict__ labels, const double *__restrict__ table, int nlab,
-                              const double *__restrict__ sig_vox, Grid g, uint8_t *flags, int *err)
+// Mark the finest-level bricks that contain a node of a conducting voxel and validate labels / conductivities
+// (err: 1 = label out of table, 2 = bad sigma).  A thread takes 16 consecutive voxels (one 16-byte load of labels
+// where the array is aligned), and stores the flags of the few bricks they touch where these read as unmarked: one
+// voxel per thread with eight stores each was bound by the stores (250x150x900 voxels: 107 us; this form 21 us).
+constexpr int FLAG_V = 16;
+
+template <bool VOX>
+__global__ __launch_bounds__(256) void k_brick_flags(const uint8_t *__restrict__ labels,
+                                                     const double *__restrict__ table, int nlab,
+                                                     const double *__restrict__ sig_vox, Grid g, uint8_t *flags,
+                                                     int *err)
 {
+    // per label: 0 air, 1 conductor, 2 not in the table
+    __shared__ uint8_t kind[256];
+    if (!VOX) {
+        kind[threadIdx.x] = (int)threadIdx.x < nlab ? table[threadIdx.x] > 0.0 : 2;
+        __syncthreads();
+    }
     const long long nvox = (long long)g.nx * g.ny * g.nz;
-    for (long long v = (long long)blockIdx.x * blockDim.x + threadIdx.x; v < nvox;
-         v += (long long)gridDim.x * blockDim.x) {
-        double s;
-        if (sig_vox) {
-            s = sig_vox[v];
-            if (!(s >= 0.0) || !isfinite(s)) { *err = 2; continue; }
+    const bool wide = !VOX && ((uintptr_t)labels & 15) == 0;
+    for (long long v0 = ((long long)blockIdx.x * 256 + threadIdx.x) * FLAG_V; v0 < nvox;
+         v0 += (long long)gridDim.x * 256 * FLAG_V) {
+        const int n = nvox - v0 < FLAG_V ? (int)(nvox - v0) : FLAG_V;
+        uint32_t q[4] = {0u, 0u, 0u, 0u};
+        uint32_t pos = 0u;   // bit u: voxel v0 + u conducts
+        if (VOX) {
+#pragma unroll
+            for (int u = 0; u < FLAG_V; ++u) {
+                const double sg = sig_vox[u < n ? v0 + u : v0];
+                if (u < n && (!(sg >= 0.0) || !isfinite(sg))) *err = 2;
+                else if (u < n && sg > 0.0) pos |= 1u << u;
+            }
         } else {
-            const int lab = labels[v];
-            if (lab >= nlab) { *err = 1; continue; }
-            s = table[lab];
+            if (wide && n == FLAG_V) {
+                const uint4 w = *(const uint4 *)(labels + v0);
+                q[0] = w.x;
+                q[1] = w.y;
+                q[2] = w.z;
+                q[3] = w.w;
+            } else {
+#pragma unroll
+                for (int u = 0; u < FLAG_V; ++u) q[u / 4] |= (uint32_t)labels[u < n ? v0 + u : v0] << (8 * (u % 4));
+            }
+#pragma unroll
+            for (int u = 0; u < FLAG_V; ++u) {
+                const int k = kind[(q[u / 4] >> (8 * (u % 4))) & 255u];
+                if (u < n && k == 2) *err = 1;
+                if (u < n && k == 1) pos |= 1u << u;
+            }
         }
-        if (!(s > 0.0)) continue;
-        const int i = (int)(v % g.nx), j = (int)((v / g.nx) % g.ny), k = (int)(v / ((long long)g.nx * g.ny));
-        for (int c = 0; c < 8; ++c) {
-            const int bi = (i + (c & 1)) >> 3, bj = (j + ((c >> 1) & 1)) >> 3, bk = (k + (c >> 2)) >> 3;
-            flags[bi + (long long)g.Gx * (bj + (long long)g.Gy * bk)] = 1;
+        if (pos == 0u) continue;
+        int i, j, k;
+        if (nvox <= 0x7fffffffLL) {
+            const unsigned v = (unsigned)v0, r = v / (unsigned)g.nx;
+            i = (int)(v - r * (unsigned)g.nx);
+            k = (int)(r / (unsigned)g.ny);
+            j = (int)(r - (unsigned)k * (unsigned)g.ny);
+        } else {
+            const long long r = v0 / g.nx;
+            i = (int)(v0 - r * g.nx);
+            k = (int)(r / g.ny);
+            j = (int)(r - (long long)k * g.ny);
+        }
+        // row by row: the nodes that conducting voxels touch, eight to a brick
+        for (int left = n; left > 0;) {
+            const int len = left < g.nx - i ? left : g.nx - i;
+            const uint32_t p = pos & ((1u << len) - 1u);
+            int bi = i >> 3;
+            for (uint32_t m = (p | p << 1) << (i & 7); m != 0u; m >>= 8, ++bi)
+                if (m & 255u)
+                    for (int bk = k >> 3; bk <= (k + 1) >> 3; ++bk)
+                        for (int bj = j >> 3; bj <= (j + 1) >> 3; ++bj) {
+                            uint8_t *f = flags + bi + (long long)g.Gx * (bj + (long long)g.Gy * bk);
+                            if (*f == 0) *f = 1;
+                        }
+            pos >>= len;
+            left -= len;
+            i = 0;
+            if (++j == g.ny) {
+                j = 0;
+                ++k;
+            }
         }
     }
 }
 
-// out[0]: bits of the largest weight (starts at 0), out[1]: bits of the smallest positive one (starts at
-// the bits of +inf); non-negative floats order like their bit patterns
-__global__ __launch_bounds__(256) void k_wmax(const float *w, long long n, unsigned *out)
-{
-    __shared__ float smax[4], smin[4];
-    float m = 0.0f, mp = INFINITY;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const float v = w[i];
-        m = fmaxf(m, v);
-        if (v > 0.0f) mp = fminf(mp, v);
-    }
-    // wave, then workgroup, then one atomic per workgroup
-    for (int off = 32; off > 0; off >>= 1) {
-        m = fmaxf(m, __shfl_down(m, off, 64));
-        mp = fminf(mp, __shfl_down(mp, off, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        smax[threadIdx.x >> 6] = m;
-        smin[threadIdx.x >> 6] = mp;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < 4; ++k) {
-            m = fmaxf(m, smax[k]);
-            mp = fminf(mp, smin[k]);
-        }
-        atomicMax(out, __float_as_uint(m));
-        atomicMin(out + 1, __float_as_uint(mp));
-    }
-}
 __global__ void k_w16(const float *w, long long n, float inv, uint16_t *h)
 {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
         h[i] = __half_as_ushort(__float2half_rn(w[i] * inv));
-}
-hipError_t launch_wmax(const float *w, long long n, unsigned *out, hipStream_t s)
-{
-    SPFD_LAUNCH(k_wmax, dim3(1024), dim3(256), 0, s, w, n, out);
-    return hipGetLastError();
 }
 hipError_t launch_w16(const float *w, long long n, float inv, uint16_t *h, hipStream_t s)
 {
@@ -129,86 +154,178 @@ hipError_t launch_brick_flags(const uint8_t *labels, const double *table, int nl
                               const Grid &g, uint8_t *flags, int *err, hipStream_t s)
 {
     const long long nvox = (long long)g.nx * g.ny * g.nz;
-    long long blocks = (nvox + 255) / 256;
+    long long blocks = (nvox + 256 * FLAG_V - 1) / (256 * FLAG_V);
     if (blocks > 65536) blocks = 65536;
-    SPFD_LAUNCH(k_brick_flags, dim3((unsigned)blocks), dim3(256), 0, s, labels, table, nlab, sig_vox, g,
-                       flags, err);
+    if (sig_vox)
+        SPFD_LAUNCH(k_brick_flags<true>, dim3((unsigned)blocks), dim3(256), 0, s, labels, table, nlab, sig_vox, g,
+                    flags, err);
+    else
+        SPFD_LAUNCH(k_brick_flags<false>, dim3((unsigned)blocks), dim3(256), 0, s, labels, table, nlab, sig_vox, g,
+                    flags, err);
     return hipGetLastError();
 }
 
-// label tile of a brick: voxels (8*bx - 1 + a, 8*by - 1 + b, 8*bz - 1 + c), a,b,c in 0..8; outside = air (0)
-__global__ void k_label_tiles(const uint8_t *__restrict__ labels, Grid g, const int4 *__restrict__ coord,
-                              uint8_t *tiles)
+// Masks of one brick from the eight waves' node layers, and its unknowns counted into the level's statistics
+__device__ __forceinline__ void brick_masks(bool unknown, int b, unsigned long long *__restrict__ cmask,
+                                            LevelStat *stat, unsigned long long nm[8])
 {
-    const int b = blockIdx.x;
-    const int4 c = coord[b];
-    for (int idx = threadIdx.x; idx < TILE_BYTES; idx += blockDim.x) {
-        uint8_t lab = 0;
-        if (idx < TILE_VOX) {
-            const int a = idx % 9, bb = (idx / 9) % 9, cc = idx / 81;
-            const int i = c.x * 8 - 1 + a, j = c.y * 8 - 1 + bb, k = c.z * 8 - 1 + cc;
-            if (i >= 0 && j >= 0 && k >= 0 && i < g.nx && j < g.ny && k < g.nz)
-                lab = labels[i + (long long)g.nx * (j + (long long)g.ny * k)];
+    const int t = threadIdx.x;
+    const unsigned long long m = __ballot(unknown);
+    if ((t & 63) == 0) nm[t >> 6] = m;
+    __syncthreads();
+    if (t == 0) {
+        unsigned long long any = 0ull;
+        unsigned count = 0;
+        for (int k = 0; k < 8; ++k) {
+            any |= nm[k];
+            count += (unsigned)__popcll(nm[k]);
         }
-        tiles[(long long)b * TILE_BYTES + idx] = lab;
+        cmask[b] = any;
+        if (count) atomicAdd(&stat[b % LEVEL_STATS].count, count);
     }
 }
 
-hipError_t launch_label_tiles(const uint8_t *labels, const Grid &g, const int4 *coord, int nb, uint8_t *tiles,
-                              hipStream_t s)
+// The finest level, one workgroup per brick: stored conductances M_e (Eq. (3): mean sigma of the 4 voxels sharing
+// the edge times dual area / length) of the edges to +x, +y, +z (FP32 too with a conductivity per voxel), label
+// tiles (label form: voxels (8 bx - 1 + a, 8 by - 1 + b, 8 bz - 1 + c), a, b, c in 0..8; outside = air (0)), inverse
+// diagonals, the node columns with unknowns, bit masks of the conducting edges and of the unknowns for the
+// components, and the number of unknowns.  All of it follows from the 9x9x9 voxels, staged in LDS once; as six
+// kernels, of which four read the stored weights again, this was 0.54 ms at 8.9 M unknowns; in one it is 117 us, bound
+// by the bytes it writes.
+template <bool VOX>
+__global__ __launch_bounds__(NT) void k_finest_setup(const uint8_t *__restrict__ labels,
+                                                     const double *__restrict__ table,
+                                                     const double *__restrict__ sig_vox, Grid g, double gx, double gy,
+                                                     double gz, const int4 *__restrict__ coord, long long stride,
+                                                     FinestSetup out)
+{
+    __shared__ double tile[TILE_VOX + 7];
+    __shared__ unsigned long long nm[8];
+    const int b = blockIdx.x, t = threadIdx.x;
+    const int4 c = coord[b];
+#pragma unroll
+    for (int idx = t; idx < TILE_BYTES; idx += NT) {
+        uint8_t lab = 0;
+        double sg = 0.0;
+        if (idx < TILE_VOX) {
+            const int i = c.x * 8 - 1 + idx % 9, j = c.y * 8 - 1 + (idx / 9) % 9, k = c.z * 8 - 1 + idx / 81;
+            if (i >= 0 && j >= 0 && k >= 0 && i < g.nx && j < g.ny && k < g.nz) {
+                const long long v = i + (long long)g.nx * (j + (long long)g.ny * k);
+                if (VOX) {
+                    sg = sig_vox[v];
+                } else {
+                    lab = labels[v];
+                    sg = table[lab];
+                }
+            }
+            tile[idx] = sg;
+        }
+        if (!VOX) out.tiles[(long long)b * TILE_BYTES + idx] = lab;
+    }
+    __syncthreads();
+    int tx, ty, tz;
+    brick_xyz(t, tx, ty, tz);
+    double W[6];
+    const double geo4[3] = {gx, gy, gz};
+    tile_weights(tile, tx, ty, tz, geo4, W);
+    const long long n = (long long)b * BS + t;
+    out.w64[n] = W[NPX];
+    out.w64[stride + n] = W[NPY];
+    out.w64[2 * stride + n] = W[NPZ];
+    if (VOX) {
+        out.w32[n] = (float)W[NPX];
+        out.w32[stride + n] = (float)W[NPY];
+        out.w32[2 * stride + n] = (float)W[NPZ];
+    }
+    double D;
+    {
+        // the sum of the rounded weights, as every reader of the stored ones forms it (no products fused into it)
+#pragma clang fp contract(off)
+        D = ((((W[0] + W[1]) + W[2]) + W[3]) + W[4]) + W[5];
+    }
+    const double v = D > 0.0 ? 1.0 / D : 0.0;
+    if (out.dinv64) out.dinv64[n] = v;
+    if (out.dinv32) out.dinv32[n] = (float)v;
+    const unsigned long long ex = __ballot(W[NPX] > 0.0), ey = __ballot(W[NPY] > 0.0), ez = __ballot(W[NPZ] > 0.0);
+    brick_masks(D > 0.0, b, out.cmask, out.stat, nm);
+    if ((t & 63) == 0) {
+        unsigned long long *e = out.emask + (long long)b * EMASK + tz;
+        e[0] = ex;
+        e[8] = ey;
+        e[16] = ez;
+        e[24] = nm[tz];
+    }
+}
+
+hipError_t launch_finest_setup(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
+                               const double geo4[3], const int4 *coord, int nb, const FinestSetup &out, hipStream_t s)
 {
     if (nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_label_tiles, dim3(nb), dim3(256), 0, s, labels, g, coord, tiles);
+    if (sig_vox ? !out.w32 : !out.tiles) return hipErrorInvalidValue;
+    if (sig_vox)
+        SPFD_LAUNCH(k_finest_setup<true>, dim3(nb), dim3(NT), 0, s, labels, table, sig_vox, g, geo4[0], geo4[1],
+                    geo4[2], coord, (long long)nb * BS, out);
+    else
+        SPFD_LAUNCH(k_finest_setup<false>, dim3(nb), dim3(NT), 0, s, labels, table, sig_vox, g, geo4[0], geo4[1],
+                    geo4[2], coord, (long long)nb * BS, out);
     return hipGetLastError();
 }
 
-__device__ __forceinline__ double vox_sig(const uint8_t *labels, const double *table, const double *sig_vox,
-                                          const Grid &g, int i, int j, int k)
+// A coarse structured level from its stored weights: inverse diagonals (0 where the diagonal vanishes), the node
+// columns with unknowns, the number of unknowns, and the largest and smallest positive FP32 weight
+__global__ __launch_bounds__(NT) void k_struct_setup(const double *__restrict__ w, const float *__restrict__ w32,
+                                                     long long stride, Topo topo, double *__restrict__ d64,
+                                                     float *__restrict__ d32, unsigned long long *__restrict__ cmask,
+                                                     LevelStat *stat)
 {
-    if (i < 0 || j < 0 || k < 0 || i >= g.nx || j >= g.ny || k >= g.nz) return 0.0;
-    const long long v = i + (long long)g.nx * (j + (long long)g.ny * k);
-    return sig_vox ? sig_vox[v] : table[labels[v]];
-}
-
-// Stored finest-level conductances M_e (Eq. (3)) for the edges to +x, +y, +z
-// of every brick node: mean sigma of the 4 voxels sharing the edge times
-// dual area / length.
-__global__ void k_weights0(const uint8_t *__restrict__ labels, const double *__restrict__ table,
-                           const double *__restrict__ sig_vox, Grid g, double gx, double gy, double gz,
-                           const int4 *__restrict__ coord, double *w64, float *w32, long long stride)
-{
+    __shared__ unsigned long long nm[8];
+    __shared__ float smax[8], smin[8];
     const int b = blockIdx.x, t = threadIdx.x;
     int tx, ty, tz;
     brick_xyz(t, tx, ty, tz);
-    const int4 c = coord[b];
-    const int i = c.x * 8 + tx, j = c.y * 8 + ty, k = c.z * 8 + tz;
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    if (i < g.Nx && j < g.Ny && k < g.Nz) {
-        sx = ((vox_sig(labels, table, sig_vox, g, i, j - 1, k - 1) + vox_sig(labels, table, sig_vox, g, i, j, k - 1)) +
-              vox_sig(labels, table, sig_vox, g, i, j - 1, k)) + vox_sig(labels, table, sig_vox, g, i, j, k);
-        sy = ((vox_sig(labels, table, sig_vox, g, i - 1, j, k - 1) + vox_sig(labels, table, sig_vox, g, i, j, k - 1)) +
-              vox_sig(labels, table, sig_vox, g, i - 1, j, k)) + vox_sig(labels, table, sig_vox, g, i, j, k);
-        sz = ((vox_sig(labels, table, sig_vox, g, i - 1, j - 1, k) + vox_sig(labels, table, sig_vox, g, i, j - 1, k)) +
-              vox_sig(labels, table, sig_vox, g, i - 1, j, k)) + vox_sig(labels, table, sig_vox, g, i, j, k);
+    int nb[6];
+    brick_nbrs(topo.nbr, b, nb);
+    const long long base = (long long)b * BS;
+    long long I[6];
+    nbr_index(base, t, tx, ty, tz, nb, I);
+    double W[6];
+    stored_weights(w, stride, base, t, I, W);
+    float m = 0.0f, mp = INFINITY;
+    for (int d = 0; d < 3; ++d) {
+        const float v = w32[d * stride + base + t];
+        m = fmaxf(m, v);
+        if (v > 0.0f) mp = fminf(mp, v);
     }
-    const long long n = (long long)b * BS + t;
-    const double wx = sx * gx, wy = sy * gy, wz = sz * gz;
-    w64[n] = wx;
-    w64[stride + n] = wy;
-    w64[2 * stride + n] = wz;
-    if (w32) {
-        w32[n] = (float)wx;
-        w32[stride + n] = (float)wy;
-        w32[2 * stride + n] = (float)wz;
+    const double D = diag_of(W);
+    const double v = D > 0.0 ? 1.0 / D : 0.0;
+    if (d64) d64[base + t] = v;
+    if (d32) d32[base + t] = (float)v;
+    for (int off = 32; off > 0; off >>= 1) {
+        m = fmaxf(m, __shfl_down(m, off, 64));
+        mp = fminf(mp, __shfl_down(mp, off, 64));
+    }
+    if ((t & 63) == 0) {
+        smax[tz] = m;
+        smin[tz] = mp;
+    }
+    brick_masks(D > 0.0, b, cmask, stat, nm);   // (its barrier also orders smax and smin)
+    if (t == 0) {
+        for (int k = 0; k < 8; ++k) {
+            m = fmaxf(m, smax[k]);
+            mp = fminf(mp, smin[k]);
+        }
+        // non-negative floats order like their bit patterns; the smallest as a largest of the complements
+        atomicMax(&stat[b % LEVEL_STATS].wmax, __float_as_uint(m));
+        atomicMax(&stat[b % LEVEL_STATS].wmin_not, ~__float_as_uint(mp));
     }
 }
 
-hipError_t launch_weights0(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
-                           const double geo4[3], const int4 *coord, int nb, double *w64, float *w32, hipStream_t s)
+hipError_t launch_struct_setup(const double *w64, const float *w32, long long stride, Topo topo, double *d64,
+                               float *d32, unsigned long long *cmask, LevelStat *stat, hipStream_t s)
 {
-    if (nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_weights0, dim3(nb), dim3(NT), 0, s, labels, table, sig_vox, g, geo4[0], geo4[1], geo4[2],
-                       coord, w64, w32, (long long)nb * BS);
+    if (topo.nb <= 0) return hipSuccess;
+    SPFD_LAUNCH(k_struct_setup, dim3(topo.nb), dim3(NT), 0, s, w64, w32, stride, Topo{topo.nb, topo.nbr}, d64, d32,
+                cmask, stat);
     return hipGetLastError();
 }
 
@@ -301,21 +418,6 @@ __device__ __forceinline__ void punite(int *p, int a, int b)
     }
 }
 
-__global__ void k_cc_init(const double *__restrict__ w, long long stride, Topo topo, int *parent)
-{
-    const int b = blockIdx.x, t = threadIdx.x;
-    int nb[6];
-    brick_nbrs(topo.nbr, b, nb);
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    double W[6];
-    const long long base = (long long)b * BS;
-    long long I[6];
-    nbr_index(base, t, tx, ty, tz, nb, I);
-    stored_weights(w, stride, base, t, I, W);
-    parent[base + t] = diag_of(W) > 0.0 ? (int)(base + t) : -1;
-}
-
 // union-find in LDS over the conducting edges inside one brick
 __device__ __forceinline__ int lfind(int *p, int x)
 {
@@ -345,52 +447,76 @@ __device__ __forceinline__ void lunite(int *p, int a, int b)
 // storing every node's brick-local root as its parent; then, after the kernel
 // boundary, across the brick faces only (global union-find), so the
 // device-wide atomics see short chains.
-__global__ void k_cc_local(const double *__restrict__ w, long long stride, int *parent)
+// Edges and unknowns come from the finest level's bit masks, 256 B per brick, not from its 12 KB of weights.  An
+// edge that closes a square of conducting edges with the edge before it (x, or for z also y) joins nothing new: its
+// union is left out, and a brick of one tissue takes 63 + 448 unions along rows instead of 1344.
+__global__ void k_cc_local(const unsigned long long *__restrict__ emask, int *parent)
 {
     __shared__ int lp[BS];
     const int b = blockIdx.x, t = threadIdx.x;
     int tx, ty, tz;
     brick_xyz(t, tx, ty, tz);
     const long long base = (long long)b * BS;
-    lp[t] = parent[base + t] >= 0 ? t : -1;
+    const unsigned long long *e = emask + (long long)b * EMASK + tz;
+    const int lane = t & 63;
+    const unsigned long long mx = e[0], my = e[8], mz = e[16], mn = e[24];
+    const unsigned long long ux = tz < 7 ? e[1] : 0ull, uy = tz < 7 ? e[9] : 0ull;   // the layer above
+    // left: bits of x edges that end at a node (the edge from its -x neighbour inside the brick), and so on
+    const unsigned long long no_x0 = 0xfefefefefefefefeull;
+    const unsigned long long in_x = (mx << 1) & no_x0, in_ux = (ux << 1) & no_x0;
+    const unsigned long long in_y = my << 8, in_uy = uy << 8;
+    // rows (along x) are joined by the row's own start: no unions at all
+    const bool node = (mn >> lane) & 1ull;
+    int start = tx;
+    {
+        const unsigned row = (unsigned)(in_x >> (8 * ty)) & 255u;   // bit x: joined to x - 1
+        while (start > 0 && ((row >> start) & 1u)) --start;
+    }
+    lp[t] = node ? t - tx + start : -1;
     __syncthreads();
-    if (tx < 7 && w[base + t] > 0.0) lunite(lp, t, t + 1);
-    if (ty < 7 && w[stride + base + t] > 0.0) lunite(lp, t, t + 8);
-    if (tz < 7 && w[2 * stride + base + t] > 0.0) lunite(lp, t, t + 64);
+    // y edges: left out where the edge at x - 1 and the x edges of both rows close the square
+    const unsigned long long sq_y = (my << 1) & no_x0 & in_x & (in_x >> 8);
+    const unsigned long long sq_z = ((mz << 1) & no_x0 & in_x & in_ux) | ((mz << 8) & in_y & in_uy);
+    if (ty < 7 && ((my & ~sq_y) >> lane) & 1ull) lunite(lp, t, t + 8);
+    if (tz < 7 && ((mz & ~sq_z) >> lane) & 1ull) lunite(lp, t, t + 64);
     __syncthreads();
-    if (lp[t] >= 0) parent[base + t] = (int)base + lfind(lp, t);
+    parent[base + t] = node ? (int)base + lfind(lp, t) : -1;
 }
 
-// Unions across the three plus faces of a brick.  Most face edges join the
-// same pair of brick-local components as the face edge next to them: a face
-// node whose (own parent, neighbour's parent) pair equals that of the previous
-// node on the face skips its union (same sets, already joined or about to be).
-__global__ void k_cc_union(const double *__restrict__ w, long long stride, Topo topo, int *parent)
+// Unions across the three plus faces of a brick, one wave per brick (a lane per face node): the time is the chains
+// of dependent loads, so what counts is how many bricks are in flight.  Most face edges join the same pair of
+// brick-local components as the face edge next to them: a face node whose (own parent, neighbour's parent) pair
+// equals that of the previous node on the face skips its union (same sets, already joined or about to be).
+// (8.9 M unknowns, components of each brick and unions: 271 + 324 us with a workgroup per brick and every edge
+// united, now 75 + 222 us, beside the coarsening.)
+__global__ __launch_bounds__(256) void k_cc_union(const unsigned long long *__restrict__ emask, Topo topo, int *parent)
 {
-    __shared__ int la[BS], lb[BS];
-    const int b = blockIdx.x, t = threadIdx.x;
-    int nb[6];
-    brick_nbrs(topo.nbr, b, nb);
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    const long long base = (long long)b * BS;
-    const int me = (int)(base + t);
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= topo.nb) return;
+    const unsigned long long *e = emask + (long long)b * EMASK;
+    const int lo = lane & 7, hi = lane >> 3;
+    const int base = b * BS;
+    int me[3], other[3], pm[3], po[3];
+    bool edge[3];
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const bool face = d == 0 ? tx == 7 : d == 1 ? ty == 7 : tz == 7;
-        const int nbk = nb[d == 0 ? NPX : d == 1 ? NPY : NPZ];
-        const int other = nbk * BS + t - (d == 0 ? 7 : d == 1 ? 56 : 448);
-        const bool edge = face && nbk >= 0 && w[d * stride + base + t] > 0.0;
-        la[t] = edge ? pload(parent, me) : -1;
-        lb[t] = edge ? pload(parent, other) : -1;
-        __syncthreads();
-        // previous node on the face: one step along its first in-face axis, else its second
-        int prev = -1;
-        if (d == 0) prev = ty > 0 ? t - 8 : (tz > 0 ? t - 64 : -1);
-        else if (d == 1) prev = tx > 0 ? t - 1 : (tz > 0 ? t - 64 : -1);
-        else prev = tx > 0 ? t - 1 : (ty > 0 ? t - 8 : -1);
-        const bool same = prev >= 0 && la[prev] == la[t] && lb[prev] == lb[t];
-        if (edge && !same) punite(parent, me, other);
-        __syncthreads();
+        const int nbk = topo.nbr[b * 6 + (d == 0 ? NPX : d == 1 ? NPY : NPZ)];
+        // face nodes in the order of their two other axes
+        const int t = d == 0 ? 7 + 8 * lo + 64 * hi : d == 1 ? lo + 56 + 64 * hi : lane + 448;
+        const unsigned long long word = e[8 * d + (d == 2 ? 7 : hi)];
+        edge[d] = nbk >= 0 && ((word >> (t & 63)) & 1ull);
+        me[d] = base + t;
+        other[d] = nbk * BS + t - (d == 0 ? 7 : d == 1 ? 56 : 448);
+        pm[d] = edge[d] ? pload(parent, me[d]) : -1;
+        po[d] = edge[d] ? pload(parent, other[d]) : -1;
+    }
+    // previous node on the face: one step along its first axis, else its second
+    const int prev = lo > 0 ? lane - 1 : hi > 0 ? lane - 8 : 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int lm = __shfl(pm[d], prev, 64), lq = __shfl(po[d], prev, 64);
+        const bool same = lane > 0 && lm == pm[d] && lq == po[d];
+        if (edge[d] && !same) punite(parent, me[d], other[d]);
     }
 }
 
@@ -503,16 +629,14 @@ __global__ void k_cc_assign(const int *__restrict__ parent, const int *__restric
 }
 
 // scan_tmp needs (n/2048 + 1) ints
-hipError_t launch_components(const double *w64, long long stride, Topo topo, int *parent, int *flag, int *idx,
-                             int *scan_tmp, int *comp, int *counts_or_null, int *ncomp_dev, hipStream_t s)
+hipError_t launch_components(const unsigned long long *emask, Topo topo, int *parent, int *flag, int *idx,
+                             int *scan_tmp, int *comp, int *ncomp_dev, hipStream_t s)
 {
-    (void)counts_or_null;
     const int nb = topo.nb;
     const long long n = (long long)nb * BS;
     if (nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_cc_init, dim3(nb), dim3(NT), 0, s, w64, stride, topo, parent);
-    SPFD_LAUNCH(k_cc_local, dim3(nb), dim3(NT), 0, s, w64, stride, parent);
-    SPFD_LAUNCH(k_cc_union, dim3(nb), dim3(NT), 0, s, w64, stride, topo, parent);
+    SPFD_LAUNCH(k_cc_local, dim3(nb), dim3(NT), 0, s, emask, parent);
+    SPFD_LAUNCH(k_cc_union, dim3((nb + 3) / 4), dim3(256), 0, s, emask, topo, parent);
     const unsigned gb = (unsigned)((n + 255) / 256 > 65536 ? 65536 : (n + 255) / 256);
     SPFD_LAUNCH(k_cc_store_root, dim3(gb), dim3(256), 0, s, parent, n);
     SPFD_LAUNCH(k_cc_flatten, dim3(gb), dim3(256), 0, s, parent, n, flag);
@@ -656,66 +780,6 @@ __global__ __launch_bounds__(256) void k_coarse_assemble_brick(const double *__r
 // the nonzeros, regularisation with alpha_c = mean diagonal / size^2, and
 // Gauss-Jordan inversion (no pivoting needed for an SPD matrix).
 // work: 2n ints + n doubles.
-// Column masks of a structured level: bit tx + 8 ty of brick b is set when a
-// node (tx,ty,*) of the brick has a positive diagonal (is an unknown).
-__global__ __launch_bounds__(NT) void k_col_masks(const double *__restrict__ w, long long stride, Topo topo,
-                                                  unsigned long long *__restrict__ mask)
-{
-    __shared__ unsigned long long m;
-    const int bk = blockIdx.x;
-    const int t = threadIdx.x;
-    if (t == 0) m = 0ull;
-    __syncthreads();
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    int nb[6];
-    brick_nbrs(topo.nbr, bk, nb);
-    const long long base = (long long)bk * BS;
-    long long I[6];
-    nbr_index(base, t, tx, ty, tz, nb, I);
-    double W[6];
-    stored_weights(w, stride, base, t, I, W);
-    if (diag_of(W) > 0.0) atomicOr(&m, 1ull << (t & 63));
-    __syncthreads();
-    if (t == 0) mask[bk] = m;
-}
-
-// inverse diagonals of a structured level from its stored weights (0 where the diagonal vanishes)
-__global__ __launch_bounds__(NT) void k_dinv_struct(const double *__restrict__ w, long long stride, Topo topo,
-                                                    double *__restrict__ d64, float *__restrict__ d32)
-{
-    const int bk = blockIdx.x;
-    const int t = threadIdx.x;
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    int nb[6];
-    brick_nbrs(topo.nbr, bk, nb);
-    const long long base = (long long)bk * BS;
-    long long I[6];
-    nbr_index(base, t, tx, ty, tz, nb, I);
-    double W[6];
-    stored_weights(w, stride, base, t, I, W);
-    const double D = diag_of(W);
-    const double v = D > 0.0 ? 1.0 / D : 0.0;
-    d64[base + t] = v;
-    d32[base + t] = (float)v;
-}
-
-hipError_t launch_dinv_struct(const double *w64, long long stride, Topo topo, double *d64, float *d32, hipStream_t s)
-{
-    if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_dinv_struct, dim3(topo.nb), dim3(NT), 0, s, w64, stride, topo, d64, d32);
-    return hipGetLastError();
-}
-
-hipError_t launch_col_masks(const double *w64, long long stride, Topo topo, unsigned long long *mask, hipStream_t s)
-{
-    if (topo.nb <= 0) return hipSuccess;
-    Topo tp{topo.nb, topo.nbr, nullptr};
-    SPFD_LAUNCH(k_col_masks, dim3(topo.nb), dim3(NT), 0, s, w64, stride, tp, mask);
-    return hipGetLastError();
-}
-
 // Make the coarsest matrix definite: A += sum over its connected components c
 // of (mean diagonal of c / |c|) 1_c 1_c^T.  For right sides with zero sum per
 // component the inverse of the result applies the pseudo-inverse and returns

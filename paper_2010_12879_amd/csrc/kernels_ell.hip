@@ -621,8 +621,8 @@ __global__ void k_dinv_ell(int n, int K, const int *__restrict__ col, const doub
         for (int k = 0; k < K; ++k)
             if (col[(long long)k * n + i] >= 0) d += val[(long long)k * n + i];
         const double v = d > 0.0 ? 1.0 / d : 0.0;
-        d64[i] = v;
-        d32[i] = (float)v;
+        if (d64) d64[i] = v;
+        if (d32) d32[i] = (float)v;
     }
 }
 
