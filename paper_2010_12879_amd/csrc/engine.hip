@@ -60,6 +60,7 @@ struct Level {
     int *d_mptr = nullptr;          // members of each row in the finer level (CSR)
     int *d_mem = nullptr;
     int *d_memb = nullptr;          // the same as a direct table of 8 per row (null: an aggregate has more)
+    int *d_uf = nullptr;            // build: start of the union-find over the level's rows (the row, -1 if no unknown)
     int *d_agg = nullptr;           // this level's unknown -> row of the next (split) level, -1 if none
     unsigned long long *d_cmask = nullptr;  // node columns with unknowns, per brick (structured levels)
     double *d_dinv64 = nullptr;             // inverse diagonal (0 where it vanishes), of the cycle's precision
@@ -276,11 +277,13 @@ void raw_free(Ctx *c, void *p)
         (void)hipFree(p);
 }
 
+// device buffers are whole multiples of 256 bytes (so is a clear of one, which is then one fill, not two)
+size_t padded(size_t bytes) { return bytes == 0 ? 256 : (bytes + 255) & ~(size_t)255; }
+
 template <typename T>
 T *dalloc(Ctx *c, std::vector<void *> &owner, size_t count)
 {
-    size_t bytes = count * sizeof(T);
-    bytes = bytes == 0 ? 256 : (bytes + 255) & ~(size_t)255;
+    const size_t bytes = padded(count * sizeof(T));
     void *p = nullptr;
     for (size_t i = 0; i < c->pool.size(); ++i)
         if (c->pool[i].first == bytes) {
@@ -469,38 +472,36 @@ void build_topology(Ctx *c, Level &L, const std::vector<uint8_t> &flags, std::ve
     HIPCHK(hipStreamSynchronize(c->stream));
 }
 
-// rows of an ELL level with a positive diagonal (the sum of the row's stored entries, in the order the
-// enumeration of the coarsest level uses), counted by many workgroups
-__global__ __launch_bounds__(256) void k_count_ell_dofs(int n, int K, const int *__restrict__ col,
-                                                        const double *__restrict__ val, int *count)
-{
-    __shared__ int cnt;
-    if (threadIdx.x == 0) cnt = 0;
-    __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        double d = 0.0;
-        for (int k = 0; k < K; ++k)
-            if (col[(long long)k * n + i] >= 0) d += val[(long long)k * n + i];
-        if (d > 0.0) atomicAdd(&cnt, 1);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && cnt) atomicAdd(count, cnt);
-}
-
 constexpr int MAX_LEVELS = 20;
 
-// the statistics of a structured level whose setup kernel is queued (waits for it)
+// the statistics of a level whose setup kernel is queued (waits for it)
+const LevelStat *fetch_stat(Ctx *c, const void *d_stat)
+{
+    HIPCHK(hipMemcpyAsync(c->h_ints, d_stat, LEVEL_STATS * sizeof(LevelStat), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    return (const LevelStat *)c->h_ints;
+}
+
 LevelStat level_stat(Ctx *c, const LevelStat *d_stat)
 {
-    LevelStat *h = (LevelStat *)c->h_ints;
-    HIPCHK(hipMemcpyAsync(h, d_stat, LEVEL_STATS * sizeof(LevelStat), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    const LevelStat *h = fetch_stat(c, d_stat);
     LevelStat a{};
     for (int i = 0; i < LEVEL_STATS; ++i) {
         a.count += h[i].count;
         a.wmax = std::max(a.wmax, h[i].wmax);
         a.wmin_not = std::max(a.wmin_not, h[i].wmin_not);
+    }
+    return a;
+}
+
+EllStat ell_stat(Ctx *c, const EllStat *d_stat)
+{
+    const EllStat *h = (const EllStat *)fetch_stat(c, d_stat);
+    EllStat a{};
+    for (int i = 0; i < LEVEL_STATS; ++i) {
+        a.count += h[i].count;
+        a.longest = std::max(a.longest, h[i].longest);
+        a.over |= h[i].over;
     }
     return a;
 }
@@ -1280,49 +1281,44 @@ void alloc_dinv(Ctx *c, Level &L)
 }
 
 // Coarse level whose unknowns are the connected pieces of the 2x2x2
-// aggregates of F (F structured or ELL), with its ELL Galerkin operator.
-Level split_level(Ctx *c, Level &F)
+// aggregates of F (F structured or ELL), with its ELL Galerkin operator.  The host waits twice: for the number of
+// pieces, and for the level's statistics (st, cleared).
+Level split_level(Ctx *c, Level &F, EllStat *st)
 {
     Level C;
     C.ell = true;
     const long long nf = F.nodes();
-    int *parent = dalloc<int>(c, c->hier_allocs, nf);
-    int *flag = dalloc<int>(c, c->hier_allocs, nf);
-    int *idx = dalloc<int>(c, c->hier_allocs, nf);
-    int *tmp = dalloc<int>(c, c->hier_allocs, nf / 2048 + 2);
-    if (F.ell)
-        HIPCHK(launch_pieces_ell(F.nrow, F.K, F.d_col, F.d_val64, F.d_pos, parent, c->stream));
-    else
-        HIPCHK(launch_pieces_brick(F.d_w64, F.nodes(), F.topo(), F.d_coord, parent, c->stream));
-    HIPCHK(launch_pieces_finish(parent, nf, flag, c->stream));
-    HIPCHK(scan_exclusive_ints(flag, nf, idx, tmp, c->d_ints, c->stream));
+    int *root = nullptr, *idx = nullptr, *part = nullptr;
+    uint8_t *reach = nullptr;
+    if (F.ell) {
+        root = dalloc<int>(c, c->hier_allocs, nf);
+        idx = dalloc<int>(c, c->hier_allocs, nf);
+        part = dalloc<int>(c, c->hier_allocs, piece_parts((int)nf));
+        HIPCHK(launch_pieces_ell(F.nrow, F.K, F.d_col, F.d_val64, F.d_pos, F.d_uf, root, idx, part, c->d_ints,
+                                 c->stream));
+    } else {
+        reach = dalloc<uint8_t>(c, c->hier_allocs, nf);
+        part = dalloc<int>(c, c->hier_allocs, 2 * F.nb);
+        HIPCHK(launch_pieces_brick(F.d_w64, nf, F.topo(), reach, part, c->d_ints, c->stream));
+    }
     HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     const int nc = c->h_ints[0];
     C.nrow = nc;
-    C.d_pos = dalloc<int4>(c, c->hier_allocs, nc + 1);
-    if (F.ell)
-        HIPCHK(launch_piece_pos_ell(F.nrow, parent, idx, F.d_pos, C.d_pos, c->stream));
-    else
-        HIPCHK(launch_piece_pos_brick(parent, idx, F.topo(), F.d_coord, C.d_pos, c->stream));
-    // fine -> coarse map and member lists
+    C.d_pos = dalloc<int4>(c, c->hier_allocs, nc);
     F.d_agg = dalloc<int>(c, c->hier_allocs, nf);
-    int *count = dalloc<int>(c, c->hier_allocs, nc + 1);
-    HIPCHK(hipMemsetAsync(count, 0, (nc + 1) * sizeof(int), c->stream));
-    HIPCHK(launch_pieces_assign(parent, idx, nf, F.d_agg, count, c->stream));
-    C.d_mptr = dalloc<int>(c, c->hier_allocs, nc + 1);
-    int *tmp2 = dalloc<int>(c, c->hier_allocs, nc / 2048 + 2);
-    HIPCHK(scan_exclusive_ints(count, nc + 1, C.d_mptr, tmp2, c->d_ints + 1, c->stream));
-    HIPCHK(hipMemcpyAsync(c->h_ints + 1, c->d_ints + 1, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    const int nmem = c->h_ints[1];
-    C.d_mem = dalloc<int>(c, c->hier_allocs, nmem + 1);
-    HIPCHK(hipMemsetAsync(count, 0, (nc + 1) * sizeof(int), c->stream));
-    HIPCHK(launch_members(F.d_agg, nf, nc, C.d_mptr, count, C.d_mem, c->stream));
-    C.d_memb = dalloc<int>(c, c->hier_allocs, (size_t)nc * 8 + 1);
-    HIPCHK(hipMemsetAsync(c->d_ints + 4, 0, sizeof(int), c->stream));
-    HIPCHK(launch_members8(nc, C.d_mptr, C.d_mem, C.d_memb, c->d_ints + 4, c->stream));
-    // Galerkin rows: lengths, then the ELL arrays
+    // members: row pointers and, behind them, the cursors of the fill
+    C.d_mptr = dalloc<int>(c, c->hier_allocs, F.ell ? 2 * nc + 1 : nc + 1);
+    C.d_mem = dalloc<int>(c, c->hier_allocs, nf);
+    C.d_memb = dalloc<int>(c, c->hier_allocs, (size_t)nc * 8);
+    if (F.ell) {
+        HIPCHK(hipMemsetAsync(C.d_mptr, 0, padded((2 * nc + 1) * sizeof(int)), c->stream));
+        HIPCHK(launch_members_ell(F.nrow, root, idx, part, F.d_pos, nc, F.d_agg, C.d_pos, C.d_mptr,
+                                  C.d_mptr + nc + 1, C.d_mem, C.d_memb, st, c->stream));
+    } else {
+        HIPCHK(launch_pieces_write(reach, F.nb, F.d_coord, part, nc, F.d_agg, C.d_pos, C.d_mptr, C.d_mem, C.d_memb,
+                                   c->stream));
+    }
     FineLevelArgs fa{};
     if (F.ell) {
         fa.n = F.nrow;
@@ -1331,37 +1327,44 @@ Level split_level(Ctx *c, Level &F)
         fa.val = F.d_val64;
     } else {
         fa.w = F.d_w64;
-        fa.stride = F.nodes();
+        fa.stride = nf;
         fa.nbr = F.d_nbr;
     }
-    int *len = dalloc<int>(c, c->hier_allocs, nc + 1);
-    HIPCHK(hipMemsetAsync(c->d_ints + 2, 0, 2 * sizeof(int), c->stream));
-    HIPCHK(launch_galerkin_ell(fa, F.d_agg, nc, C.d_mptr, C.d_mem, 0, len, 0, nullptr, nullptr, nullptr, c->d_ints + 2,
-                               c->d_ints + 3, c->stream));
-    HIPCHK(hipMemcpyAsync(c->h_ints + 2, c->d_ints + 2, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    if (c->h_ints[2]) throw HipFail{hipErrorInvalidValue, "split aggregate with too many coarse neighbours"};
-    if (c->h_ints[4]) C.d_memb = nullptr;   // an aggregate of more than 8 members: the CSR restriction
+    alloc_dinv(c, C);
+    C.d_uf = dalloc<int>(c, c->hier_allocs, nc);
+    auto alloc_rows = [&](int K) {
+        C.K = K;
+        C.d_col = dalloc<int>(c, c->hier_allocs, (size_t)K * nc);
+        C.d_val64 = dalloc<double>(c, c->hier_allocs, (size_t)K * nc);
+        C.d_val32 = dalloc<float>(c, c->hier_allocs, (size_t)K * nc);
+    };
     // rows of up to 8 entries are stored with 8 (padding: column -1, value 0), the width of the fixed-width
     // cycle kernels of the ELL levels
-    C.K = std::max(c->h_ints[3], 8);
-    C.d_col = dalloc<int>(c, c->hier_allocs, (size_t)C.K * nc + 1);
-    C.d_val64 = dalloc<double>(c, c->hier_allocs, (size_t)C.K * nc + 1);
-    C.d_val32 = dalloc<float>(c, c->hier_allocs, (size_t)C.K * nc + 1);
-    HIPCHK(launch_galerkin_ell(fa, F.d_agg, nc, C.d_mptr, C.d_mem, 1, len, C.K, C.d_col, C.d_val64, C.d_val32,
-                               c->d_ints + 2, c->d_ints + 3, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    // unknowns of the new level: rows with a conducting connection (their number only)
-    HIPCHK(hipMemsetAsync(c->d_ints, 0, sizeof(int), c->stream));
-    if (C.nrow > 0)
-        hipLaunchKernelGGL(k_count_ell_dofs, dim3((unsigned)((C.nrow + 255) / 256)), dim3(256), 0, c->stream, C.nrow,
-                           C.K, C.d_col, C.d_val64, c->d_ints);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    C.dofs = c->h_ints[0];
-    alloc_dinv(c, C);
-    HIPCHK(launch_dinv_ell(C.nrow, C.K, C.d_col, C.d_val64, C.d_dinv64, C.d_dinv32, c->stream));
+    const bool narrow = !F.ell || F.K == ELL_K8;
+    if (narrow) {
+        alloc_rows(ELL_K8);
+        HIPCHK(launch_galerkin_rows8(fa, F.d_agg, nc, C.d_mptr, C.d_mem, C.d_col, C.d_val64, C.d_val32, C.d_dinv64,
+                                     C.d_dinv32, C.d_uf, st, c->stream));
+    }
+    EllStat a = ell_stat(c, st);
+    if (a.over) C.d_memb = nullptr;   // an aggregate of more than 8 members: the CSR restriction
+    if (!narrow || a.longest > ELL_K8) {
+        // row lengths, then the ELL arrays
+        int *len = dalloc<int>(c, c->hier_allocs, nc);
+        HIPCHK(hipMemsetAsync(c->d_ints + 2, 0, 2 * sizeof(int), c->stream));
+        HIPCHK(hipMemsetAsync(st, 0, LEVEL_STATS * sizeof(EllStat), c->stream));
+        HIPCHK(launch_galerkin_ell(fa, F.d_agg, nc, C.d_mptr, C.d_mem, 0, len, 0, nullptr, nullptr, nullptr,
+                                   c->d_ints + 2, c->d_ints + 3, c->stream));
+        HIPCHK(hipMemcpyAsync(c->h_ints, c->d_ints + 2, 2 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        if (c->h_ints[0]) throw HipFail{hipErrorInvalidValue, "split aggregate with too many coarse neighbours"};
+        alloc_rows(std::max(c->h_ints[1], ELL_K8));
+        HIPCHK(launch_galerkin_ell(fa, F.d_agg, nc, C.d_mptr, C.d_mem, 1, len, C.K, C.d_col, C.d_val64, C.d_val32,
+                                   c->d_ints + 2, c->d_ints + 3, c->stream));
+        HIPCHK(launch_ell_setup(nc, C.K, C.d_col, C.d_val64, C.d_dinv64, C.d_dinv32, C.d_uf, st, c->stream));
+        a = ell_stat(c, st);
+    }
+    C.dofs = a.count;   // rows with a conducting connection
     return C;
 }
 
@@ -1385,7 +1388,7 @@ spfd_status do_build(Ctx *c)
     uint8_t *d_head = dalloc<uint8_t>(c, c->hier_allocs, stat_bytes + sizeof(int) + nbg);
     LevelStat *d_stat = (LevelStat *)d_head;
     int *d_err = (int *)(d_head + stat_bytes);
-    HIPCHK(hipMemsetAsync(d_head, 0, stat_bytes + sizeof(int) + nbg, c->stream));
+    HIPCHK(hipMemsetAsync(d_head, 0, padded(stat_bytes + sizeof(int) + nbg), c->stream));
     HIPCHK(launch_brick_flags(c->d_labels, c->d_table64, c->nlab, c->voxel_mode ? c->d_sigvox : nullptr, g,
                               (uint8_t *)(d_err + 1), d_err, c->stream));
     uint8_t *hflags = stage(c, sizeof(int) + nbg);
@@ -1439,7 +1442,7 @@ spfd_status do_build(Ctx *c)
         const bool split = !c->opt.no_split && (l >= c->opt.split_level || F.ell);
         if (!F.ell && F.N[0] == 1 && F.N[1] == 1 && F.N[2] == 1) break;
         if (split) {
-            Level C = split_level(c, F);
+            Level C = split_level(c, F, (EllStat *)(d_stat + c->lv.size() * LEVEL_STATS));
             c->lv.push_back(std::move(C));
             continue;
         }

@@ -374,20 +374,35 @@ struct FineLevelT {
     const T *val;
 };
 // pieces = connected parts of each 2x2x2 aggregate; parent = union-find forest
-hipError_t launch_pieces_brick(const double *w64, long long stride, Topo topo, const int4 *coord, int *parent,
+constexpr int ELL_K8 = 8;   // row width of the fixed-width ELL kernels
+// What the build needs to know of a split level, laid out and cleared like LevelStat (over: entry 0 only)
+struct EllStat {
+    unsigned count, longest, over, pad;
+};
+static_assert(sizeof(EllStat) == sizeof(LevelStat), "the levels' statistics share one array");
+hipError_t launch_pieces_brick(const double *w64, long long stride, Topo topo, uint8_t *reach, int *part, int *nc,
                                hipStream_t s);
-hipError_t launch_pieces_ell(int n, int K, const int *col, const double *val, const int4 *pos, int *parent,
-                             hipStream_t s);
-hipError_t launch_pieces_finish(int *parent, long long n, int *flag, hipStream_t s);
-hipError_t launch_pieces_assign(const int *parent, const int *idx, long long n, int *agg, int *count, hipStream_t s);
-hipError_t launch_piece_pos_brick(const int *parent, const int *idx, Topo topo, const int4 *coord, int4 *pos,
-                                  hipStream_t s);
-hipError_t launch_piece_pos_ell(int n, const int *parent, const int *idx, const int4 *fpos, int4 *pos, hipStream_t s);
-hipError_t launch_members(const int *agg, long long n, int nc, const int *mptr, int *cursor, int *mem, hipStream_t s);
+hipError_t launch_pieces_write(const uint8_t *reach, int nb, const int4 *coord, const int *part, int nc, int *agg,
+                               int4 *pos, int *mptr, int *mem, int *memb, hipStream_t s);
+int piece_parts(int n);
+hipError_t launch_pieces_ell(int n, int K, const int *col, const double *val, const int4 *pos, int *parent, int *root,
+                             int *idx, int *part, int *nc, hipStream_t s);
+hipError_t launch_members_ell(int n, const int *root, const int *idx, int *part, const int4 *fpos, int nc,
+                              int *agg, int4 *pos, int *mptr, int *cursor, int *mem, int *memb, EllStat *stat,
+                              hipStream_t s);
+hipError_t launch_galerkin_rows8(const FineLevelArgs &fa, const int *agg, int nc, const int *mptr, const int *mem,
+                                 int *col, double *val64, float *val32, double *d64, float *d32, int *parent,
+                                 EllStat *stat, hipStream_t s);
+// rows of any length: pass 0 their lengths (*overflow: one with more than 48 entries), pass 1 the ELL arrays
 hipError_t launch_galerkin_ell(const FineLevelArgs &fa, const int *agg, int nc, const int *mptr, const int *mem,
                                int pass, int *len, int K, int *col, double *val64, float *val32, int *overflow,
                                int *maxlen, hipStream_t s);
-hipError_t scan_exclusive_ints(const int *in, long long n, int *out, int *tmp, int *total, hipStream_t s);
+hipError_t launch_ell_setup(int n, int K, const int *col, const double *val, double *d64, float *d32, int *parent,
+                            EllStat *stat, hipStream_t s);
+// exclusive sums in place by one workgroup; the total into *total where given
+hipError_t scan_small(int *v, int n, int *total, hipStream_t s);
+// exclusive sums in place, by one workgroup or several (tmp: n / 2048 + 1 ints)
+hipError_t scan_ints(int *v, int n, int *tmp, hipStream_t s);
 template <typename T>
 hipError_t launch_ell_cheb_first(int n, int K, const int *col, const T *val, const T *b, T *x, T c0, const Scal *sc,
                                  const Batch &bt, hipStream_t s);
@@ -403,10 +418,6 @@ hipError_t launch_restrict_members(const FineLevelT<T> &f, long long nrows, cons
                                    const int *mptr, const int *mem, T *bc, const Scal *sc, const Batch &bt,
                                    hipStream_t s, T *xc = nullptr, const T *dinv_c = nullptr, T c0 = T(0),
                                    const int *memb = nullptr);
-// direct member table memb[p*8 + j] of the restriction (*over = 1 if an aggregate has more than 8 members)
-hipError_t launch_members8(int nc, const int *mptr, const int *mem, int *memb, int *over, hipStream_t s);
-// inverse diagonals (0 where the diagonal vanishes), into d64 or d32 or both
-hipError_t launch_dinv_ell(int n, int K, const int *col, const double *val, double *d64, float *d32, hipStream_t s);
 template <typename T>
 hipError_t launch_prolong_agg(long long n, const int *agg, T *x, const T *xc, T scale, const Scal *sc,
                               const Batch &bt, hipStream_t s);

@@ -541,7 +541,7 @@ __global__ void k_cc_store_root(int *parent, long long n)
 // the sums, offsets); SCAN_CHUNK elements per block
 constexpr int SCAN_CHUNK = 2048;
 
-__global__ void k_scan_blocks(const int *__restrict__ in, long long n, int *out, int *bsum)
+__global__ void k_scan_blocks(const int *in, long long n, int *out, int *bsum)
 {
     __shared__ int s[NT];
     const long long off = (long long)blockIdx.x * SCAN_CHUNK;
@@ -569,30 +569,36 @@ __global__ void k_scan_blocks(const int *__restrict__ in, long long n, int *out,
     if (t == NT - 1) bsum[blockIdx.x] = s[t];
 }
 
-__global__ void k_scan_sums(int *bsum, int nblk, int *total)
+// exclusive sums of v[0..n) in place, one workgroup: each thread a run of consecutive values, 64 sums per wave
+__global__ __launch_bounds__(1024) void k_scan_sums(int *v, int n, int *total)
 {
-    __shared__ int s[NT];
-    __shared__ int carry;
-    const int t = threadIdx.x;
-    if (t == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < nblk; base += NT) {
-        const int i = base + t;
-        const int v = i < nblk ? bsum[i] : 0;
-        s[t] = v;
-        __syncthreads();
-        for (int d = 1; d < NT; d <<= 1) {
-            const int add = t >= d ? s[t - d] : 0;
-            __syncthreads();
-            s[t] += add;
-            __syncthreads();
-        }
-        if (i < nblk) bsum[i] = carry + s[t] - v;
-        __syncthreads();
-        if (t == NT - 1) carry += s[t];
-        __syncthreads();
+    __shared__ int wsum[16];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int per = (n + 1023) / 1024, i0 = t * per, i1 = min(i0 + per, n);
+    int sum = 0;
+    for (int i = i0; i < i1; ++i) sum += v[i];
+    int incl = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += u;
     }
-    if (t == 0) *total = carry;
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    int run = incl - sum;
+    for (int k = 0; k < wv; ++k) run += wsum[k];
+    if (total && t == 1023) *total = run + sum;
+    for (int i = i0; i < i1; ++i) {
+        const int u = v[i];
+        v[i] = run;
+        run += u;
+    }
+}
+
+hipError_t scan_small(int *v, int n, int *total, hipStream_t s)
+{
+    if (n <= 0) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_scan_sums, dim3(1), dim3(1024), 0, s, v, n, total);
+    return hipGetLastError();
 }
 
 __global__ void k_scan_add(int *out, long long n, const int *bsum)
@@ -610,14 +616,16 @@ static hipError_t scan_exclusive(const int *in, long long n, int *out, int *bsum
     const long long nblk = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     if (nblk <= 0) return hipSuccess;
     SPFD_LAUNCH(k_scan_blocks, dim3((unsigned)nblk), dim3(NT), 0, s, in, n, out, bsum);
-    SPFD_LAUNCH(k_scan_sums, dim3(1), dim3(NT), 0, s, bsum, (int)nblk, total);
+    HIP_RETURN_IF(scan_small(bsum, (int)nblk, total, s));
     SPFD_LAUNCH(k_scan_add, dim3((unsigned)nblk), dim3(NT), 0, s, out, n, bsum);
     return hipGetLastError();
 }
 
-hipError_t scan_exclusive_ints(const int *in, long long n, int *out, int *tmp, int *total, hipStream_t s)
+// one workgroup where each of its threads takes at most 16 values (its loads are 16 apart), else three launches
+hipError_t scan_ints(int *v, int n, int *tmp, hipStream_t s)
 {
-    return scan_exclusive(in, n, out, tmp, total, s);
+    if (n <= 16 * 1024) return scan_small(v, n, nullptr, s);
+    return scan_exclusive(v, n, v, tmp, nullptr, s);
 }
 
 __global__ void k_cc_assign(const int *__restrict__ parent, const int *__restrict__ idx, long long n, int *comp)

@@ -48,9 +48,16 @@ __device__ __forceinline__ void uf_unite(int *p, int a, int b)
 }
 
 // ---------------------------------------------------------------- pieces of a structured (brick) level
-// parent[n] = n for unknowns (D > 0), -1 otherwise
-__global__ void k_piece_init_brick(const double *__restrict__ w, long long stride, Topo topo, int *parent)
+// The connected pieces of every 2x2x2 aggregate of a brick (bricks start at multiples of 8, so an aggregate lies in
+// one brick): reach[n] = the nodes of node n's aggregate that conducting edges inside it connect to n, as bits
+// (dx + 2 dy + 4 dz), 0 for a node without a positive diagonal.  The smallest node of a piece stands for it.
+// part[b] and part[nb + b]: pieces and unknowns of brick b.  (Twelve edges and eight nodes fit in a thread's
+// registers; a union-find over the level took four launches.)
+__global__ __launch_bounds__(NT) void k_pieces_brick(const double *__restrict__ w, long long stride, Topo topo,
+                                                     uint8_t *__restrict__ reach, int *__restrict__ part)
 {
+    __shared__ unsigned long long e[3][8];
+    __shared__ int count[2][8];
     const int b = blockIdx.x, t = threadIdx.x;
     int nb[6];
     brick_nbrs(topo.nbr, b, nb);
@@ -61,143 +68,217 @@ __global__ void k_piece_init_brick(const double *__restrict__ w, long long strid
     nbr_index(base, t, tx, ty, tz, nb, I);
     double W[6];
     stored_weights(w, stride, base, t, I, W);
-    parent[base + t] = diag_of(W) > 0.0 ? (int)(base + t) : -1;
-}
-
-// unite across the edges that stay inside a 2x2x2 aggregate: the +d edge of a
-// node with an even grid coordinate along d (bricks start at multiples of 8,
-// so both ends are in the same brick)
-__global__ void k_piece_union_brick(const double *__restrict__ w, long long stride, Topo topo, int *parent)
-{
-    const int b = blockIdx.x, t = threadIdx.x;
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    const long long base = (long long)b * BS;
-    const int me = (int)(base + t);
-    if ((tx & 1) == 0 && w[base + t] > 0.0) uf_unite(parent, me, me + 1);
-    if ((ty & 1) == 0 && w[stride + base + t] > 0.0) uf_unite(parent, me, me + 8);
-    if ((tz & 1) == 0 && w[2 * stride + base + t] > 0.0) uf_unite(parent, me, me + 64);
-}
-
-// position (at the coarse level) of the piece rooted at node n
-__global__ void k_piece_pos_brick(const int *__restrict__ parent, const int *__restrict__ idx, Topo topo,
-                                  const int4 *__restrict__ coord, int4 *pos)
-{
-    const int b = blockIdx.x, t = threadIdx.x;
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    const long long n = (long long)b * BS + t;
-    if (parent[n] == (int)n) {
-        const int4 c = coord[b];
-        pos[idx[n]] = make_int4((c.x * 8 + tx) >> 1, (c.y * 8 + ty) >> 1, (c.z * 8 + tz) >> 1, 0);
+    const unsigned long long ex = __ballot(W[NPX] > 0.0), ey = __ballot(W[NPY] > 0.0), ez = __ballot(W[NPZ] > 0.0);
+    if ((t & 63) == 0) {
+        e[0][tz] = ex;
+        e[1][tz] = ey;
+        e[2][tz] = ez;
     }
+    __syncthreads();
+    const int z0 = tz & ~1, s0 = (tx & ~1) + 8 * (ty & ~1);
+    auto quad = [&](unsigned long long m) {   // the four nodes of a layer
+        m >>= s0;
+        return (unsigned)((m & 3ull) | ((m >> 6) & 12ull));
+    };
+    // edges by their lower node
+    const unsigned X = (quad(e[0][z0]) | quad(e[0][z0 + 1]) << 4) & 0x55u;
+    const unsigned Y = (quad(e[1][z0]) | quad(e[1][z0 + 1]) << 4) & 0x33u;
+    const unsigned Z = quad(e[2][z0]);
+    const int q = (tx & 1) + 2 * (ty & 1) + 4 * (tz & 1);
+    unsigned r = 1u << q;
+    for (int k = 0; k < 7; ++k)
+        r |= (r & X) << 1 | (r >> 1 & X) | (r & Y) << 2 | (r >> 2 & Y) | (r & Z) << 4 | (r >> 4 & Z);
+    const bool unknown = diag_of(W) > 0.0;
+    reach[base + t] = unknown ? (uint8_t)r : 0;
+    const int pieces = __popcll(__ballot(unknown && __ffs(r) - 1 == q)), nodes = __popcll(__ballot(unknown));
+    if ((t & 63) == 0) {
+        count[0][tz] = pieces;
+        count[1][tz] = nodes;
+    }
+    __syncthreads();
+    if (t < 2) {
+        int sum = 0;
+        for (int k = 0; k < 8; ++k) sum += count[t][k];
+        part[t * topo.nb + b] = sum;
+    }
+}
+
+// The pieces in the order of their smallest nodes: agg of every node, grid position at the coarse level, members (CSR
+// and, as at most eight, the direct table memb[p*8 + j], -1: none).  part: exclusive sums over the bricks.
+__global__ __launch_bounds__(NT) void k_pieces_write(const uint8_t *__restrict__ reach, int nb,
+                                                     const int4 *__restrict__ coord, const int *__restrict__ part,
+                                                     int nc, int *__restrict__ agg, int4 *__restrict__ pos,
+                                                     int *__restrict__ mptr, int *__restrict__ mem,
+                                                     int *__restrict__ memb)
+{
+    __shared__ int id[BS];
+    __shared__ int count[2][8];
+    const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
+    int tx, ty, tz;
+    brick_xyz(t, tx, ty, tz);
+    const int base = b * BS;
+    const unsigned r = reach[base + t];
+    const int q = (tx & 1) + 2 * (ty & 1) + 4 * (tz & 1);
+    const int corner = t - (tx & 1) - 8 * (ty & 1) - 64 * (tz & 1);   // node 0 of the aggregate
+    auto node = [&](int k) { return corner + (k & 1) + 8 * (k >> 1 & 1) + 64 * (k >> 2); };
+    const bool root = r != 0u && __ffs(r) - 1 == q;
+    const unsigned long long roots = __ballot(root);
+    const int size = root ? __popc(r) : 0;
+    int incl = size;   // members up to and with this lane's piece
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += v;
+    }
+    if (lane == 63) {
+        count[0][tz] = __popcll(roots);
+        count[1][tz] = incl;
+    }
+    __syncthreads();
+    int first = part[b], at = part[nb + b];
+    for (int k = 0; k < tz; ++k) {
+        first += count[0][k];
+        at += count[1][k];
+    }
+    first += __popcll(roots & ((1ull << lane) - 1ull));
+    at += incl - size;
+    id[t] = first;
+    __syncthreads();
+    agg[base + t] = r != 0u ? id[node(__ffs(r) - 1)] : -1;
+    if (!root) return;
+    const int4 c = coord[b];
+    pos[first] = make_int4((c.x * 8 + tx) >> 1, (c.y * 8 + ty) >> 1, (c.z * 8 + tz) >> 1, 0);
+    mptr[first] = at;
+    if (first == nc - 1) mptr[nc] = at + size;
+    int n = 0;
+    for (unsigned m = r; m != 0u; m &= m - 1u) {
+        const int i = base + node(__ffs(m) - 1);
+        mem[at + n] = i;
+        memb[(long long)first * 8 + n] = i;
+        ++n;
+    }
+    for (; n < 8; ++n) memb[(long long)first * 8 + n] = -1;
 }
 
 // ---------------------------------------------------------------- pieces of an ELL level
-__global__ void k_piece_init_ell(int n, int K, const int *__restrict__ col, const double *__restrict__ val,
-                                 int *parent)
+// (parent[i] = i for a row with a positive diagonal, else -1: written by the kernel that made the level)
+// KR: entries of a row whose loads go out together (its columns and values, then their positions); the rest of a
+// wider row goes one by one.
+template <int KR>
+__global__ __launch_bounds__(256) void k_piece_union_ell(int n, int K, const int *__restrict__ col,
+                                                         const double *__restrict__ val, const int4 *__restrict__ pos,
+                                                         int *parent)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        double d = 0.0;
-        for (int k = 0; k < K; ++k)
-            if (col[(long long)k * n + i] >= 0) d += val[(long long)k * n + i];
-        parent[i] = d > 0.0 ? i : -1;
-    }
-}
-
-__global__ void k_piece_union_ell(int n, int K, const int *__restrict__ col, const double *__restrict__ val,
-                                  const int4 *__restrict__ pos, int *parent)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        if (parent[i] < 0) continue;
-        const int4 pi = pos[i];
-        for (int k = 0; k < K; ++k) {
-            const int j = col[(long long)k * n + i];
-            if (j <= i || !(val[(long long)k * n + i] > 0.0)) continue;
-            const int4 pj = pos[j];
-            if ((pi.x >> 1) == (pj.x >> 1) && (pi.y >> 1) == (pj.y >> 1) && (pi.z >> 1) == (pj.z >> 1))
-                uf_unite(parent, i, j);
-        }
-    }
-}
-
-__global__ void k_piece_pos_ell(int n, const int *__restrict__ parent, const int *__restrict__ idx,
-                                const int4 *__restrict__ fpos, int4 *pos)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        if (parent[i] == i) {
-            const int4 p = fpos[i];
-            pos[idx[i]] = make_int4(p.x >> 1, p.y >> 1, p.z >> 1, 0);
-        }
-}
-
-// ---------------------------------------------------------------- shared steps
-__global__ void k_piece_flatten(int *parent, long long n, int *flag)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        int r = -1;
-        if (uf_load(parent, (int)i) >= 0) r = uf_find(parent, (int)i);
-        flag[i] = (r == (int)i) ? 1 : 0;
-    }
-}
-
-__global__ void k_piece_store_root(int *parent, long long n)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int p = uf_load(parent, (int)i);
-        if (p >= 0) parent[i] = uf_find(parent, (int)i);
-    }
-}
-
-__global__ void k_piece_assign(const int *__restrict__ parent, const int *__restrict__ idx, long long n, int *agg,
-                               int *count)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int p = parent[i];
-        const int a = p >= 0 ? idx[p] : -1;
-        agg[i] = a;
-        if (a >= 0) atomicAdd(count + a, 1);
-    }
-}
-
-// members of each coarse unknown, in increasing fine index (deterministic order)
-__global__ void k_members_fill(const int *__restrict__ agg, long long n, const int *__restrict__ mptr, int *cursor,
-                               int *mem)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const int a = agg[i];
-        if (a >= 0) mem[mptr[a] + atomicAdd(cursor + a, 1)] = (int)i;
-    }
-}
-
-__global__ void k_members_sort(int nc, const int *__restrict__ mptr, int *mem)
-{
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < nc; p += gridDim.x * blockDim.x) {
-        const int b = mptr[p], e = mptr[p + 1];
-        for (int i = b + 1; i < e; ++i) {
-            const int v = mem[i];
-            int j = i - 1;
-            while (j >= b && mem[j] > v) {
-                mem[j + 1] = mem[j];
-                --j;
-            }
-            mem[j + 1] = v;
-        }
-    }
-}
-
-// Direct member table of the restriction: memb[p*8 + j] = member j of aggregate p (-1: none), one load
-// instead of the CSR pair (pointer, then member); an aggregate with more than eight members sets *over
-// (the restriction then keeps the CSR form).
-__global__ void k_members8(int nc, const int *__restrict__ mptr, const int *__restrict__ mem, int *__restrict__ memb,
-                           int *over)
-{
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < nc; p += gridDim.x * blockDim.x) {
-        const int b = mptr[p], e = mptr[p + 1];
-        if (e - b > 8) *over = 1;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int4 pi = pos[i];
+    auto together = [&](const int4 &pj) {
+        return (pi.x >> 1) == (pj.x >> 1) && (pi.y >> 1) == (pj.y >> 1) && (pi.z >> 1) == (pj.z >> 1);
+    };
+    int j[KR];
+    double w[KR];
+    int4 pj[KR];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) memb[(long long)p * 8 + j] = b + j < e ? mem[b + j] : -1;
+    for (int k = 0; k < KR; ++k) {
+        j[k] = col[(long long)k * n + i];
+        w[k] = val[(long long)k * n + i];
     }
+#pragma unroll
+    for (int k = 0; k < KR; ++k) pj[k] = pos[j[k] >= 0 ? j[k] : i];
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+        if (j[k] > i && w[k] > 0.0 && together(pj[k])) uf_unite(parent, i, j[k]);
+    for (int k = KR; k < K; ++k) {
+        const int m = col[(long long)k * n + i];
+        if (m > i && val[(long long)k * n + i] > 0.0 && together(pos[m])) uf_unite(parent, i, m);
+    }
+}
+
+// root of every row (-1: none), number of the roots before it in its workgroup's rows, and their total
+constexpr int ROOTS_WG = 256;
+__global__ __launch_bounds__(ROOTS_WG) void k_piece_roots(int *parent, int n, int *__restrict__ root,
+                                                          int *__restrict__ idx, int *__restrict__ part)
+{
+    __shared__ int count[ROOTS_WG / 64];
+    const int i = blockIdx.x * ROOTS_WG + threadIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int r = -1;
+    if (i < n && uf_load(parent, i) >= 0) r = uf_find(parent, i);
+    const unsigned long long m = __ballot(r >= 0 && r == i);
+    if (lane == 0) count[wv] = __popcll(m);
+    __syncthreads();
+    int before = __popcll(m & ((1ull << lane) - 1ull)), total = 0;
+    for (int k = 0; k < ROOTS_WG / 64; ++k) {
+        if (k < wv) before += count[k];
+        total += count[k];
+    }
+    if (i < n) {
+        root[i] = r;
+        idx[i] = before;
+    }
+    if (threadIdx.x == 0) part[blockIdx.x] = total;
+}
+
+// aggregate of every row, position of its pieces, number of members (count cleared before)
+__global__ void k_piece_assign(int n, const int *__restrict__ root, const int *__restrict__ idx,
+                               const int *__restrict__ part, const int4 *__restrict__ fpos, int *__restrict__ agg,
+                               int4 *__restrict__ pos, int *count)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int r = root[i];
+    const int a = r >= 0 ? idx[r] + part[r / ROOTS_WG] : -1;
+    agg[i] = a;
+    if (a < 0) return;
+    atomicAdd(count + a, 1);
+    if (r == i) {
+        const int4 p = fpos[i];
+        pos[a] = make_int4(p.x >> 1, p.y >> 1, p.z >> 1, 0);
+    }
+}
+
+// members of each coarse unknown; put in increasing fine index (deterministic order) by the sort, which also writes
+// the direct table and sets stat->over when an aggregate has more than eight (the restriction then keeps the CSR form)
+__global__ void k_members_fill(const int *__restrict__ agg, int n, const int *__restrict__ mptr, int *cursor, int *mem)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int a = agg[i];
+    if (a >= 0) mem[mptr[a] + atomicAdd(cursor + a, 1)] = i;
+}
+
+__global__ void k_members_sort(int nc, const int *__restrict__ mptr, int *mem, int *__restrict__ memb, EllStat *stat)
+{
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= nc) return;
+    const int b = mptr[p], e = mptr[p + 1];
+    if (e - b <= 8) {   // in registers: odd-even transposition, absent members last
+        unsigned v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = b + j < e ? (unsigned)mem[b + j] : 0xffffffffu;
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+#pragma unroll
+            for (int j = r & 1; j + 1 < 8; j += 2) {
+                const unsigned lo = v[j] < v[j + 1] ? v[j] : v[j + 1], hi = v[j] < v[j + 1] ? v[j + 1] : v[j];
+                v[j] = lo;
+                v[j + 1] = hi;
+            }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (b + j < e) mem[b + j] = (int)v[j];
+            memb[(long long)p * 8 + j] = (int)v[j];   // (absent: -1)
+        }
+        return;
+    }
+    for (int i = b + 1; i < e; ++i) {
+        const int v = mem[i];
+        int j = i - 1;
+        while (j >= b && mem[j] > v) {
+            mem[j + 1] = mem[j];
+            --j;
+        }
+        mem[j + 1] = v;
+    }
+    stat->over = 1;
 }
 
 // ---------------------------------------------------------------- Galerkin rows
@@ -299,6 +380,97 @@ __global__ void k_max_int(const int *__restrict__ v, int n, int *out)
     if (threadIdx.x == 0) *out = s[0];
 }
 
+// Rows of at most ELL_K8 entries, which nearly all levels have, in one pass: eight lanes per row.  Lane q collects the
+// edges of member q (of each round of eight members), then the eight lanes go through all of them in the order of
+// the general kernel, lane s holding entry s of the row.  The row's diagonal, its inverse and its start value of the
+// next level's union-find follow.  A row with more entries sets stat->longest, and the level is built by the
+// general kernel.  (One thread per row with its entries in scratch memory, once to count and once to fill: 2 x 45 us
+// for 21 k rows, 2 x 70 us for 3 k, and five waits of the host per level; this form 13 and 16 us.)
+template <bool BRICK>
+__global__ __launch_bounds__(256) void k_galerkin_rows8(FineLevel f, const int *__restrict__ agg, int nc,
+                                                        const int *__restrict__ mptr, const int *__restrict__ mem,
+                                                        int *__restrict__ col, double *__restrict__ val64,
+                                                        float *__restrict__ val32, double *__restrict__ d64,
+                                                        float *__restrict__ d32, int *__restrict__ parent, EllStat *stat)
+{
+    constexpr int E = BRICK ? 6 : ELL_K8;
+    const int lane = threadIdx.x & 63, s = lane & 7, first = lane & ~7;
+    const int p = blockIdx.x * 32 + (threadIdx.x >> 3);
+    const bool row = p < nc;
+    const int mb = row ? mptr[p] : 0, me = row ? mptr[p + 1] : 0;
+    int c = -1, m = 0;
+    double ws = 0.0;
+    for (int r = mb; __any(r < me); r += 8) {
+        int a[E];
+        double w[E];
+        const bool have = r + s < me;
+        const int i = have ? mem[r + s] : 0;
+        if (BRICK) {
+            const int b = i / BS, t = i % BS;
+            int tx, ty, tz;
+            brick_xyz(t, tx, ty, tz);
+            int nb[6];
+            brick_nbrs(f.nbr, b, nb);
+            long long I[6];
+            nbr_index((long long)b * BS, t, tx, ty, tz, nb, I);
+            double W[6];
+            stored_weights(f.w, f.stride, (long long)b * BS, t, I, W);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                a[k] = agg[I[k]];
+                w[k] = W[k];
+                if (!(have && W[k] > 0.0 && I[k] != i && a[k] != p)) a[k] = -1;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                a[k] = f.col[(long long)k * f.n + i];
+                w[k] = f.val[(long long)k * f.n + i];
+            }
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                const int j = a[k];
+                a[k] = agg[j >= 0 ? j : i];
+                if (!(have && j >= 0 && w[k] > 0.0 && a[k] != p)) a[k] = -1;
+            }
+        }
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                const int A = __shfl(a[k], first + q, 64);
+                const double v = __shfl(w[k], first + q, 64);
+                const bool match = A >= 0 && c == A;
+                const bool found = ((__ballot(match) >> first) & 255ull) != 0ull;
+                if (match) ws += v;
+                if (A >= 0 && !found) {
+                    if (s == m) {
+                        c = A;
+                        ws = v;
+                    }
+                    ++m;
+                }
+            }
+    }
+    if (m > ELL_K8 && s == 0) atomicMax(&stat[blockIdx.x % LEVEL_STATS].longest, (unsigned)m);
+    if (row) {
+        const long long e = (long long)s * nc + p;
+        col[e] = c;
+        val64[e] = ws;
+        val32[e] = (float)ws;
+    }
+    double d = 0.0;
+    for (int q = 0; q < 8; ++q) d += __shfl(ws, first + q, 64);
+    const bool unknown = row && s == 0 && d > 0.0;
+    const int count = __popcll(__ballot(unknown));
+    if (lane == 0 && count) atomicAdd(&stat[blockIdx.x % LEVEL_STATS].count, (unsigned)count);
+    if (row && s == 0) {
+        const double v = d > 0.0 ? 1.0 / d : 0.0;
+        if (d64) d64[p] = v;
+        if (d32) d32[p] = (float)v;
+        parent[p] = d > 0.0 ? p : -1;
+    }
+}
+
 static unsigned gblocks(long long n, int bs = 256, long long cap = 65536)
 {
     long long b = (n + bs - 1) / bs;
@@ -306,70 +478,54 @@ static unsigned gblocks(long long n, int bs = 256, long long cap = 65536)
     return (unsigned)(b > cap ? cap : b);
 }
 
-hipError_t launch_pieces_brick(const double *w64, long long stride, Topo topo, const int4 *coord, int *parent,
+hipError_t launch_pieces_brick(const double *w64, long long stride, Topo topo, uint8_t *reach, int *part, int *nc,
                                hipStream_t s)
 {
-    if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_piece_init_brick, dim3(topo.nb), dim3(NT), 0, s, w64, stride, topo, parent);
-    SPFD_LAUNCH(k_piece_union_brick, dim3(topo.nb), dim3(NT), 0, s, w64, stride, topo, parent);
-    (void)coord;
-    return hipGetLastError();
+    if (topo.nb <= 0) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_pieces_brick, dim3(topo.nb), dim3(NT), 0, s, w64, stride, topo, reach, part);
+    HIP_RETURN_IF(hipGetLastError());
+    HIP_RETURN_IF(scan_small(part, topo.nb, nc, s));
+    return scan_small(part + topo.nb, topo.nb, nullptr, s);
 }
 
-hipError_t launch_pieces_ell(int n, int K, const int *col, const double *val, const int4 *pos, int *parent,
-                             hipStream_t s)
+hipError_t launch_pieces_write(const uint8_t *reach, int nb, const int4 *coord, const int *part, int nc, int *agg,
+                               int4 *pos, int *mptr, int *mem, int *memb, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_piece_init_ell, dim3(gblocks(n)), dim3(256), 0, s, n, K, col, val, parent);
-    SPFD_LAUNCH(k_piece_union_ell, dim3(gblocks(n)), dim3(256), 0, s, n, K, col, val, pos, parent);
+    if (nb <= 0 || nc <= 0) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_pieces_write, dim3(nb), dim3(NT), 0, s, reach, nb, coord, part, nc, agg, pos, mptr, mem, memb);
     return hipGetLastError();
 }
 
-hipError_t launch_pieces_finish(int *parent, long long n, int *flag, hipStream_t s)
+int piece_parts(int n) { return (n + ROOTS_WG - 1) / ROOTS_WG; }
+
+hipError_t launch_pieces_ell(int n, int K, const int *col, const double *val, const int4 *pos, int *parent, int *root,
+                             int *idx, int *part, int *nc, hipStream_t s)
 {
-    SPFD_LAUNCH(k_piece_store_root, dim3(gblocks(n)), dim3(256), 0, s, parent, n);
-    SPFD_LAUNCH(k_piece_flatten, dim3(gblocks(n)), dim3(256), 0, s, parent, n, flag);
-    return hipGetLastError();
+    if (n <= 0) return hipErrorInvalidValue;
+    if (K < ELL_K8) return hipErrorInvalidValue;   // (every level is stored with that many or more)
+    SPFD_LAUNCH(k_piece_union_ell<ELL_K8>, dim3((n + 255) / 256), dim3(256), 0, s, n, K, col, val, pos, parent);
+    SPFD_LAUNCH(k_piece_roots, dim3(piece_parts(n)), dim3(ROOTS_WG), 0, s, parent, n, root, idx, part);
+    HIP_RETURN_IF(hipGetLastError());
+    return scan_small(part, piece_parts(n), nc, s);
 }
 
-hipError_t launch_pieces_assign(const int *parent, const int *idx, long long n, int *agg, int *count, hipStream_t s)
+hipError_t launch_members_ell(int n, const int *root, const int *idx, int *part, const int4 *fpos, int nc,
+                              int *agg, int4 *pos, int *mptr, int *cursor, int *mem, int *memb, EllStat *stat,
+                              hipStream_t s)
 {
-    SPFD_LAUNCH(k_piece_assign, dim3(gblocks(n)), dim3(256), 0, s, parent, idx, n, agg, count);
+    if (n <= 0 || nc <= 0) return hipErrorInvalidValue;
+    const dim3 rows((n + 255) / 256);
+    // mptr holds the numbers of members, cleared by the caller with the cursors, and becomes their exclusive sums
+    // (scratch: part, n / ROOTS_WG >= (nc + 1) / SCAN_CHUNK ints, read by then)
+    SPFD_LAUNCH(k_piece_assign, rows, dim3(256), 0, s, n, root, idx, part, fpos, agg, pos, mptr);
+    HIP_RETURN_IF(hipGetLastError());
+    HIP_RETURN_IF(scan_ints(mptr, nc + 1, part, s));
+    SPFD_LAUNCH(k_members_fill, rows, dim3(256), 0, s, agg, n, mptr, cursor, mem);
+    SPFD_LAUNCH(k_members_sort, dim3((nc + 255) / 256), dim3(256), 0, s, nc, mptr, mem, memb, stat);
     return hipGetLastError();
 }
 
-hipError_t launch_piece_pos_brick(const int *parent, const int *idx, Topo topo, const int4 *coord, int4 *pos,
-                                  hipStream_t s)
-{
-    if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_piece_pos_brick, dim3(topo.nb), dim3(NT), 0, s, parent, idx, topo, coord, pos);
-    return hipGetLastError();
-}
-
-hipError_t launch_piece_pos_ell(int n, const int *parent, const int *idx, const int4 *fpos, int4 *pos, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_piece_pos_ell, dim3(gblocks(n)), dim3(256), 0, s, n, parent, idx, fpos, pos);
-    return hipGetLastError();
-}
-
-hipError_t launch_members(const int *agg, long long n, int nc, const int *mptr, int *cursor, int *mem, hipStream_t s)
-{
-    SPFD_LAUNCH(k_members_fill, dim3(gblocks(n)), dim3(256), 0, s, agg, n, mptr, cursor, mem);
-    if (nc > 0) SPFD_LAUNCH(k_members_sort, dim3(gblocks(nc)), dim3(256), 0, s, nc, mptr, mem);
-    return hipGetLastError();
-}
-
-hipError_t launch_members8(int nc, const int *mptr, const int *mem, int *memb, int *over, hipStream_t s)
-{
-    if (nc <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_members8, dim3(gblocks(nc)), dim3(256), 0, s, nc, mptr, mem, memb, over);
-    return hipGetLastError();
-}
-
-hipError_t launch_galerkin_ell(const FineLevelArgs &fa, const int *agg, int nc, const int *mptr, const int *mem,
-                               int pass, int *len, int K, int *col, double *val64, float *val32, int *overflow,
-                               int *maxlen, hipStream_t s)
+static FineLevel fine_level(const FineLevelArgs &fa)
 {
     FineLevel f;
     f.w = fa.w;
@@ -379,6 +535,29 @@ hipError_t launch_galerkin_ell(const FineLevelArgs &fa, const int *agg, int nc, 
     f.K = fa.K;
     f.col = fa.col;
     f.val = fa.val;
+    return f;
+}
+
+hipError_t launch_galerkin_rows8(const FineLevelArgs &fa, const int *agg, int nc, const int *mptr, const int *mem,
+                                 int *col, double *val64, float *val32, double *d64, float *d32, int *parent,
+                                 EllStat *stat, hipStream_t s)
+{
+    if (nc <= 0 || (!fa.w && fa.K != ELL_K8)) return hipErrorInvalidValue;
+    const dim3 grid((nc + 31) / 32);
+    if (fa.w)
+        SPFD_LAUNCH(k_galerkin_rows8<true>, grid, dim3(256), 0, s, fine_level(fa), agg, nc, mptr, mem, col, val64, val32,
+                    d64, d32, parent, stat);
+    else
+        SPFD_LAUNCH(k_galerkin_rows8<false>, grid, dim3(256), 0, s, fine_level(fa), agg, nc, mptr, mem, col, val64,
+                    val32, d64, d32, parent, stat);
+    return hipGetLastError();
+}
+
+hipError_t launch_galerkin_ell(const FineLevelArgs &fa, const int *agg, int nc, const int *mptr, const int *mem,
+                               int pass, int *len, int K, int *col, double *val64, float *val32, int *overflow,
+                               int *maxlen, hipStream_t s)
+{
+    const FineLevel f = fine_level(fa);
     if (nc <= 0) return hipSuccess;
     SPFD_LAUNCH(k_galerkin_rows, dim3(gblocks(nc, 128)), dim3(128), 0, s, f, agg, nc, mptr, mem, pass, len, K,
                        col, val64, val32, overflow);
@@ -531,7 +710,6 @@ __device__ __forceinline__ T fine_resid(const FineLevelT<T> &f, const T *__restr
 // depend on scheduling.  With xc: also the coarse level's first Chebyshev
 // step, xc = c0 D^-1 b_c.
 constexpr int RLANES = 8;
-constexpr int ELL_K8 = 8;   // row width of the fixed-width ELL kernels
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_restrict_rows(FineLevelT<T> f, int nc, const int *__restrict__ mptr,
@@ -613,23 +791,30 @@ __global__ __launch_bounds__(256) void k_restrict8(FineLevelT<T> f, int nc, cons
 }
 
 // inverse diagonals (0 where the diagonal vanishes) of an ELL level
-__global__ void k_dinv_ell(int n, int K, const int *__restrict__ col, const double *__restrict__ val,
-                           double *__restrict__ d64, float *__restrict__ d32)
+__global__ __launch_bounds__(256) void k_ell_setup(int n, int K, const int *__restrict__ col,
+                                                   const double *__restrict__ val, double *__restrict__ d64,
+                                                   float *__restrict__ d32, int *__restrict__ parent, EllStat *stat)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        double d = 0.0;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    double d = 0.0;
+    if (i < n) {
         for (int k = 0; k < K; ++k)
             if (col[(long long)k * n + i] >= 0) d += val[(long long)k * n + i];
         const double v = d > 0.0 ? 1.0 / d : 0.0;
         if (d64) d64[i] = v;
         if (d32) d32[i] = (float)v;
+        parent[i] = d > 0.0 ? i : -1;
     }
+    const int count = __popcll(__ballot(d > 0.0));
+    if ((threadIdx.x & 63) == 0 && count) atomicAdd(&stat[blockIdx.x % LEVEL_STATS].count, (unsigned)count);
 }
 
-hipError_t launch_dinv_ell(int n, int K, const int *col, const double *val, double *d64, float *d32, hipStream_t s)
+// inverse diagonals, start of the next level's union-find and number of unknowns of a level made by the general kernel
+hipError_t launch_ell_setup(int n, int K, const int *col, const double *val, double *d64, float *d32, int *parent,
+                            EllStat *stat, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_dinv_ell, dim3(gblocks(n)), dim3(256), 0, s, n, K, col, val, d64, d32);
+    SPFD_LAUNCH(k_ell_setup, dim3((n + 255) / 256), dim3(256), 0, s, n, K, col, val, d64, d32, parent, stat);
     return hipGetLastError();
 }
 

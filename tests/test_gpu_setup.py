@@ -43,3 +43,26 @@ def test_unknowns_and_components(shape, fill, voxel):
     with pytest.raises(P.SPFDError):   # the last voxel's label is not in the table
         lab[-1, -1, -1] = 7
         P.Solver(torch.from_numpy(lab).to(DEV), [0.0, 0.4], h)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,fill,split_level", [((20, 21, 37), 0.28, 1), ((24, 24, 24), 0.4, 1),
+                                                    ((31, 40, 33), 0.22, 2), ((40, 40, 40), 0.34, 1)], ids=str)
+def test_split_levels(shape, fill, split_level, prec):
+    """Split levels of random sparse bodies, where pieces have many neighbours and aggregates more than eight
+    members, down to a coarsest level of at most 48 unknowns: the Galerkin operators are exact, so the solve reaches
+    1e-12 and agrees with the oracle's (also at 1e-12) to the condition number times that, below 1e-7."""
+    print(f"case split {shape} {fill} {split_level} {prec}", flush=True)
+    rng = np.random.default_rng(shape[0] + shape[2])
+    lab = (rng.random(shape) < fill).astype(np.uint8) * rng.integers(1, 4, shape).astype(np.uint8)
+    lab[0, 0, 0] = 1
+    table, h = [0.0, 0.1, 0.6, 1.7], (2e-3, 2e-3, 3e-3)
+    a = rng.standard_normal((3,) + tuple(n + 1 for n in shape))
+    s = P.Solver(torch.from_numpy(lab).to(DEV), table, h, precision=prec, split_level=split_level, coarsest_max=48)
+    psi, info = s.solve(torch.from_numpy(a).to(DEV), tol=1e-12, max_iter=400)
+    widths = [P.spfd_level_info(s.handle, k)["row_entries"] for k in range(s.info()["n_levels"])]
+    s.close()
+    ref, _ = oracle.solve(np.asarray(table)[lab], h, a, tol=1e-12)
+    print("row entries", widths, "iterations", info["iterations"], flush=True)
+    assert info["status"] == "OK" and min(widths) == 7 and max(widths) >= 9
+    assert np.linalg.norm(psi.cpu().numpy() - ref) <= 1e-7 * np.linalg.norm(ref)
