@@ -36,8 +36,6 @@ struct Level {
     int N[3] = {0, 0, 0};        // nodes
     int G[3] = {0, 0, 0};        // bricks
     int nb = 0;
-    std::vector<int> slot_of;    // dense brick grid -> slot (host)
-    std::vector<int4> coord;     // slot -> brick coordinates (host)
     int *d_slot_of = nullptr;
     int *d_nbr = nullptr;
     int4 *d_coord = nullptr;
@@ -169,8 +167,6 @@ struct Ctx {
     std::vector<std::pair<int, int>> seg_cache;   // per level: bricks and the tuned segment (4 or 8)
     int *d_ints = nullptr;    // small scratch ints
     int *h_ints = nullptr;    // pinned: scratch (LEVEL_STATS entries), then the number of components
-    uint8_t *h_stage = nullptr;   // pinned staging for the host-built tables of the hierarchy
-    size_t stage_cap = 0;
     // the library's own stream (all work) and the caller's stream it follows
     hipStream_t user_stream = nullptr;
     hipEvent_t ev_user = nullptr;
@@ -408,71 +404,39 @@ struct TScope {
 // packed voxel models start at node layers that are multiples of this, one empty layer apart at least
 constexpr int MODEL_ALIGN = 64;
 
-// ------------------------------------------------------------ brick topology on the host
-// Pinned staging of at least `bytes` (copies from pageable memory go through a
-// slow bounce buffer).  Call only while nothing in the stream uses the previous area.
-uint8_t *stage(Ctx *c, size_t bytes)
+// ------------------------------------------------------------ brick topology
+// Bricks of the structured levels on the device: the finest level (its flags are set) and the levels that 2x2x2
+// aggregation may make of it, L0 first.  One wait of the host, for the numbers of bricks and the error word before
+// them (d_err and, behind it, room for MAX_LEVELS counts), which is returned; nothing else is made if it is set or no
+// brick is active.
+int build_topology(Ctx *c, std::vector<Level> &levels, uint8_t *flags0, int *d_err)
 {
-    if (bytes > c->stage_cap) {
-        HIPCHK(hipStreamSynchronize(c->stream));
-        if (c->h_stage) (void)hipHostFree(c->h_stage);
-        c->h_stage = nullptr;
-        c->stage_cap = 0;
-        const size_t cap = std::max<size_t>(bytes, (size_t)4 << 20);
-        HIPCHK(hipHostMalloc((void **)&c->h_stage, cap, hipHostMallocDefault));
-        c->stage_cap = cap;
+    TopoLevels t{};
+    t.n = (int)levels.size();
+    for (int l = 0; l < t.n; ++l) {
+        TopoLevel &T = t.lv[l];
+        const Level &L = levels[l];
+        for (int d = 0; d < 3; ++d) T.G[d] = L.G[d];
+        T.cells = L.G[0] * L.G[1] * L.G[2];
+        T.flags = l == 0 ? flags0 : dalloc<uint8_t>(c, c->hier_allocs, T.cells);
+        T.part = dalloc<int>(c, c->hier_allocs, T.cells / TOPO_WG + 1);
     }
-    return c->h_stage;
-}
-
-void build_topology(Ctx *c, Level &L, const std::vector<uint8_t> &flags, std::vector<void *> &owner)
-{
-    const int G0 = L.G[0], G1 = L.G[1], G2 = L.G[2];
-    L.slot_of.assign((size_t)G0 * G1 * G2, -1);
-    L.coord.clear();
-    // slots in brick-grid order (x fastest): neighbours along x are adjacent slots
-    for (int bz = 0; bz < G2; ++bz)
-        for (int by = 0; by < G1; ++by)
-            for (int bx = 0; bx < G0; ++bx) {
-                const size_t id = bx + (size_t)G0 * (by + (size_t)G1 * bz);
-                if (flags[id]) {
-                    L.slot_of[id] = (int)L.coord.size();
-                    L.coord.push_back(make_int4(bx, by, bz, 0));
-                }
-            }
-    L.nb = (int)L.coord.size();
-    std::vector<int> nbr((size_t)L.nb * 6 + 6, -1);
-    auto look = [&](int x, int y, int z) -> int {
-        if (x < 0 || y < 0 || z < 0 || x >= G0 || y >= G1 || z >= G2) return -1;
-        return L.slot_of[x + (size_t)G0 * (y + (size_t)G1 * z)];
-    };
-    for (int s = 0; s < L.nb; ++s) {
-        const int4 q = L.coord[s];
-        nbr[s * 6 + NMX] = look(q.x - 1, q.y, q.z);
-        nbr[s * 6 + NPX] = look(q.x + 1, q.y, q.z);
-        nbr[s * 6 + NMY] = look(q.x, q.y - 1, q.z);
-        nbr[s * 6 + NPY] = look(q.x, q.y + 1, q.z);
-        nbr[s * 6 + NMZ] = look(q.x, q.y, q.z - 1);
-        nbr[s * 6 + NPZ] = look(q.x, q.y, q.z + 1);
-    }
-    L.d_slot_of = dalloc<int>(c, owner, L.slot_of.size());
-    L.d_nbr = dalloc<int>(c, owner, nbr.size());
-    L.d_coord = dalloc<int4>(c, owner, L.coord.size() + 1);
-    // the three tables through one pinned staging area
-    const size_t b0 = L.slot_of.size() * sizeof(int), b1 = nbr.size() * sizeof(int),
-                 b2 = L.coord.size() * sizeof(int4);
-    const size_t o1 = (b0 + 255) & ~(size_t)255, o2 = o1 + ((b1 + 255) & ~(size_t)255);
-    uint8_t *st = stage(c, o2 + b2);
-    memcpy(st, L.slot_of.data(), b0);
-    memcpy(st + o1, nbr.data(), b1);
-    if (b2) memcpy(st + o2, L.coord.data(), b2);
-    HIPCHK(hipMemcpyAsync(L.d_slot_of, st, b0, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(L.d_nbr, st + o1, b1, hipMemcpyHostToDevice, c->stream));
-    if (L.nb) HIPCHK(hipMemcpyAsync(L.d_coord, st + o2, b2, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(launch_topo_count(t, d_err + 1, c->stream));
+    HIPCHK(hipMemcpyAsync(c->h_ints, d_err, (1 + t.n) * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    if (c->h_ints[0] != 0 || c->h_ints[1] == 0) return c->h_ints[0];
+    for (int l = 0; l < t.n; ++l) {
+        TopoLevel &T = t.lv[l];
+        Level &L = levels[l];
+        L.nb = T.nb = c->h_ints[1 + l];
+        L.d_slot_of = T.slot_of = dalloc<int>(c, c->hier_allocs, T.cells);
+        L.d_coord = T.coord = dalloc<int4>(c, c->hier_allocs, L.nb);
+        L.d_nbr = T.nbr = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 6);
+        if (l + 1 < t.n) L.d_parent_slot = T.parent_slot = dalloc<int>(c, c->hier_allocs, L.nb);
+    }
+    HIPCHK(launch_topo_fill(t, c->stream));
+    return 0;
 }
-
-constexpr int MAX_LEVELS = 20;
 
 // the statistics of a level whose setup kernel is queued (waits for it)
 const LevelStat *fetch_stat(Ctx *c, const void *d_stat)
@@ -1383,29 +1347,37 @@ spfd_status do_build(Ctx *c)
     Grid &g = c->g;
     // 1. bricks of the finest level + input validation
     const size_t nbg = (size_t)g.Gx * g.Gy * g.Gz;
-    // cleared at once: the levels' statistics, the error word and, right behind it, the brick flags
-    const size_t stat_bytes = MAX_LEVELS * LEVEL_STATS * sizeof(LevelStat);
-    uint8_t *d_head = dalloc<uint8_t>(c, c->hier_allocs, stat_bytes + sizeof(int) + nbg);
+    // cleared at once: the levels' statistics, the error word, room for their numbers of bricks and the brick flags
+    const size_t stat_bytes = MAX_LEVELS * LEVEL_STATS * sizeof(LevelStat), flags_at = stat_bytes + 256;
+    static_assert((1 + MAX_LEVELS) * sizeof(int) <= 256, "error word and brick counts");
+    if (nbg > 0x7fffffffULL) return fail(c, SPFD_INVALID_ARG, "grid too large");
+    uint8_t *d_head = dalloc<uint8_t>(c, c->hier_allocs, flags_at + nbg);
     LevelStat *d_stat = (LevelStat *)d_head;
     int *d_err = (int *)(d_head + stat_bytes);
-    HIPCHK(hipMemsetAsync(d_head, 0, padded(stat_bytes + sizeof(int) + nbg), c->stream));
+    HIPCHK(hipMemsetAsync(d_head, 0, padded(flags_at + nbg), c->stream));
     HIPCHK(launch_brick_flags(c->d_labels, c->d_table64, c->nlab, c->voxel_mode ? c->d_sigvox : nullptr, g,
-                              (uint8_t *)(d_err + 1), d_err, c->stream));
-    uint8_t *hflags = stage(c, sizeof(int) + nbg);
-    HIPCHK(hipMemcpyAsync(hflags, d_err, sizeof(int) + nbg, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    int bad;
-    memcpy(&bad, hflags, sizeof(int));
-    std::vector<uint8_t> flags(hflags + sizeof(int), hflags + sizeof(int) + nbg);
+                              d_head + flags_at, d_err, c->stream));
+    // the structured levels there may be: from level split_level on, coarse levels are unstructured
+    std::vector<Level> structured(1);
+    for (int d = 0; d < 3; ++d) structured[0].N[d] = d == 0 ? g.Nx : d == 1 ? g.Ny : g.Nz;
+    structured[0].G[0] = g.Gx; structured[0].G[1] = g.Gy; structured[0].G[2] = g.Gz;
+    while (structured.size() < MAX_LEVELS && (c->opt.no_split || (int)structured.size() <= c->opt.split_level)) {
+        const Level &F = structured.back();
+        if (F.N[0] == 1 && F.N[1] == 1 && F.N[2] == 1) break;
+        Level C;
+        for (int d = 0; d < 3; ++d) {
+            C.N[d] = (F.N[d] + 1) / 2;
+            C.G[d] = (C.N[d] + 7) / 8;
+        }
+        structured.push_back(C);
+    }
+    const int bad = build_topology(c, structured, d_head + flags_at, d_err);
     if (bad == 1) return fail(c, SPFD_INVALID_ARG, "a voxel label is not covered by the sigma table");
     if (bad == 2) return fail(c, SPFD_INVALID_ARG, "per-voxel sigma must be finite and >= 0");
-    c->lv.emplace_back();
+    if (structured[0].nb == 0) return fail(c, SPFD_INVALID_ARG, "no conducting voxel");
+    if ((long long)structured[0].nb * BS > 0x7fffffffLL) return fail(c, SPFD_INVALID_ARG, "grid too large");
+    c->lv.push_back(structured[0]);
     Level &L0 = c->lv[0];
-    L0.N[0] = g.Nx; L0.N[1] = g.Ny; L0.N[2] = g.Nz;
-    L0.G[0] = g.Gx; L0.G[1] = g.Gy; L0.G[2] = g.Gz;
-    build_topology(c, L0, flags, c->hier_allocs);
-    if (L0.nb == 0) return fail(c, SPFD_INVALID_ARG, "no conducting voxel");
-    if ((long long)L0.nb * BS > 0x7fffffffLL) return fail(c, SPFD_INVALID_ARG, "grid too large");
     // 2. finest-level conductances (stored FP64 for setup; label tiles for the solve) and what else follows from them
     const long long n_fine = L0.nodes();
     unsigned long long *emask = dalloc<unsigned long long>(c, c->hier_allocs, (size_t)L0.nb * EMASK);
@@ -1446,28 +1418,7 @@ spfd_status do_build(Ctx *c)
             c->lv.push_back(std::move(C));
             continue;
         }
-        Level C;
-        for (int d = 0; d < 3; ++d) {
-            C.N[d] = (F.N[d] + 1) / 2;
-            C.G[d] = (C.N[d] + 7) / 8;
-        }
-        std::vector<uint8_t> cflags((size_t)C.G[0] * C.G[1] * C.G[2], 0);
-        for (int s = 0; s < F.nb; ++s) {
-            const int4 q = F.coord[s];
-            cflags[(q.x >> 1) + (size_t)C.G[0] * ((q.y >> 1) + (size_t)C.G[1] * (q.z >> 1))] = 1;
-        }
-        build_topology(c, C, cflags, c->hier_allocs);
-        std::vector<int> ps(F.nb);
-        for (int s = 0; s < F.nb; ++s) {
-            const int4 q = F.coord[s];
-            ps[s] = C.slot_of[(q.x >> 1) + (size_t)C.G[0] * ((q.y >> 1) + (size_t)C.G[1] * (q.z >> 1))];
-        }
-        F.d_parent_slot = dalloc<int>(c, c->hier_allocs, F.nb);
-        {
-            uint8_t *st = stage(c, ps.size() * sizeof(int));  // (the stream is idle: topology just synced)
-            memcpy(st, ps.data(), ps.size() * sizeof(int));
-            HIPCHK(hipMemcpyAsync(F.d_parent_slot, st, ps.size() * sizeof(int), hipMemcpyHostToDevice, c->stream));
-        }
+        Level C = structured[l + 1];
         C.d_w64 = dalloc<double>(c, c->hier_allocs, (size_t)3 * C.nodes());
         C.d_w32 = dalloc<float>(c, c->hier_allocs, (size_t)3 * C.nodes());
         HIPCHK(launch_galerkin(F.d_w64, F.nodes(), F.d_slot_of, F.G[0], F.G[1], F.G[2], F.N[0], F.N[1], F.N[2], C.d_coord,
@@ -1492,11 +1443,15 @@ spfd_status do_build(Ctx *c)
             if (mw > 0.0f && (double)mp / mw * 32768.0 >= 0x1p-14) {
                 C.w16s = mw / 32768.0f;
                 C.d_w16 = dalloc<uint16_t>(c, c->hier_allocs, (size_t)3 * C.nodes());
-                HIPCHK(launch_w16(C.d_w32, 3LL * C.nodes(), 1.0f / C.w16s, C.d_w16, c->stream));
             }
         }
         c->lv.push_back(std::move(C));
     }
+    // (here, not in the loop: the kernels the host waits for come first)
+    if (c->lv.size() > 1 && c->lv[1].d_w16)
+        HIPCHK(launch_w16(c->lv[1].d_w32, 3LL * c->lv[1].nodes(), 1.0f / c->lv[1].w16s, c->lv[1].d_w16, c->stream));
+    for (size_t l = 0; l < c->lv.size(); ++l)   // (only levels restricted to a structured one have parents)
+        if (!c->lv[l].ell && (l + 1 == c->lv.size() || c->lv[l + 1].ell)) c->lv[l].d_parent_slot = nullptr;
     for (Level &L : c->lv)
         if (!L.ell && L.nb > 0 && L.nb <= LEG_MOST) {
             L.d_nbr27 = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 27);
@@ -1553,8 +1508,11 @@ spfd_status model_ranges(Ctx *c)
     const Level &L0 = c->lv[0];
     int m = 0;
     for (int k = 0; k < c->np; ++k) c->mfirst[k] = c->mcount[k] = 0;
+    std::vector<int4> coord(L0.nb);
+    HIPCHK(hipMemcpyAsync(coord.data(), L0.d_coord, (size_t)L0.nb * sizeof(int4), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
     for (int b = 0; b < L0.nb; ++b) {
-        const int z0 = L0.coord[b].z * BD;   // first node layer of the brick
+        const int z0 = coord[b].z * BD;   // first node layer of the brick
         while (m < c->np && z0 > c->mbox.zoff[m] + c->mbox.nz[m]) ++m;
         if (m == c->np || z0 + BD - 1 < c->mbox.zoff[m])
             return fail(c, SPFD_HIP_ERROR, "a brick lies outside every model's layers");
@@ -2427,7 +2385,6 @@ void spfd_destroy(spfd_handle h)
     for (hipEvent_t e : h->ev_it)
         if (e) (void)hipEventDestroy(e);
     if (h->h_ints) (void)hipHostFree(h->h_ints);
-    if (h->h_stage) (void)hipHostFree(h->h_stage);
     for (int k = 0; k < SPFD_K_COUNT; ++k)
         for (hipEvent_t e : h->tev[k]) (void)hipEventDestroy(e);
     if (h->ev_user) (void)hipEventDestroy(h->ev_user);

@@ -72,6 +72,29 @@ struct Grid {
 // ---------------------------------------------------------------- setup
 hipError_t launch_brick_flags(const uint8_t *labels, const double *table, int nlab, const double *sig_vox,
                               const Grid &g, uint8_t *flags, int *err, hipStream_t s);
+// Bricks of the structured levels, from the finest level's flags: level l's brick grid has the bricks of level l - 1
+// two by two, one is active where a child is.  Slots in brick-grid order (x fastest), so neighbours along x are
+// adjacent slots.
+struct TopoLevel {
+    int G[3];
+    int cells;             // bricks of the grid
+    uint8_t *flags;        // [cells]
+    int *part;             // active bricks per TOPO_WG cells, then their exclusive sums
+    int nb;                // active bricks (known after the host's wait)
+    int *slot_of;          // [cells], -1: not active
+    int4 *coord;           // [nb]
+    int *nbr;              // [nb * 6]
+    int *parent_slot;      // [nb]: slot in the next level (null: there is none)
+};
+constexpr int TOPO_WG = 256;
+constexpr int MAX_LEVELS = 20;
+struct TopoLevels {
+    int n;
+    TopoLevel lv[MAX_LEVELS];
+};
+// flags of the coarser levels and, into nb[l], the active bricks of every level
+hipError_t launch_topo_count(const TopoLevels &t, int *nb, hipStream_t s);
+hipError_t launch_topo_fill(const TopoLevels &t, hipStream_t s);
 // What the build needs to know of a structured level, gathered by many workgroups: LEVEL_STATS entries, all zero at
 // the start, to be added up (count) and maximised (bits of the largest weight, complement of the bits of the
 // smallest positive one, 0x807fffff or more when there is none)

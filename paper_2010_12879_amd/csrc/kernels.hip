@@ -165,6 +165,106 @@ hipError_t launch_brick_flags(const uint8_t *labels, const double *table, int nl
     return hipGetLastError();
 }
 
+// flags of level l from those of level l - 1 (l > 0), and the active bricks of each workgroup's cells
+__global__ __launch_bounds__(TOPO_WG) void k_topo_flags(TopoLevel L, TopoLevel fine, int first)
+{
+    __shared__ int count[TOPO_WG / 64];
+    const int i = blockIdx.x * TOPO_WG + threadIdx.x;
+    int f = 0;
+    if (i < L.cells) {
+        if (first) {
+            f = L.flags[i];
+        } else {
+            const int x = 2 * (i % L.G[0]), y = 2 * (i / L.G[0] % L.G[1]), z = 2 * (i / L.G[0] / L.G[1]);
+            for (int k = 0; k < 8; ++k) {
+                const int cx = x + (k & 1), cy = y + (k >> 1 & 1), cz = z + (k >> 2);
+                if (cx < fine.G[0] && cy < fine.G[1] && cz < fine.G[2])
+                    f |= fine.flags[cx + fine.G[0] * (cy + fine.G[1] * cz)];
+            }
+            L.flags[i] = (uint8_t)f;
+        }
+    }
+    const unsigned long long m = __ballot(f != 0);
+    if ((threadIdx.x & 63) == 0) count[threadIdx.x >> 6] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int k = 0; k < TOPO_WG / 64; ++k) sum += count[k];
+        L.part[blockIdx.x] = sum;
+    }
+}
+
+// slots and coordinates of one level per launch row
+__global__ __launch_bounds__(TOPO_WG) void k_topo_slots(TopoLevels t)
+{
+    __shared__ int count[TOPO_WG / 64];
+    const TopoLevel &L = t.lv[blockIdx.y];
+    if ((int)blockIdx.x * TOPO_WG >= L.cells) return;
+    const int i = blockIdx.x * TOPO_WG + threadIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const bool on = i < L.cells && L.flags[i] != 0;
+    const unsigned long long m = __ballot(on);
+    if (lane == 0) count[wv] = __popcll(m);
+    __syncthreads();
+    int slot = L.part[blockIdx.x] + __popcll(m & ((1ull << lane) - 1ull));
+    for (int k = 0; k < wv; ++k) slot += count[k];
+    if (i >= L.cells) return;
+    L.slot_of[i] = on ? slot : -1;
+    if (on) L.coord[slot] = make_int4(i % L.G[0], i / L.G[0] % L.G[1], i / L.G[0] / L.G[1], 0);
+}
+
+// the six neighbours of every brick and the coarse brick that holds it (slots are complete)
+__global__ __launch_bounds__(TOPO_WG) void k_topo_nbr(TopoLevels t)
+{
+    const int l = blockIdx.y;
+    const TopoLevel &L = t.lv[l];
+    const int b = blockIdx.x * TOPO_WG + threadIdx.x;
+    if (b >= L.nb) return;
+    const int4 c = L.coord[b];
+    auto look = [&](int x, int y, int z) {
+        return x < 0 || y < 0 || z < 0 || x >= L.G[0] || y >= L.G[1] || z >= L.G[2]
+                   ? -1
+                   : L.slot_of[x + L.G[0] * (y + L.G[1] * z)];
+    };
+    int *nbr = L.nbr + (long long)b * 6;
+    nbr[NMX] = look(c.x - 1, c.y, c.z);
+    nbr[NPX] = look(c.x + 1, c.y, c.z);
+    nbr[NMY] = look(c.x, c.y - 1, c.z);
+    nbr[NPY] = look(c.x, c.y + 1, c.z);
+    nbr[NMZ] = look(c.x, c.y, c.z - 1);
+    nbr[NPZ] = look(c.x, c.y, c.z + 1);
+    if (L.parent_slot) {
+        const TopoLevel &C = t.lv[l + 1];
+        L.parent_slot[b] = C.slot_of[(c.x >> 1) + C.G[0] * ((c.y >> 1) + C.G[1] * (c.z >> 1))];
+    }
+}
+
+hipError_t launch_topo_count(const TopoLevels &t, int *nb, hipStream_t s)
+{
+    if (t.n < 1 || t.n > MAX_LEVELS) return hipErrorInvalidValue;
+    for (int l = 0; l < t.n; ++l) {
+        const TopoLevel &L = t.lv[l];
+        const int wg = (L.cells + TOPO_WG - 1) / TOPO_WG;
+        SPFD_LAUNCH(k_topo_flags, dim3(wg), dim3(TOPO_WG), 0, s, L, t.lv[l > 0 ? l - 1 : 0], l == 0);
+        HIP_RETURN_IF(hipGetLastError());
+        HIP_RETURN_IF(scan_small(L.part, wg, nb + l, s));
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_topo_fill(const TopoLevels &t, hipStream_t s)
+{
+    if (t.n < 1 || t.n > MAX_LEVELS || t.lv[t.n - 1].parent_slot) return hipErrorInvalidValue;
+    int cells = 0, nb = 0;
+    for (int l = 0; l < t.n; ++l) {
+        cells = t.lv[l].cells > cells ? t.lv[l].cells : cells;
+        nb = t.lv[l].nb > nb ? t.lv[l].nb : nb;
+    }
+    if (nb <= 0) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_topo_slots, dim3((cells + TOPO_WG - 1) / TOPO_WG, t.n), dim3(TOPO_WG), 0, s, t);
+    SPFD_LAUNCH(k_topo_nbr, dim3((nb + TOPO_WG - 1) / TOPO_WG, t.n), dim3(TOPO_WG), 0, s, t);
+    return hipGetLastError();
+}
+
 // Masks of one brick from the eight waves' node layers, and its unknowns counted into the level's statistics
 __device__ __forceinline__ void brick_masks(bool unknown, int b, unsigned long long *__restrict__ cmask,
                                             LevelStat *stat, unsigned long long nm[8])
