@@ -1,8 +1,9 @@
 // One leg of the multigrid cycle on a small structured level in one kernel.
 //
-// A workgroup owns one brick.  It loads the brick and H nodes around it (H =
-// the level's smoothing degree), runs every Chebyshev step of the leg on that
-// region, exchanging x through LDS, and stores what its own 8x8x8 nodes give:
+// A workgroup owns one brick (on the smallest levels an eighth of one).  It
+// loads it and H nodes around it (H = the level's smoothing degree), runs
+// every Chebyshev step of the leg on that region, exchanging x through LDS,
+// and stores what its own nodes give:
 //   down: the steps from the level's first iterate, the residual and its
 //         restriction (with the coarser level's first iterate);
 //   up:   the coarse-grid correction and the steps; on the finest level also
@@ -48,19 +49,22 @@ __device__ __forceinline__ float brecip<float>(float d) { return __builtin_amdgc
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-template <int H>
+// Block of one workgroup: the brick, or a part of it (BX x BY x BZ nodes)
+template <int H, int BX, int BY, int BZ>
 struct BrickGeom {
-    static constexpr int E = 8 + 2 * H;      // region edge
-    static constexpr int ZS = E / 4;         // nodes per thread, consecutive in z
-    static constexpr int NTH = 4 * E * E;    // threads
-    static constexpr int EC = E * E * E;
+    static constexpr int EX = BX + 2 * H, EY = BY + 2 * H, EZ = BZ + 2 * H;   // region
+    static constexpr int ZS = EZ / 4;                                         // nodes per thread, consecutive in z
+    static constexpr int NTH = 4 * EX * EY;                                   // threads
+    static constexpr int EC = EX * EY * EZ;
+    static constexpr int NX = 8 / BX, NY = 8 / BY, PARTS = NX * NY * (8 / BZ);
+    static_assert(EZ % 4 == 0 && NTH <= 1024 && EC >= BS && NTH >= BX * BY * BZ, "one region, one workgroup");
 };
 
-// distance of region coordinate e from the brick along its axis
-template <int H>
+// distance of region coordinate e from the block (B nodes) along its axis
+template <int H, int B>
 __device__ __forceinline__ int halo_depth(int e)
 {
-    return e < H ? H - e : (e >= 8 + H ? e - 7 - H : 0);
+    return e < H ? H - e : (e >= B + H ? e - (B - 1) - H : 0);
 }
 
 enum { BR_LABEL = 0, BR_STORED = 1, BR_HALF = 2 };
@@ -68,20 +72,27 @@ enum { BR_LABEL = 0, BR_STORED = 1, BR_HALF = 2 };
 // OPK: the operator (label form, stored weights, FP16 weights).  FINE: the finest level (down: the first
 // iterate is c0 D^-1 b, formed here; up: the dot products).  UP: the upward leg.  CELL: the coarser level is
 // an ELL level (member table, aggregate map).
-template <typename T, int H, int OPK, bool FINE, bool UP, bool CELL>
-__global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
+template <typename T, int H, int BX, int BY, int BZ, int OPK, bool FINE, bool UP, bool CELL>
+__global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(BrickLeg<T> A)
 {
 #pragma clang fp contract(off)
-    using G = BrickGeom<H>;
+    using G = BrickGeom<H, BX, BY, BZ>;
     constexpr int SEG = sizeof(T) == 4 ? 8 : 4;   // nodes per lane of the column kernels on the finest level
-    constexpr int E = G::E, ZS = G::ZS, NTH = G::NTH;
+    constexpr int EX = G::EX, EY = G::EY, EZ = G::EZ, EL = EX * EY, ZS = G::ZS, NTH = G::NTH;
     constexpr bool LABEL = OPK == BR_LABEL;
-    constexpr int EV = E + 1, NV = LABEL ? EV * EV * EV : 1;
+    constexpr int VX = EX + 1, VY = EY + 1, VL = VX * VY, NV = LABEL ? VL * (EZ + 1) : 1;
+    auto depth_x = [](int e) { return halo_depth<H, BX>(e); };
+    auto depth_y = [](int e) { return halo_depth<H, BY>(e); };
+    auto depth_z = [](int e) { return halo_depth<H, BZ>(e); };
     __shared__ T xs[2][G::EC], xe[FINE && !UP ? G::EC : 1];
     __shared__ T sig[NV], tab[LABEL ? MAX_LABELS : 1];
     __shared__ int nslot[27], npar[27];
-    const int b = xcd_brick(blockIdx.x, A.nb);
-    if (b < 0) return;
+    const int part = xcd_brick(blockIdx.x, A.nb * G::PARTS);
+    if (part < 0) return;
+    const int b = part / G::PARTS;
+    // the block's place in the brick, and the brick's node at region coordinate 0
+    const int ox = part % G::NX * BX, oy = part / G::NX % G::NY * BY, oz = part % G::PARTS / (G::NX * G::NY) * BZ;
+    const int rx = ox - H, ry = oy - H, rz = oz - H;
     const int t = threadIdx.x;
     const int stop = A.sc[blockIdx.y].done;
     const int4 fc = A.coord[b];
@@ -96,9 +107,9 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
     if (stop) return;   // (uniform)
     const long long vo = blockIdx.y * A.vs;
     // the thread's nodes: region column (ex, ey), layers ez0 .. ez0 + ZS - 1
-    const int ex = t % E, ey = (t / E) % E, ez0 = (t / (E * E)) * ZS;
-    const int hxy = halo_depth<H>(ex) + halo_depth<H>(ey);
-    const int lx = (ex - H) & 7, ly = (ey - H) & 7;
+    const int ex = t % EX, ey = (t / EX) % EY, ez0 = (t / EL) * ZS;
+    const int hxy = depth_x(ex) + depth_y(ey);
+    const int lx = (ex + rx) & 7, ly = (ey + ry) & 7;
     const bool own_xy = hxy == 0;
     const bool act = own_xy && ((cm >> (lx + 8 * ly)) & 1ull);
     // voxel labels of the region (voxel layer v lies below node layer v): one round of loads, no use yet
@@ -108,19 +119,19 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
 #pragma unroll
         for (int k = 0; k < NL; ++k) {
             const int e = t + k * NTH;
-            const int i = 8 * fc.x + e % EV - H - 1, j = 8 * fc.y + (e / EV) % EV - H - 1,
-                      l = 8 * fc.z + e / (EV * EV) - H - 1;
+            const int i = 8 * fc.x + e % VX + rx - 1, j = 8 * fc.y + (e / VX) % VY + ry - 1,
+                      l = 8 * fc.z + e / VL + rz - 1;
             const bool in = e < NV && i >= 0 && j >= 0 && l >= 0 && i < A.g.nx && j < A.g.ny && l < A.g.nz;
             lab[k] = in ? A.labels[i + (long long)A.g.nx * (j + (long long)A.g.ny * l)] : 0;
         }
     }
     __syncthreads();
     auto brick_of = [&](int x, int y, int z) {   // index into nslot / npar of a region coordinate
-        return (x < H ? 0 : x >= 8 + H ? 2 : 1) + 3 * (y < H ? 0 : y >= 8 + H ? 2 : 1) + 9 * (z < H ? 0 : z >= 8 + H ? 2 : 1);
+        return ((x + rx) >> 3) + 1 + 3 * (((y + ry) >> 3) + 1) + 9 * (((z + rz) >> 3) + 1);
     };
     auto slot_of = [&](int x, int y, int z) -> long long {   // slot of a region node, -1 in an absent brick
         const int s = nslot[brick_of(x, y, z)];
-        return s < 0 ? -1 : (long long)s * BS + ((x - H) & 7) + 8 * ((y - H) & 7) + 64 * ((z - H) & 7);
+        return s < 0 ? -1 : (long long)s * BS + ((x + rx) & 7) + 8 * ((y + ry) & 7) + 64 * ((z + rz) & 7);
     };
     // every load of the node data in one round: b, the iterate (down on the finest level: D^-1), the weights
     T bv[ZS], xv[ZS], xf[ZS], W[ZS][6], D[ZS];
@@ -130,7 +141,7 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
     const bool scaled = FINE && A.bscale;
 #pragma unroll
     for (int z = 0; z < ZS; ++z) {
-        const int h = hxy + halo_depth<H>(ez0 + z);
+        const int h = hxy + depth_z(ez0 + z);
         n[z] = h <= H ? slot_of(ex, ey, ez0 + z) : -1;
         bv[z] = xv[z] = T(0);
         if (CELL) ag[z] = -1;
@@ -145,7 +156,7 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
         uint16_t hw[OPK == BR_HALF ? ZS : 1][6];
 #pragma unroll
         for (int z = 0; z < ZS; ++z) {
-            const bool in = n[z] >= 0 && hxy + halo_depth<H>(ez0 + z) < H;
+            const bool in = n[z] >= 0 && hxy + depth_z(ez0 + z) < H;
             const long long mx = in ? slot_of(ex - 1, ey, ez0 + z) : -1, my = in ? slot_of(ex, ey - 1, ez0 + z) : -1;
             const long long mz = in && z == 0 ? slot_of(ex, ey, ez0 - 1) : -1;
             const long long st = A.stride;
@@ -188,9 +199,9 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
             } else if (n[z] >= 0) {
                 const int ez = ez0 + z, p = npar[brick_of(ex, ey, ez)];
                 // fine node (8 f + l) -> node (4 (f & 1) + l / 2) of the parent brick
-                const int px = (((ex - H + 8 * fc.x) >> 3) & 1) * 4 + (lx >> 1);
-                const int py = (((ey - H + 8 * fc.y) >> 3) & 1) * 4 + (ly >> 1);
-                const int pz = (((ez - H + 8 * fc.z) >> 3) & 1) * 4 + (((ez - H) & 7) >> 1);
+                const int px = (((ex + rx + 8 * fc.x) >> 3) & 1) * 4 + (lx >> 1);
+                const int py = (((ey + ry + 8 * fc.y) >> 3) & 1) * 4 + (ly >> 1);
+                const int pz = (((ez + rz + 8 * fc.z) >> 3) & 1) * 4 + (((ez + rz) & 7) >> 1);
                 cv[z] = xc[(long long)p * BS + px + 8 * py + 64 * pz];
             }
         }
@@ -200,27 +211,28 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
             if (!CELL || ag[z] >= 0) xv[z] = fmadd(A.scale, cv[z], xv[z]);
         }
     }
-    // down: what the restriction reads besides the residual, loaded ahead
+    // down: what the restriction reads besides the residual, loaded ahead; the thread's aggregate in the brick
+    const int cx = ox / 2 + t % (BX / 2), cy = oy / 2 + t / (BX / 2) % (BY / 2), cz = oz / 2 + t / (BX * BY / 4);
     int rp = -1, rm[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
     long long rn = 0;
     T rdc = T(0);
     if constexpr (!UP) {
         if constexpr (CELL) {
-            if (t < BS) {   // the first member of a piece stores it
-                const int p = A.agg[(long long)b * BS + t];
+            if (t < BX * BY * BZ) {   // the first member of a piece stores it
+                const int own = b * BS + ox + t % BX + 8 * (oy + t / BX % BY) + 64 * (oz + t / (BX * BY));
+                const int p = A.agg[own];
                 if (p >= 0) {
                     const int4 m0 = ((const int4 *)A.memb)[2 * (long long)p], m1 = ((const int4 *)A.memb)[2 * (long long)p + 1];
                     rm[0] = m0.x, rm[1] = m0.y, rm[2] = m0.z, rm[3] = m0.w;
                     rm[4] = m1.x, rm[5] = m1.y, rm[6] = m1.z, rm[7] = m1.w;
-                    if (rm[0] == b * BS + t) {
+                    if (rm[0] == own) {
                         rp = p;
                         if (A.xcout) rdc = A.dinv_c[p];
                     }
                 }
             }
-        } else if (t < 64) {
-            rn = (long long)npar[13] * BS + ((fc.x & 1) * 4 + (t & 3)) + 8 * ((fc.y & 1) * 4 + ((t >> 2) & 3)) +
-                 64 * ((fc.z & 1) * 4 + (t >> 4));
+        } else if (t < BX * BY * BZ / 8) {
+            rn = (long long)npar[13] * BS + ((fc.x & 1) * 4 + cx) + 8 * ((fc.y & 1) * 4 + cy) + 64 * ((fc.z & 1) * 4 + cz);
             rp = 0;
             if (A.xcout) rdc = A.dinv_c[rn];
         }
@@ -232,11 +244,11 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
         __syncthreads();
         T lo[4], hi[4];
         auto plane = [&](int v, T q[4]) {
-            const T *p = sig + EV * EV * v + EV * ey + ex;
+            const T *p = sig + VL * v + VX * ey + ex;
             q[0] = p[0];
             q[1] = p[1];
-            q[2] = p[EV];
-            q[3] = p[EV + 1];
+            q[2] = p[VX];
+            q[3] = p[VX + 1];
         };
         plane(ez0, lo);
 #pragma unroll
@@ -255,7 +267,7 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
             T d = fmadd(A.geo4[0], smx, W[z][NPX]);
             d = fmadd(A.geo4[1], smy, d);
             d = fmadd(A.geo4[1], spy, d);
-            d = ((ez0 + z - H) & (SEG - 1)) == 0 ? fmadd(A.geo4[2], smz, d) : d + W[z][NMZ];
+            d = ((ez0 + z + rz) & (SEG - 1)) == 0 ? fmadd(A.geo4[2], smz, d) : d + W[z][NMZ];
             D[z] = fmadd(A.geo4[2], spz, d);
 #pragma unroll
             for (int k = 0; k < 4; ++k) lo[k] = hi[k];
@@ -280,17 +292,17 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
         xp[z] = T(0);
     }
     int cur = 0;
-    const int at = ex + E * (ey + E * ez0);
-    const int oxm = ex > 0 ? -1 : 0, oxp = ex < E - 1 ? 1 : 0, oym = ey > 0 ? -E : 0, oyp = ey < E - 1 ? E : 0;
-    const int ozm = ez0 > 0 ? -E * E : 0, ozp = ez0 + ZS < E ? E * E : 0;
+    const int at = ex + EX * ey + EL * ez0;
+    const int oxm = ex > 0 ? -1 : 0, oxp = ex < EX - 1 ? 1 : 0, oym = ey > 0 ? -EX : 0, oyp = ey < EY - 1 ? EX : 0;
+    const int ozm = ez0 > 0 ? -EL : 0, ozp = ez0 + ZS < EZ ? EL : 0;
     auto publish = [&]() {
 #pragma unroll
-        for (int z = 0; z < ZS; ++z) xs[cur][at + E * E * z] = xv[z];
+        for (int z = 0; z < ZS; ++z) xs[cur][at + EL * z] = xv[z];
         __syncthreads();
     };
     // neighbours of the thread's node z (at the region's faces stand-ins whose results are not used)
     auto nbrs = [&](int z, T N[6]) {
-        const T *p = xs[cur] + at + E * E * z;
+        const T *p = xs[cur] + at + EL * z;
         N[NMX] = p[oxm];
         N[NPX] = p[oxp];
         N[NMY] = p[oym];
@@ -313,8 +325,8 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
     if constexpr (FACES || FACTORS) {
 #pragma unroll
         for (int z = 0; z < ZS; ++z) {
-            xs[1][at + E * E * z] = xf[z];
-            if constexpr (FACTORS) xe[at + E * E * z] = di1[z];
+            xs[1][at + EL * z] = xf[z];
+            if constexpr (FACTORS) xe[at + EL * z] = di1[z];
         }
     }
     publish();
@@ -329,7 +341,7 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
         for (int z = 0; z < ZS; ++z) {
             T N[6], d[6];
             nbrs(z, N);
-            const T *f = xs[1] + at + E * E * z;
+            const T *f = xs[1] + at + EL * z;
             if constexpr (FACES) {
                 if (s == 0) {
                     if (lx == 0) N[NMX] = f[oxm];
@@ -342,9 +354,9 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
             for (int e = 0; e < 6; ++e) d[e] = xv[z] - N[e];
             if constexpr (FACTORS) {
                 if (s == 0) {
-                    const int lz = (ez0 + z - H) & (SEG - 1);
-                    const int om = z > 0 ? -E * E : ozm, op = z < ZS - 1 ? E * E : ozp;
-                    const T *g = xe + at + E * E * z;
+                    const int lz = (ez0 + z + rz) & (SEG - 1);
+                    const int om = z > 0 ? -EL : ozm, op = z < ZS - 1 ? EL : ozp;
+                    const T *g = xe + at + EL * z;
                     if (lz == 0) d[NMZ] = scaled ? fmadd(-A.c0, f[om], xv[z]) : fmadd(-f[om], g[om], xv[z]);
                     if (lz == SEG - 1) d[NPZ] = scaled ? fmadd(-A.c0, f[op], xv[z]) : fmadd(-f[op], g[op], xv[z]);
                 }
@@ -372,17 +384,17 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
     T *xo = A.xout + vo;
 #pragma unroll
     for (int z = 0; z < ZS; ++z)
-        if (act && halo_depth<H>(ez0 + z) == 0) xo[n[z]] = xv[z];
+        if (act && depth_z(ez0 + z) == 0) xo[n[z]] = xv[z];
     if constexpr (UP) {
-        if constexpr (FINE) {
+        if constexpr (FINE && G::PARTS == 1) {
             if (!A.part) return;
             // z.b of the own nodes, summed as the column kernels' waves do: lane = node column, the nodes of a
             // segment in order, then the wave's sum; one partial per segment (4 of them to a group)
             T *xd = xs[cur], *bd = xs[cur] + BS;   // (nobody reads this buffer any more)
 #pragma unroll
             for (int z = 0; z < ZS; ++z)
-                if (own_xy && halo_depth<H>(ez0 + z) == 0) {
-                    const int l = lx + 8 * ly + 64 * (ez0 + z - H);
+                if (own_xy && depth_z(ez0 + z) == 0) {
+                    const int l = lx + 8 * ly + 64 * (ez0 + z + rz);
                     xd[l] = act ? xv[z] : T(0);
                     bd[l] = act ? bz[z] : T(0);
                 }
@@ -407,14 +419,14 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
     for (int z = 0; z < ZS; ++z) {
         T N[6];
         nbrs(z, N);
-        if (own_xy && halo_depth<H>(ez0 + z) == 0) {
+        if (own_xy && depth_z(ez0 + z) == 0) {
             T d[6];
             const T x0 = scaled ? xv[z] - bv[z] : xv[z];
 #pragma unroll
             for (int e = 0; e < 6; ++e) d[e] = x0 - N[e];
             const T y = apply(d, W[z]);
             const T r = scaled ? -y : bv[z] - y;
-            rs[lx + 8 * ly + 64 * (ez0 + z - H)] = act ? r : T(0);
+            rs[lx + 8 * ly + 64 * (ez0 + z + rz)] = act ? r : T(0);
         }
     }
     __syncthreads();
@@ -428,7 +440,7 @@ __global__ __launch_bounds__(BrickGeom<H>::NTH) void k_brick_leg(BrickLeg<T> A)
         sum = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
         rn = rp;
     } else {
-        const T *q = rs + 2 * (t & 3) + 16 * ((t >> 2) & 3) + 128 * (t >> 4);
+        const T *q = rs + 2 * cx + 16 * cy + 128 * cz;
         const T a00 = q[0] + q[64], a10 = q[1] + q[65], a01 = q[8] + q[72], a11 = q[9] + q[73];
         sum = (a00 + a10) + (a01 + a11);
     }
@@ -456,15 +468,36 @@ hipError_t launch_nbr27(const int *slot_of, const int4 *coord, int nb, const int
     return hipGetLastError();
 }
 
+// Up to this many bricks (times right sides) a brick is dealt to eight workgroups, an eighth (4x4x4 nodes) each: the
+// regions are 1.7 to 6.8 times smaller than the brick's own (H = 4: 1,728 nodes for 4,096; H = 2: 512 for 1,728), and
+// 384 workgroups still run at once.  Solves, whole bricks -> eighths on the levels named: 31^3 (48 and 8 bricks) 591
+// -> 545 us, 64x48x56 (25) 728 -> 685, 96x80x120 (30) 837 -> 759; with 66 bricks (131x97x203) 1,210 -> 1,344 us, with
+// 80 (128x96x256) 1,041 -> 1,198.  Quarters (8x4x4) there: 1,210 -> 1,242 in FP64, 1,053 -> 1,010 in FP32.  In FP64
+// the H = 4 region keeps a compute unit busy by itself, so there one workgroup per unit: with 36 bricks (56^3) FP64
+// takes 589 -> 627 us, FP32 559 -> 533.
+template <typename T, int H>
+constexpr long long leg_eighths_most() { return sizeof(T) == 8 && H == 4 ? 32 : 48; }
+
+template <typename T, int H, int BX, int BY, int BZ, int OPK, bool FINE, bool CELL>
+static hipError_t leg_parts(const BrickLeg<T> &A, int up, int n, hipStream_t s)
+{
+    using G = BrickGeom<H, BX, BY, BZ>;
+    const dim3 grid(xcd_grid(A.nb * G::PARTS), n), block(G::NTH);
+    if (up)
+        SPFD_LAUNCH((k_brick_leg<T, H, BX, BY, BZ, OPK, FINE, true, CELL>), grid, block, 0, s, A);
+    else
+        SPFD_LAUNCH((k_brick_leg<T, H, BX, BY, BZ, OPK, FINE, false, CELL>), grid, block, 0, s, A);
+    return hipGetLastError();
+}
+
 template <typename T, int H, int OPK, bool FINE, bool CELL>
 static hipError_t leg(const BrickLeg<T> &A, int up, int n, hipStream_t s)
 {
-    const dim3 grid(xcd_grid(A.nb), n), block(BrickGeom<H>::NTH);
-    if (up)
-        SPFD_LAUNCH((k_brick_leg<T, H, OPK, FINE, true, CELL>), grid, block, 0, s, A);
-    else
-        SPFD_LAUNCH((k_brick_leg<T, H, OPK, FINE, false, CELL>), grid, block, 0, s, A);
-    return hipGetLastError();
+    // (the partial sums run over the columns of a whole brick)
+    const bool whole = FINE && up && A.part;
+    if (!whole && (long long)A.nb * n <= leg_eighths_most<T, H>())
+        return leg_parts<T, H, 4, 4, 4, OPK, FINE, CELL>(A, up, n, s);
+    return leg_parts<T, H, 8, 8, 8, OPK, FINE, CELL>(A, up, n, s);
 }
 
 template <typename T>

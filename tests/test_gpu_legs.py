@@ -47,3 +47,28 @@ def test_legs_equal_separate_kernels(opts, prec):
     s.close()
     assert info["status"] == "OK" and infos[1]["iterations"] == info["iterations"]
     assert torch.equal(one, many[1])
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("opts", [{}, {"voxel": True}, {"level1_degree": 2}, {"coarsest_max": 48}, {"level1_fp32": True},
+                                  {"smoother": "chebyshev4", "split_level": 1, "coarsest_max": 48}], ids=str)
+def test_eighths_equal_whole_bricks(opts, prec):
+    """A source alone on few bricks (levels dealt out in eighths of bricks) and in a batch of three (whole bricks on
+    the larger levels) or of 48 (on all of them): the same bits."""
+    print(f"case leg eighths {opts} {prec}", flush=True)
+    opts = dict(opts)
+    voxel = opts.pop("voxel", False)
+    w = W.random_ellipsoid_phantom(31, 29, 37, seed=11, n_ell=6, semi_range=(4.0, 9.0))
+    sig = _dev(w.sigma_voxel() * np.random.default_rng(3).uniform(0.8, 1.2, w.labels.shape)) if voxel else w.sigma_table
+    s = P.Solver(_dev(w.labels), sig, w.h, precision=prec, **opts)
+    bricks = [s_["slots"] // 512 for s_ in (P.spfd_level_info(s.handle, k) for k in range(s.info()["n_levels"]))
+              if s_["kind"] == "structured"]
+    assert bricks[0] > 16 and bricks[1] <= 48, bricks
+    a = _dev(w.a)
+    one, info = s.solve((a * 1.01).contiguous(), tol=1e-10, max_iter=300)
+    for n in (3, 48):
+        many, infos = s.solve(torch.stack([a * (1.0 + 0.01 * k) for k in range(n)]), tol=1e-10, max_iter=300)
+        assert infos[1]["iterations"] == info["iterations"]
+        assert torch.equal(one, many[1])
+    s.close()
+    assert info["status"] == "OK"
