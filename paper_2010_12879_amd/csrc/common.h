@@ -206,6 +206,23 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
     return s;
 }
 
+// number of set flags in the threads before this one, and in *total those of all 1024 threads (count: 16 ints in LDS)
+__device__ __forceinline__ int flags_before(bool flag, int *count, int *total)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(flag);
+    __syncthreads();
+    if (lane == 0) count[wv] = __popcll(m);
+    __syncthreads();
+    int before = __popcll(m & ((1ull << lane) - 1ull)), all = 0;
+    for (int k = 0; k < 16; ++k) {
+        if (k < wv) before += count[k];
+        all += count[k];
+    }
+    *total = all;
+    return before;
+}
+
 // the scalars into host memory; with a stamp (> 0) the host may poll for them: it sees the stamp after the rest
 __device__ __forceinline__ void store_mirror(Scal *mirror, const Scal *sc, int stamp, int row = 0)
 {

@@ -780,18 +780,16 @@ hipError_t launch_comp_counts(const int *comp, long long n, int *counts, hipStre
 // ---------------------------------------------------------------- coarsest level
 // Enumerate the unknowns (D > 0) of the coarsest level in node order, one
 // workgroup; adj[dof][6] = neighbour unknowns or -1.
-__global__ void k_coarse_enum(const double *__restrict__ w, long long stride, Topo topo, int *dof_of_node,
+__global__ __launch_bounds__(1024) void k_coarse_enum(const double *__restrict__ w, long long stride, Topo topo, int *dof_of_node,
                               int *node_of_dof, int *adj, int *ndof, int maxdof)
 {
-    __shared__ int s[1024];
-    __shared__ int carry;
+    __shared__ int count[16];
     const int t = threadIdx.x;
     const long long n = (long long)topo.nb * BS;
-    if (t == 0) carry = 0;
-    __syncthreads();
+    int carry = 0;
     for (long long base = 0; base < n; base += 1024) {
         const long long i = base + t;
-        int isdof = 0;
+        bool isdof = false;
         if (i < n) {
             const int b = (int)(i / BS), tt = (int)(i % BS);
             int tx, ty, tz;
@@ -802,22 +800,13 @@ __global__ void k_coarse_enum(const double *__restrict__ w, long long stride, To
             stored_weights(w, stride, (long long)b * BS, tt, I, W);
             isdof = diag_of(W) > 0.0;
         }
-        s[t] = isdof;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const int add = t >= d ? s[t - d] : 0;
-            __syncthreads();
-            s[t] += add;
-            __syncthreads();
-        }
-        const int id = carry + s[t] - isdof;
+        int total;
+        const int id = carry + flags_before(isdof, count, &total);
         if (i < n) {
             dof_of_node[i] = isdof ? id : -1;
             if (isdof && id < maxdof) node_of_dof[id] = (int)i;
         }
-        __syncthreads();
-        if (t == 1023) carry += s[t];
-        __syncthreads();
+        carry += total;
     }
     if (t == 0) *ndof = carry;
     __syncthreads();
@@ -936,9 +925,10 @@ __global__ __launch_bounds__(256) void k_creg_pattern(int n, const double *__res
     if (lane == 0) w.deg[q] = d;
 }
 
-// One thread per unknown (n <= 1024), labels in LDS, the row's first CREG_NB neighbours in registers: a round of
-// the propagation is a few LDS reads (labels and neighbours in global memory, and one thread adding up the
-// diagonals, took 103 us on 641 unknowns; this form 52 us).
+// One thread per unknown (n <= 1024): union-find in LDS over the row's neighbours, the first CREG_NB of them in
+// registers; the smallest unknown labels its component.  (641 unknowns: rounds of minimum labels in global memory, and
+// one thread adding up the diagonals, 103 us; the rounds in LDS, and a read under the comparison, 50
+// us; this form 25 us.)
 constexpr int CREG_NB = 16;
 
 __global__ __launch_bounds__(1024) void k_creg_components(int n, const double *__restrict__ A, int *work)
@@ -946,7 +936,6 @@ __global__ __launch_bounds__(1024) void k_creg_components(int n, const double *_
     const CoarseWork w = coarse_work(n, work);
     const int q = threadIdx.x;
     const bool in = q < n;
-    __shared__ int changed;
     __shared__ int label[1024], size[1024];
     __shared__ double sdiag[1024];
     int nb[CREG_NB];
@@ -956,39 +945,23 @@ __global__ __launch_bounds__(1024) void k_creg_components(int n, const double *_
     sdiag[q] = in ? A[(long long)q * n + q] : 0.0;
     label[q] = q;
     size[q] = 0;
-    auto get = [&](int m) { return __hip_atomic_load(label + m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
-    // minimum label over each component: neighbour minima plus pointer jumping
-    do {
-        __syncthreads();
-        if (q == 0) changed = 0;
-        __syncthreads();
-        if (in) {
-            const int c0 = get(q);
-            int c = c0;
-#pragma unroll
-            for (int k = 0; k < CREG_NB; ++k) {
-                const int cm = get(nb[k]);
-                c = cm < c ? cm : c;
-            }
-            for (int k = CREG_NB; k < d; ++k) {
-                const int cm = get(w.adj[(long long)q * CMAXADJ + k]);
-                c = cm < c ? cm : c;
-            }
-            if (d < 0)
-                for (int m = 0; m < n; ++m)
-                    if (m != q && A[(long long)q * n + m] != 0.0) {
-                        const int cm = get(m);
-                        c = cm < c ? cm : c;
-                    }
-            const int cc = get(c);
-            c = cc < c ? cc : c;
-            if (c < c0) {
-                __hip_atomic_store(label + q, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                changed = 1;
-            }
+    __syncthreads();
+    if (in) {
+        for (int k = 0; k < CREG_NB; ++k)
+            if (nb[k] > q) lunite(label, q, nb[k]);
+        for (int k = CREG_NB; k < d; ++k) {
+            const int m = w.adj[(long long)q * CMAXADJ + k];
+            if (m > q) lunite(label, q, m);
         }
-        __syncthreads();
-    } while (changed);
+        if (d < 0)   // (its neighbours of smaller index may have it in a list or not)
+            for (int m = 0; m < n; ++m)
+                if (m != q && A[(long long)q * n + m] != 0.0) lunite(label, q, m);
+    }
+    __syncthreads();
+    const int root = in ? lfind(label, q) : q;
+    __syncthreads();
+    label[q] = root;
+    __syncthreads();
     if (in) {
         w.comp[q] = label[q];
         atomicAdd(size + label[q], 1);
@@ -999,8 +972,17 @@ __global__ __launch_bounds__(1024) void k_creg_components(int n, const double *_
     // diagonal sum of each component, in the order of the unknowns, by the unknown that gives it its label
     double sum = 0.0;
     if (label[q] == q) {
-#pragma unroll 16
-        for (int m = 0; m < n; ++m) sum += label[m] == q ? sdiag[m] : 0.0;
+        for (int m0 = 0; m0 < 1024 && m0 < n; m0 += 16) {   // (labels from n on are their own)
+            double v[16];
+            int l[16];
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {   // all read before any is used: a read under the comparison waits for it
+                v[m] = sdiag[m0 + m];
+                l[m] = label[m0 + m];
+            }
+#pragma unroll
+            for (int m = 0; m < 16; ++m) sum += l[m] == q ? v[m] : 0.0;
+        }
     }
     w.cdiag[q] = sum;
 }

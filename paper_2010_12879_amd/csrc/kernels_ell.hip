@@ -990,39 +990,26 @@ SPFD_INST_ELL(float)
 
 // ---------------------------------------------------------------- coarsest level given as ELL
 // unknowns = rows with D > 0, in row order; adjacency among them
-__global__ void k_coarse_enum_ell(int n, int K, const int *__restrict__ col, const double *__restrict__ val,
+__global__ __launch_bounds__(1024) void k_coarse_enum_ell(int n, int K, const int *__restrict__ col, const double *__restrict__ val,
                                   int *dof_of_row, int *row_of_dof, int *ndof, int maxdof)
 {
-    __shared__ int s[1024];
-    __shared__ int carry;
+    __shared__ int count[16];
     const int t = threadIdx.x;
-    if (t == 0) carry = 0;
-    __syncthreads();
+    int carry = 0;
     for (int base = 0; base < n; base += 1024) {
         const int i = base + t;
-        int isdof = 0;
-        if (i < n) {
-            double d = 0.0;
+        double d = 0.0;
+        if (i < n)
             for (int k = 0; k < K; ++k)
                 if (col[(long long)k * n + i] >= 0) d += val[(long long)k * n + i];
-            isdof = d > 0.0;
-        }
-        s[t] = isdof;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const int add = t >= d ? s[t - d] : 0;
-            __syncthreads();
-            s[t] += add;
-            __syncthreads();
-        }
-        const int id = carry + s[t] - isdof;
+        const bool isdof = d > 0.0;
+        int total;
+        const int id = carry + flags_before(isdof, count, &total);
         if (i < n) {
             dof_of_row[i] = isdof ? id : -1;
             if (isdof && id < maxdof) row_of_dof[id] = i;
         }
-        __syncthreads();
-        if (t == 1023) carry += s[t];
-        __syncthreads();
+        carry += total;
     }
     if (t == 0) *ndof = carry;
 }
