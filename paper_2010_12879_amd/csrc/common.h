@@ -44,9 +44,12 @@ struct Scal {
 
 constexpr int MAX_MODELS = 16;     // voxel models packed into one handle
 
+// ints per brick's record; in it, where the brick's table of conductivities starts (packed models: each its own)
+constexpr int NBR = 8, NTAB = 6;
+
 struct Topo {
     int nb;                                    // active bricks
-    const int *nbr;                            // [nb*6]
+    const int *nbr;                            // [nb*NBR]: the six neighbours' slots (-1: absent), then NTAB
     const unsigned long long *cmask = nullptr; // [nb]: bit tx + 8 ty set when the node column (tx,ty,*)
                                                // holds an unknown (nullptr: all columns)
     // np > 0: the bricks of np voxel models packed into one level; launch row blockIdx.y = m works on
@@ -140,7 +143,7 @@ __device__ __forceinline__ void stored_weights(const T *__restrict__ w, long lon
 // the six neighbour slots of a brick (uniform across the workgroup: scalar loads)
 __device__ __forceinline__ void brick_nbrs(const int *nbr, int b, int nb[6])
 {
-    const int *p = nbr + b * 6;
+    const int *p = nbr + b * NBR;
 #pragma unroll
     for (int k = 0; k < 6; ++k) nb[k] = p[k];
 }

@@ -96,7 +96,9 @@ struct Ctx {
     long long mnodes_off[MAX_MODELS + 1] = {};   // offsets of the models' dense node arrays in psi
     int mfirst[MAX_MODELS] = {}, mcount[MAX_MODELS] = {};   // the models' finest-level bricks (after build)
     int2 *d_mrange = nullptr;                               // the same on the device (first, count)
-    double *d_mtables = nullptr;                            // [MAX_MODELS][MAX_LABELS] conductivity tables
+    double *d_mtables = nullptr;                            // [MAX_MODELS][MAX_LABELS] conductivity tables (NaN:
+                                                            // not covered), the same with 0 there, and that in FP32
+    bool mlabel = false;        // packed models solve in label form (every model's label 0 is air, as outside its box)
     int nlab = 0;
     double table[MAX_LABELS];
     double *d_table64 = nullptr;
@@ -431,7 +433,7 @@ int build_topology(Ctx *c, std::vector<Level> &levels, uint8_t *flags0, int *d_e
         L.nb = T.nb = c->h_ints[1 + l];
         L.d_slot_of = T.slot_of = dalloc<int>(c, c->hier_allocs, T.cells);
         L.d_coord = T.coord = dalloc<int4>(c, c->hier_allocs, L.nb);
-        L.d_nbr = T.nbr = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * 6);
+        L.d_nbr = T.nbr = dalloc<int>(c, c->hier_allocs, (size_t)L.nb * NBR);
         if (l + 1 < t.n) L.d_parent_slot = T.parent_slot = dalloc<int>(c, c->hier_allocs, L.nb);
     }
     HIPCHK(launch_topo_fill(t, c->stream));
@@ -470,6 +472,9 @@ EllStat ell_stat(Ctx *c, const EllStat *d_stat)
     return a;
 }
 
+// the finest level's operator is stored (else in label form)
+bool stored_fine(const Ctx *c) { return c->voxel_mode && !c->mlabel; }
+
 template <typename T>
 OpArgs<T> level_op(Ctx *c, int l);
 
@@ -480,11 +485,12 @@ OpArgs<double> level_op<double>(Ctx *c, int l)
     const Level &L = c->lv[l];
     op.stride = L.nodes();
     op.short_below = c->opt.short_segment_bricks;
-    if (l == 0 && !c->voxel_mode) {
+    if (l == 0 && !stored_fine(c)) {
         op.w = nullptr;
         op.tiles = L.d_tiles;
-        op.table = c->d_table64;
+        op.table = c->mlabel ? c->d_mtables + MAX_MODELS * MAX_LABELS : c->d_table64;
         op.nlab = c->nlab;
+        op.models = c->mlabel ? L.d_nbr : nullptr;
         for (int d = 0; d < 3; ++d) op.geo4[d] = c->geo4[d];
     } else {
         op.w = L.d_w64;
@@ -499,11 +505,12 @@ OpArgs<float> level_op<float>(Ctx *c, int l)
     const Level &L = c->lv[l];
     op.stride = L.nodes();
     op.short_below = L.seg == 4 ? 0x7fffffff : L.seg == 8 ? 0 : c->opt.short_segment_bricks;
-    if (l == 0 && !c->voxel_mode) {
+    if (l == 0 && !stored_fine(c)) {
         op.w = nullptr;
         op.tiles = L.d_tiles;
-        op.table = c->d_table32;
+        op.table = c->mlabel ? (const float *)(c->d_mtables + 2 * MAX_MODELS * MAX_LABELS) : c->d_table32;
         op.nlab = c->nlab;
+        op.models = c->mlabel ? L.d_nbr : nullptr;
         for (int d = 0; d < 3; ++d) op.geo4[d] = (float)c->geo4[d];
         op.bscale = c->bscale0 ? 1 : 0;
     } else {
@@ -522,7 +529,7 @@ OpArgs<float> level_op<float>(Ctx *c, int l)
 template <typename T>
 double op_bytes(Ctx *c, int l)
 {
-    if (l == 0 && !c->voxel_mode) return 1.0;
+    if (l == 0 && !stored_fine(c)) return 1.0;
     if (sizeof(T) == sizeof(float) && l == 1 && c->lv[1].d_w16) return 3.0 * sizeof(uint16_t);
     return 3.0 * sizeof(T);
 }
@@ -533,7 +540,7 @@ double op_bytes(Ctx *c, int l)
 // of the standard-beta CG.
 bool r32_scaled(const Ctx *c)
 {
-    return c->opt.precision == SPFD_MIXED && !c->voxel_mode && c->lv.size() > 1 && c->lv[0].d_dinv32 != nullptr;
+    return c->opt.precision == SPFD_MIXED && !stored_fine(c) && c->lv.size() > 1 && c->lv[0].d_dinv32 != nullptr;
 }
 
 template <typename T>
@@ -809,6 +816,7 @@ void brick_leg(Ctx *c, int l, bool up, const T *b, const T *xin, T *xout, const 
         A.g = c->g;
         A.table = op.table;
         A.nlab = op.nlab;
+        A.models = op.models;
         for (int d = 0; d < 3; ++d) A.geo4[d] = op.geo4[d];
     }
     A.bscale = op.bscale;
@@ -1039,7 +1047,7 @@ void tune_segments(Ctx *c)
     for (size_t l = 0; l + 1 < c->lv.size(); ++l) {
         Level &L = c->lv[l];
         L.seg = 0;
-        if (L.ell || (l == 0 && !c->voxel_mode) || L.nb <= 0) continue;
+        if (L.ell || (l == 0 && !stored_fine(c)) || L.nb <= 0) continue;
         if (l < c->seg_cache.size() && c->seg_cache[l].first == L.nb) {
             L.seg = c->seg_cache[l].second;
             continue;
@@ -1382,7 +1390,8 @@ spfd_status do_build(Ctx *c)
     const long long n_fine = L0.nodes();
     unsigned long long *emask = dalloc<unsigned long long>(c, c->hier_allocs, (size_t)L0.nb * EMASK);
     L0.d_w64 = dalloc<double>(c, c->hier_allocs, (size_t)3 * n_fine);
-    if (c->voxel_mode)
+    if (c->mlabel) HIPCHK(launch_brick_models(L0.d_coord, L0.nb, c->mbox, L0.d_nbr, c->stream));
+    if (stored_fine(c))
         L0.d_w32 = dalloc<float>(c, c->hier_allocs, (size_t)3 * n_fine);
     else
         L0.d_tiles = dalloc<uint8_t>(c, c->hier_allocs, (size_t)L0.nb * TILE_BYTES);
@@ -2433,6 +2442,7 @@ spfd_status set_geometry(spfd_handle h, int nx, int ny, int nz, double hx, doubl
         h->geo4[2] = 0.25 * (hx * hy / hz);
         h->np = 0;
         h->d_mtables = nullptr;
+        h->mlabel = false;
         h->seg_cache.clear();
         h->d_labels = dalloc<uint8_t>(h, h->geo_allocs, nvox);
         if (labels)
@@ -2581,13 +2591,29 @@ spfd_status spfd_set_sigma_tables(spfd_handle h, const double *const *tables, co
         HIPCHK(hipSetDevice(h->device));
         enter(h);
         const long long nvox = (long long)h->g.nx * h->g.ny * h->g.nz;
-        if (!h->d_mtables) h->d_mtables = dalloc<double>(h, h->geo_allocs, (size_t)MAX_MODELS * MAX_LABELS);
+        // three tables of MAX_MODELS x MAX_LABELS (the last in FP32)
+        const size_t per = (size_t)MAX_MODELS * MAX_LABELS;
+        if (!h->d_mtables) h->d_mtables = dalloc<double>(h, h->geo_allocs, 2 * per + per / 2);
         double *dt = h->d_mtables;
-        HIPCHK(hipMemcpyAsync(dt, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, h->stream));
+        std::vector<double> all(2 * per + per / 2, 0.0);
+        std::vector<float> single(per, 0.0f);
+        bool air = true;
+        for (int m = 0; m < h->np; ++m) {
+            air = air && tab[(size_t)m * MAX_LABELS] == 0.0;
+            for (int l = 0; l < MAX_LABELS; ++l) {
+                const size_t i = (size_t)m * MAX_LABELS + l;
+                all[i] = tab[i];
+                all[per + i] = isfinite(tab[i]) ? tab[i] : 0.0;
+                single[i] = (float)all[per + i];
+            }
+        }
+        memcpy(all.data() + 2 * per, single.data(), per * sizeof(float));
+        HIPCHK(hipMemcpyAsync(dt, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice, h->stream));
         if (!h->d_sigvox) h->d_sigvox = dalloc<double>(h, h->geo_allocs, nvox);
         HIPCHK(launch_pack_sigma(h->d_labels, h->g, h->mbox, dt, h->d_sigvox, h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
         h->voxel_mode = true;
+        h->mlabel = air;   // (label form reads label 0 outside a model's box, where the conductivity is 0)
         h->nlab = MAX_LABELS;
         h->state = 2;
         return SPFD_OK;
@@ -2658,7 +2684,7 @@ spfd_status spfd_level_info(spfd_handle h, int level, int *kind, long long *unkn
             *segment = 0;
         else if (!fp32)
             *segment = 4;
-        else if (level == 0 && !h->voxel_mode)
+        else if (level == 0 && !stored_fine(h))
             *segment = 8;
         else
             *segment = L.seg ? L.seg : (L.nb < h->opt.short_segment_bricks ? 4 : 8);

@@ -46,6 +46,7 @@ struct OpArgs {
     const T *table;          // sigma per label (device)
     int nlab;
     T geo4[3];               // dual area / length / 4 per direction
+    const int *models = nullptr;  // packed models: the bricks' records (NTAB)
     const uint16_t *wh = nullptr;  // FP16 bits of w / whs (first coarse level of an FP32 cycle), read instead of w
     float whs = 0.0f;
     int short_below = 8192;        // stored-weight levels with fewer bricks run 4-node column segments
@@ -83,7 +84,7 @@ struct TopoLevel {
     int nb;                // active bricks (known after the host's wait)
     int *slot_of;          // [cells], -1: not active
     int4 *coord;           // [nb]
-    int *nbr;              // [nb * 6]
+    int *nbr;              // [nb * NBR]
     int *parent_slot;      // [nb]: slot in the next level (null: there is none)
 };
 constexpr int TOPO_WG = 256;
@@ -106,7 +107,7 @@ constexpr int EMASK = 32;   // words per brick: per node layer the edges to +x, 
 struct FinestSetup {
     uint8_t *tiles;   // label form
     double *w64;
-    float *w32;       // conductivity per voxel
+    float *w32;       // stored form
     double *dinv64;   // one of the two
     float *dinv32;
     unsigned long long *cmask, *emask;
@@ -319,6 +320,7 @@ struct BrickLeg {
     Grid g;
     const T *table;
     int nlab;
+    const int *models;
     T geo4[3];
     int bscale;                        // b is held as D^-1 b (finest level)
     // vectors: right side, iterate in and out (different buffers); the finest level's downward leg starts
@@ -352,6 +354,8 @@ struct ModelBoxes {
 };
 hipError_t launch_pack_labels(const uint8_t *src, int nx, int ny, int nz, uint8_t *dst, int NX, int NY, int zoff,
                               hipStream_t s);
+// the bricks' tables: that of the model whose node layers hold the brick's first
+hipError_t launch_brick_models(const int4 *coord, int nb, const ModelBoxes &mb, int *nbr, hipStream_t s);
 hipError_t launch_pack_sigma(const uint8_t *labels, const Grid &g, const ModelBoxes &mb, const double *tables,
                              double *sig, hipStream_t s);
 

@@ -24,7 +24,8 @@ __device__ __forceinline__ void stage_tile(const OpArgs<T> &op, int b, T *tile)
     const int i0 = threadIdx.x, i1 = threadIdx.x + NT;
     const int l0 = tl[i0];
     const int l1 = i1 < TILE_VOX ? tl[i1] : 0;
-    const T s0 = op.table[l0], s1 = op.table[l1];
+    const T *table = op.models ? op.table + op.models[b * NBR + NTAB] : op.table;
+    const T s0 = table[l0], s1 = table[l1];
     tile[i0] = s0;
     if (i1 < TILE_VOX) tile[i1] = s1;
 }
@@ -225,7 +226,8 @@ __global__ __launch_bounds__(TOPO_WG) void k_topo_nbr(TopoLevels t)
                    ? -1
                    : L.slot_of[x + L.G[0] * (y + L.G[1] * z)];
     };
-    int *nbr = L.nbr + (long long)b * 6;
+    int *nbr = L.nbr + (long long)b * NBR;
+    nbr[NTAB] = nbr[NTAB + 1] = 0;
     nbr[NMX] = look(c.x - 1, c.y, c.z);
     nbr[NPX] = look(c.x + 1, c.y, c.z);
     nbr[NMY] = look(c.x, c.y - 1, c.z);
@@ -311,16 +313,12 @@ __global__ __launch_bounds__(NT) void k_finest_setup(const uint8_t *__restrict__
             const int i = c.x * 8 - 1 + idx % 9, j = c.y * 8 - 1 + (idx / 9) % 9, k = c.z * 8 - 1 + idx / 81;
             if (i >= 0 && j >= 0 && k >= 0 && i < g.nx && j < g.ny && k < g.nz) {
                 const long long v = i + (long long)g.nx * (j + (long long)g.ny * k);
-                if (VOX) {
-                    sg = sig_vox[v];
-                } else {
-                    lab = labels[v];
-                    sg = table[lab];
-                }
+                if (!VOX || out.tiles) lab = labels[v];
+                sg = VOX ? sig_vox[v] : table[lab];
             }
             tile[idx] = sg;
         }
-        if (!VOX) out.tiles[(long long)b * TILE_BYTES + idx] = lab;
+        if (!VOX || out.tiles) out.tiles[(long long)b * TILE_BYTES + idx] = lab;
     }
     __syncthreads();
     int tx, ty, tz;
@@ -332,7 +330,7 @@ __global__ __launch_bounds__(NT) void k_finest_setup(const uint8_t *__restrict__
     out.w64[n] = W[NPX];
     out.w64[stride + n] = W[NPY];
     out.w64[2 * stride + n] = W[NPZ];
-    if (VOX) {
+    if (VOX && out.w32) {
         out.w32[n] = (float)W[NPX];
         out.w32[stride + n] = (float)W[NPY];
         out.w32[2 * stride + n] = (float)W[NPZ];
@@ -361,7 +359,7 @@ hipError_t launch_finest_setup(const uint8_t *labels, const double *table, const
                                const double geo4[3], const int4 *coord, int nb, const FinestSetup &out, hipStream_t s)
 {
     if (nb <= 0) return hipSuccess;
-    if (sig_vox ? !out.w32 : !out.tiles) return hipErrorInvalidValue;
+    if (!out.tiles && !(sig_vox && out.w32)) return hipErrorInvalidValue;
     if (sig_vox)
         SPFD_LAUNCH(k_finest_setup<true>, dim3(nb), dim3(NT), 0, s, labels, table, sig_vox, g, geo4[0], geo4[1],
                     geo4[2], coord, (long long)nb * BS, out);
@@ -600,7 +598,7 @@ __global__ __launch_bounds__(256) void k_cc_union(const unsigned long long *__re
     bool edge[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const int nbk = topo.nbr[b * 6 + (d == 0 ? NPX : d == 1 ? NPY : NPZ)];
+        const int nbk = topo.nbr[b * NBR + (d == 0 ? NPX : d == 1 ? NPY : NPZ)];
         // face nodes in the order of their two other axes
         const int t = d == 0 ? 7 + 8 * lo + 64 * hi : d == 1 ? lo + 56 + 64 * hi : lane + 448;
         const unsigned long long word = e[8 * d + (d == 2 ? 7 : hi)];
@@ -796,7 +794,7 @@ __global__ __launch_bounds__(1024) void k_coarse_enum(const double *__restrict__
             brick_xyz(tt, tx, ty, tz);
             double W[6];
             long long I[6];
-            nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * 6, I);
+            nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * NBR, I);
             stored_weights(w, stride, (long long)b * BS, tt, I, W);
             isdof = diag_of(W) > 0.0;
         }
@@ -817,7 +815,7 @@ __global__ __launch_bounds__(1024) void k_coarse_enum(const double *__restrict__
         const int b = i / BS, tt = i % BS;
         int tx, ty, tz;
         brick_xyz(tt, tx, ty, tz);
-        const int *nb = topo.nbr + b * 6;
+        const int *nb = topo.nbr + b * NBR;
         int m[6];
         m[NMX] = tx > 0 ? i - 1 : (nb[NMX] >= 0 ? nb[NMX] * BS + tt + 7 : -1);
         m[NPX] = tx < 7 ? i + 1 : (nb[NPX] >= 0 ? nb[NPX] * BS + tt - 7 : -1);
@@ -854,7 +852,7 @@ __global__ __launch_bounds__(256) void k_coarse_assemble_brick(const double *__r
     brick_xyz(tt, tx, ty, tz);
     double W[6];
     long long I[6];
-    nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * 6, I);
+    nbr_index((long long)b * BS, tt, tx, ty, tz, topo.nbr + b * NBR, I);
     stored_weights(w, stride, (long long)b * BS, tt, I, W);
     int m[6];
     double d = 0.0;
@@ -1632,6 +1630,24 @@ __global__ void k_pack_sigma(const uint8_t *__restrict__ labels, Grid g, ModelBo
                 sv = tables[m * MAX_LABELS + labels[v]];
         sig[v] = sv;
     }
+}
+
+__global__ __launch_bounds__(256) void k_brick_models(const int4 *__restrict__ coord, int nb, ModelBoxes mb,
+                                                      int *__restrict__ nbr)
+{
+    const int b = blockIdx.x * 256 + threadIdx.x;
+    if (b >= nb) return;
+    const int z0 = coord[b].z * BD;
+    int m = 0;
+    while (m + 1 < mb.np && z0 >= mb.zoff[m + 1]) ++m;
+    nbr[b * NBR + NTAB] = m * MAX_LABELS;
+}
+
+hipError_t launch_brick_models(const int4 *coord, int nb, const ModelBoxes &mb, int *nbr, hipStream_t s)
+{
+    if (nb <= 0 || mb.np < 1) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_brick_models, dim3((nb + 255) / 256), dim3(256), 0, s, coord, nb, mb, nbr);
+    return hipGetLastError();
 }
 
 hipError_t launch_pack_sigma(const uint8_t *labels, const Grid &g, const ModelBoxes &mb, const double *tables,

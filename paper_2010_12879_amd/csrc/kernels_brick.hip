@@ -102,8 +102,10 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
         nslot[t] = s;
         if constexpr (!CELL) npar[t] = A.parent_slot[s >= 0 ? s : 0];
     }
-    if constexpr (LABEL)
-        for (int l = t; l < MAX_LABELS; l += NTH) tab[l] = l < A.nlab ? A.table[l] : T(0);
+    if constexpr (LABEL) {
+        const T *table = A.models ? A.table + A.models[b * NBR + NTAB] : A.table;
+        for (int l = t; l < MAX_LABELS; l += NTH) tab[l] = l < A.nlab ? table[l] : T(0);
+    }
     if (stop) return;   // (uniform)
     const long long vo = blockIdx.y * A.vs;
     // the thread's nodes: region column (ex, ey), layers ez0 .. ez0 + ZS - 1

@@ -74,6 +74,7 @@ struct Seg {
     int grp;                                      // brick group of the workgroup (-1: padding)
     int z0, lane, tx, ty;
     int nb[6];                                    // neighbour bricks of bk (-1: absent)
+    int tab;                                      // where bk's conductivity table starts
     long long self;                               // slot of (tx, ty, z0)
     long long xe, ye;                             // lanes with tx = 0 or 7 (ty = 0 or 7): slot of the x (y)
                                                   // neighbour of (tx, ty, z0) in the next brick
@@ -131,6 +132,7 @@ __device__ __forceinline__ Seg<ZPL> make_seg(const Topo &topo, const Scal *sc)
         s.hc = 0;
     }
     brick_nbrs(topo.nbr, bl, s.nb);
+    s.tab = topo.nbr[bl * NBR + NTAB];
     s.active = false;
     if (s.bk < 0) return s;
     // a column without unknowns stores nothing (its slots stay zero) and
@@ -198,8 +200,9 @@ struct SegOp<T, ZPL, true> {
         g[0] = op.geo4[0];
         g[1] = op.geo4[1];
         g[2] = op.geo4[2];
+        const T *table = op.table + s.tab;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) tv[k] = (s.lane + 64 * k < op.nlab) ? op.table[s.lane + 64 * k] : T(0);
+        for (int k = 0; k < 4; ++k) tv[k] = (s.lane + 64 * k < op.nlab) ? table[s.lane + 64 * k] : T(0);
         const uint32_t *tl = (const uint32_t *)(op.tiles + (long long)s.bk * TILE_BYTES + 81 * s.z0);
 #pragma unroll
         for (int k = 0; k < NLD; ++k) lab[k] = (s.lane + 64 * k < NWD) ? tl[s.lane + 64 * k] : 0u;
