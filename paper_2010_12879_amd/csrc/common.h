@@ -52,12 +52,15 @@ struct Topo {
     const int *nbr;                            // [nb*NBR]: the six neighbours' slots (-1: absent), then NTAB
     const unsigned long long *cmask = nullptr; // [nb]: bit tx + 8 ty set when the node column (tx,ty,*)
                                                // holds an unknown (nullptr: all columns)
-    // np > 0: the bricks of np voxel models packed into one level; launch row blockIdx.y = m works on
-    // model m's bricks [prange[m].x, prange[m].x + prange[m].y) (its own scalars and partial sums).
-    // The ranges live in device memory (a uniform load), not in the kernel arguments: an argument
-    // array indexed by blockIdx.y would be copied to scratch memory in every kernel.
+    // np > 0: the bricks of np voxel models packed into one level, model m's being [prange[m].x, prange[m].x +
+    // prange[m].y), with its own scalars and partial sums (row m).  The workgroups of all models follow each other in
+    // one launch dimension, and each finds its model in the ranges (topo_group): a launch row per model, as long as
+    // the largest one's, left most workgroups of uneven models empty.  The ranges live in device memory (uniform
+    // loads; entries up to MAX_MODELS can be read), not in the kernel arguments: an argument array indexed by a row
+    // would be copied to scratch memory in every kernel.
     int np = 0;
     int pmax = 0;                    // largest range
+    int psum = 0;                    // bricks of all ranges
     const int2 *prange = nullptr;    // [np] (first brick, bricks)
 };
 
@@ -74,23 +77,50 @@ __device__ __forceinline__ int xcd_brick(int wg, int nb)
     return b < nb ? b : -1;
 }
 
-__host__ __forceinline__ int xcd_grid(int nb) { return ((nb + 7) >> 3) << 3; }
+__host__ __device__ __forceinline__ int xcd_grid(int nb) { return ((nb + 7) >> 3) << 3; }
 
-// The brick of a one-brick workgroup (-1 for padding) and its index within its
-// launch row (local; the index of its partial sum): with packed models, row
-// blockIdx.y = m covers model m's bricks.
-__device__ __forceinline__ int topo_brick(const Topo &t, int &local)
+// Row, range of bricks and group of `per` bricks within it (-1 for padding) of a workgroup: launch row blockIdx.y
+// works on all bricks, or, with packed models, the workgroups go through the models' groups one after the other
+// (MODELS false: a kernel that is launched without).
+template <bool MODELS = true>
+__device__ __forceinline__ int topo_group(const Topo &t, int per, int &row, int2 &range)
 {
-    if (t.np == 0) {
-        local = xcd_brick(blockIdx.x, t.nb);
-        return local;
+    row = blockIdx.y;
+    range = make_int2(0, t.nb);
+    if (!MODELS || t.np == 0) return xcd_brick(blockIdx.x, (t.nb + per - 1) / per);
+    int groups[MAX_MODELS], total = 0;
+#pragma unroll
+    for (int m = 0; m < MAX_MODELS; ++m) {
+        groups[m] = m < t.np ? (t.prange[m].y + per - 1) / per : 0;
+        total += groups[m];
     }
-    // the map is taken over the launch row's full length (the largest model), so that every brick of
-    // a smaller model has exactly one workgroup; the rest of the row has none
-    const int2 r = t.prange[blockIdx.y];
-    local = xcd_brick(blockIdx.x, t.pmax);
-    if (local >= r.y) local = -1;
-    return local < 0 ? -1 : r.x + local;
+    // (the launch may be a little longer than the groups: topo_grid counts a partial one for every model)
+    int g = (int)blockIdx.x < xcd_grid(total) ? xcd_brick(blockIdx.x, total) : -1;
+    row = 0;
+    if (g >= 0) {
+#pragma unroll
+        for (int m = 0; m + 1 < MAX_MODELS; ++m)
+            if (row == m && g >= groups[m]) {
+                g -= groups[m];
+                row = m + 1;
+            }
+    }
+    range = t.prange[row];
+    return g;
+}
+
+// launch grid of such workgroups (n launch rows unless models are packed)
+__host__ __forceinline__ dim3 topo_grid(const Topo &t, int per, int n)
+{
+    return t.np ? dim3(xcd_grid((t.psum + per - 1) / per + t.np), 1) : dim3(xcd_grid((t.nb + per - 1) / per), n);
+}
+
+// the brick of a one-brick workgroup (-1 for padding), its row and its index there (local, that of its partial sum)
+__device__ __forceinline__ int topo_brick(const Topo &t, int &local, int &row)
+{
+    int2 range;
+    local = topo_group(t, 1, row, range);
+    return local < 0 ? -1 : range.x + local;
 }
 
 __device__ __forceinline__ void brick_xyz(int t, int &tx, int &ty, int &tz)

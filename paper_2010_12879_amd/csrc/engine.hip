@@ -966,7 +966,10 @@ Topo cg_topo(Ctx *c)
     if (c->np) {
         t.np = c->np;
         t.prange = c->d_mrange;
-        for (int m = 0; m < c->np; ++m) t.pmax = std::max(t.pmax, c->mcount[m]);
+        for (int m = 0; m < c->np; ++m) {
+            t.pmax = std::max(t.pmax, c->mcount[m]);
+            t.psum += c->mcount[m];
+        }
     }
     return t;
 }
@@ -1533,7 +1536,7 @@ spfd_status model_ranges(Ctx *c)
         if (c->mcount[k] == 0) return fail(c, SPFD_INVALID_ARG, "a voxel model has no conducting voxel");
     int2 rg[MAX_MODELS];
     for (int k = 0; k < c->np; ++k) rg[k] = make_int2(c->mfirst[k], c->mcount[k]);
-    c->d_mrange = dalloc<int2>(c, c->hier_allocs, MAX_MODELS);
+    c->d_mrange = dalloc<int2>(c, c->hier_allocs, 2 * MAX_MODELS);   // (read up to MAX_MODELS from any model's entry)
     HIPCHK(hipMemcpyAsync(c->d_mrange, rg, c->np * sizeof(int2), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     return SPFD_OK;
@@ -2721,7 +2724,7 @@ spfd_status spfd_set_source(spfd_handle h, int rhs, const double *a)
             Topo t = L0.topo();
             t.np = 1;
             t.prange = h->d_mrange + rhs;
-            t.pmax = h->mcount[rhs];
+            t.pmax = t.psum = h->mcount[rhs];
             double *part = h->d_part + (long long)rhs * h->pstride;
             {
                 TScope ts(h, SPFD_K_RHS, (double)t.pmax * BS * (24.0 + 8.0 + op_bytes<double>(h, 0)));

@@ -1216,8 +1216,8 @@ __global__ __launch_bounds__(NT) void k_rhs(OpArgs<double> op, Topo topo, const 
 {
     __shared__ double tile[TILE_VOX + 7];
     __shared__ double red[8];
-    int loc;
-    const int bk = topo_brick(topo, loc);
+    int loc, row;
+    const int bk = topo_brick(topo, loc, row);
     if (bk < 0) return;
     int nb[6];
     brick_nbrs(topo.nbr, bk, nb);
@@ -1251,7 +1251,7 @@ hipError_t launch_rhs(const OpArgs<double> &op, Topo topo, const int4 *coord, co
 {
     if (topo.nb <= 0) return hipSuccess;
     if (topo.np > 1) return hipErrorInvalidValue;   // one model per call
-    const dim3 grid(xcd_grid(topo_count(topo)));
+    const dim3 grid = topo_grid(topo, 1, 1);
     if (op.w)
         SPFD_LAUNCH(k_rhs<false>, grid, dim3(NT), 0, s, op, topo, coord, g, zoff, a, b, part);
     else
@@ -1268,16 +1268,16 @@ __global__ __launch_bounds__(NT) void k_x_flush(Topo topo, double *__restrict__ 
                                                 long long hs, const double *__restrict__ ahist, int nh, long long vs,
                                                 const Scal *sc)
 {
-    int loc;
-    const int bk = topo_brick(topo, loc);
+    int loc, row;
+    const int bk = topo_brick(topo, loc, row);
     if (bk < 0) return;
-    const double *ah = ahist + (long long)blockIdx.y * nh;
-    const int m = min(sc[blockIdx.y].hcount, nh);
-    const int lo = max(sc[blockIdx.y].happlied, 0);
+    const double *ah = ahist + (long long)row * nh;
+    const int m = min(sc[row].hcount, nh);
+    const int lo = max(sc[row].happlied, 0);
     if (m <= lo) return;
     // a node column without unknowns holds zeros in x and every p: nothing to read or write
     if (topo.cmask && !((topo.cmask[bk] >> (threadIdx.x & 63)) & 1ull)) return;
-    const long long n = blockIdx.y * vs + (long long)bk * BS + threadIdx.x;
+    const long long n = row * vs + (long long)bk * BS + threadIdx.x;
     // every direction's load in flight (fully unrolled, wave-uniform conditions: no indexed private
     // array), then the updates in step order
     double a[MAX_PHIST];
@@ -1317,7 +1317,7 @@ hipError_t launch_x_flush(Topo topo, double *x, const TP *ph, long long hs, cons
 {
     if (topo.nb <= 0 || bt.n <= 0) return hipSuccess;
     if (nh < 2 || nh > MAX_PHIST || !ph || !ahist || !sc) return hipErrorInvalidValue;
-    SPFD_LAUNCH(k_x_flush<TP>, dim3(xcd_grid(topo_count(topo)), bt.n), dim3(NT), 0, s, topo, x, ph, hs, ahist, nh,
+    SPFD_LAUNCH(k_x_flush<TP>, topo_grid(topo, 1, bt.n), dim3(NT), 0, s, topo, x, ph, hs, ahist, nh,
                 bt.vs, sc);
     SPFD_LAUNCH(k_hist_reset, dim3((bt.n + 63) / 64), dim3(64), 0, s, sc, bt.n, full);
     return hipGetLastError();
@@ -1333,14 +1333,13 @@ __global__ __launch_bounds__(NT) void k_rupdate(Topo topo, double *__restrict__ 
                                                 float *__restrict__ r32, double *ahist, int nh)
 {
     __shared__ double red[8];
-    sc += blockIdx.y;
-    // the step size of this search direction (window slot hcount), for the update of x at the window's end
-    if (blockIdx.x == 0 && threadIdx.x == 0 && sc->done == 0 && sc->hcount < nh)
-        ahist[blockIdx.y * nh + sc->hcount] = sc->alpha;
-    int loc;
-    const int bk = topo_brick(topo, loc);
+    int loc, row;
+    const int bk = topo_brick(topo, loc, row);
     if (bk < 0) return;
-    const long long n = blockIdx.y * vs + (long long)bk * BS + threadIdx.x;
+    sc += row;
+    // the step size of this search direction (window slot hcount), for the update of x at the window's end
+    if (loc == 0 && threadIdx.x == 0 && sc->done == 0 && sc->hcount < nh) ahist[row * nh + sc->hcount] = sc->alpha;
+    const long long n = row * vs + (long long)bk * BS + threadIdx.x;
     // The loads do not wait for the stop flag (a test before them would cost one more memory round
     // trip): a stopped right side loads, but stores nothing.
     const double rv = r[n], qv = q[n];
@@ -1351,7 +1350,7 @@ __global__ __launch_bounds__(NT) void k_rupdate(Topo topo, double *__restrict__ 
         if (r32) r32[n] = (float)rn;
     }
     const double tot = block_sum(run ? rn * rn : 0.0, red);
-    if (threadIdx.x == 0 && run) part[(long long)blockIdx.y * ps + loc] = tot;
+    if (threadIdx.x == 0 && run) part[(long long)row * ps + loc] = tot;
 }
 
 hipError_t launch_rupdate(Topo topo, double *r, const double *q, double *part, Scal *sc, const Batch &bt, float *r32,
@@ -1359,7 +1358,7 @@ hipError_t launch_rupdate(Topo topo, double *r, const double *q, double *part, S
 {
     if (topo.nb <= 0) return hipSuccess;
     if (!ahist || nh < 2 || nh > MAX_PHIST) return hipErrorInvalidValue;
-    SPFD_LAUNCH(k_rupdate, dim3(xcd_grid(topo_count(topo)), bt.n), dim3(NT), 0, s, topo, r, q, part, sc, bt.vs,
+    SPFD_LAUNCH(k_rupdate, topo_grid(topo, 1, bt.n), dim3(NT), 0, s, topo, r, q, part, sc, bt.vs,
                 bt.ps, r32, ahist, nh);
     return hipGetLastError();
 }
@@ -1371,15 +1370,15 @@ __global__ __launch_bounds__(NT) void k_dots(Topo topo, const TZ *__restrict__ z
                                              long long vs, int ps)
 {
     __shared__ double red[8];
-    sc += blockIdx.y;
-    if (sc->done) return;
-    int loc;
-    const int bk = topo_brick(topo, loc);
+    int loc, row;
+    const int bk = topo_brick(topo, loc, row);
     if (bk < 0) return;
-    z += blockIdx.y * vs;
-    r += blockIdx.y * vs;
-    q += blockIdx.y * vs;
-    part += (long long)blockIdx.y * ps;
+    sc += row;
+    if (sc->done) return;
+    z += row * vs;
+    r += row * vs;
+    q += row * vs;
+    part += (long long)row * ps;
     const long long n = (long long)bk * BS + threadIdx.x;
     const double zv = (double)z[n];
     const double a = block_sum(zv * r[n], red);
@@ -1396,7 +1395,7 @@ hipError_t launch_dots(Topo topo, const TZ *z, const double *r, const double *q,
                        const Batch &bt, hipStream_t s)
 {
     if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_dots<TZ>, dim3(xcd_grid(topo_count(topo)), bt.n), dim3(NT), 0, s, topo, z, r, q, part, sc, first,
+    SPFD_LAUNCH(k_dots<TZ>, topo_grid(topo, 1, bt.n), dim3(NT), 0, s, topo, z, r, q, part, sc, first,
                 bt.vs, bt.ps);
     return hipGetLastError();
 }
@@ -1409,13 +1408,13 @@ template <typename TZ>
 __global__ __launch_bounds__(NT) void k_pupdate(Topo topo, const TZ *__restrict__ z, double *__restrict__ p,
                                                 const Scal *sc, int first, long long vs)
 {
-    sc += blockIdx.y;
-    if (sc->done) return;
-    int loc;
-    const int bk = topo_brick(topo, loc);
+    int loc, row;
+    const int bk = topo_brick(topo, loc, row);
     if (bk < 0) return;
-    z += blockIdx.y * vs;
-    p += blockIdx.y * vs;
+    sc += row;
+    if (sc->done) return;
+    z += row * vs;
+    p += row * vs;
     const long long n = (long long)bk * BS + threadIdx.x;
     const double zv = (double)z[n];
     p[n] = first ? zv : zv + sc->beta * p[n];
@@ -1426,7 +1425,7 @@ hipError_t launch_pupdate(Topo topo, const TZ *z, double *p, const Scal *sc, int
                           hipStream_t s)
 {
     if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_pupdate<TZ>, dim3(xcd_grid(topo_count(topo)), bt.n), dim3(NT), 0, s, topo, z, p, sc, first, bt.vs);
+    SPFD_LAUNCH(k_pupdate<TZ>, topo_grid(topo, 1, bt.n), dim3(NT), 0, s, topo, z, p, sc, first, bt.vs);
     return hipGetLastError();
 }
 template hipError_t launch_pupdate<double>(Topo, const double *, double *, const Scal *, int, const Batch &,

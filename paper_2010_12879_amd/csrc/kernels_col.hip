@@ -71,7 +71,8 @@ struct Seg {
     static constexpr int WPB = 8 / ZPL;           // waves per brick
     static constexpr int BPG = CWAVES / WPB;      // bricks per workgroup
     int bk;                                       // brick (-1: this wave has none)
-    int grp;                                      // brick group of the workgroup (-1: padding)
+    int grp;                                      // brick group of the workgroup in its row (-1: padding)
+    int row;                                      // right side or packed model
     int z0, lane, tx, ty;
     int nb[6];                                    // neighbour bricks of bk (-1: absent)
     int tab;                                      // where bk's conductivity table starts
@@ -92,7 +93,7 @@ __host__ __device__ __forceinline__ int col_ngroups(int nb)
     return (nb + Seg<ZPL>::BPG - 1) / Seg<ZPL>::BPG;
 }
 
-// (with packed models, launch row blockIdx.y = m covers model m's bricks; grp
+// (with packed models, row m is model m and covers its bricks; grp
 // is the group's index within the row, the index of its partial sum)
 //
 // The uniform records a wave needs before its first vector load (the brick's
@@ -104,17 +105,14 @@ __host__ __device__ __forceinline__ int col_ngroups(int nb)
 // short kernels.  So the column mask and the scalars are required (launches
 // that never stop pass zeroed scalars).  The stop flag is written only by an
 // earlier kernel of the stream, so a plain load sees it.
-template <int ZPL, bool FLAG = true>
+template <int ZPL, bool FLAG = true, bool MODELS = false>
 __device__ __forceinline__ Seg<ZPL> make_seg(const Topo &topo, const Scal *sc)
 {
     Seg<ZPL> s;
-    const int2 rg = topo.np ? topo.prange[blockIdx.y] : make_int2(0, topo.nb);
+    int2 rg;
+    s.grp = topo_group<MODELS>(topo, Seg<ZPL>::BPG, s.row, rg);
     const int cnt = rg.y, first = rg.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the map covers the launch row's full length (with packed models, the largest model's groups), so
-    // that each group of a smaller model has exactly one workgroup
-    s.grp = xcd_brick(blockIdx.x, col_ngroups<ZPL>(topo_count(topo)));
-    if (s.grp >= col_ngroups<ZPL>(cnt)) s.grp = -1;
     s.lane = threadIdx.x & 63;
     s.tx = s.lane & 7;
     s.ty = s.lane >> 3;
@@ -125,8 +123,8 @@ __device__ __forceinline__ Seg<ZPL> make_seg(const Topo &topo, const Scal *sc)
     const unsigned long long cm = topo.cmask[bl];
     if constexpr (FLAG) {
         // (adjacent fields of the row's scalars: loaded together)
-        s.stop = sc[blockIdx.y].done != 0;
-        s.hc = sc[blockIdx.y].hcount;
+        s.stop = sc[s.row].done != 0;
+        s.hc = sc[s.row].hcount;
     } else {
         s.stop = false;
         s.hc = 0;
@@ -836,14 +834,14 @@ template <int NC>
 struct RowSum {
     double v[NC];
 
-    __device__ __forceinline__ void load(const FinIn &fin, const Topo &topo, int zpl)
+    __device__ __forceinline__ void load(const FinIn &fin, const Topo &topo, int zpl, int row)
     {
         int n = fin.n;
         if (fin.rows) {   // packed models: the row's own bricks, or groups of the CG step
-            const int cnt = topo.prange[blockIdx.y].y, per = CWAVES * zpl / 8;
+            const int cnt = topo.prange[row].y, per = CWAVES * zpl / 8;
             n = fin.rows == 1 ? cnt : (cnt + per - 1) / per;
         }
-        const double *part = fin.part + (long long)blockIdx.y * fin.ps;
+        const double *part = fin.part + (long long)row * fin.ps;
         const int lane = threadIdx.x & 63;
         if (fin.quads) {   // (FIN_QUADS sums at most)
 #pragma unroll
@@ -888,20 +886,20 @@ __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Top
     constexpr bool WIDE = std::is_same<TZ, double>::value;
     double *lds = col_lds<double, ZPL, LABEL>();
     __shared__ double red[CWAVES];
-    const Seg<ZPL> s = make_seg<ZPL>(topo, sc);
-    sc += blockIdx.y;
+    const Seg<ZPL> s = make_seg<ZPL, true, true>(topo, sc);
+    sc += s.row;
     // a stopped right side (batched solves, a step queued past the stop) returns before its loads; a full
     // window (not reached: the host updates x first) stores nothing
     if (s.grp < 0 || s.stop || s.hc < 0 || s.hc >= nh) return;
-    zv += blockIdx.y * vs;
-    const TZ *__restrict__ pin = ph + (long long)(s.hc == 0 ? nh - 1 : s.hc - 1) * hs + blockIdx.y * vs;
-    TZ *__restrict__ pout = ph + (long long)s.hc * hs + blockIdx.y * vs;
-    if (q) q += blockIdx.y * vs;
-    part += (long long)blockIdx.y * ps;
+    zv += s.row * vs;
+    const TZ *__restrict__ pin = ph + (long long)(s.hc == 0 ? nh - 1 : s.hc - 1) * hs + s.row * vs;
+    TZ *__restrict__ pout = ph + (long long)s.hc * hs + s.row * vs;
+    if (q) q += s.row * vs;
+    part += (long long)s.row * ps;
     RowSum<FIN> rs;
     double rz = 0.0;
     if constexpr (FIN > 0) {
-        rs.load(fin, topo, ZPL);
+        rs.load(fin, topo, ZPL, s.row);
         rz = sc->rz;
     }
     double dot = 0.0;
@@ -916,7 +914,7 @@ __global__ __launch_bounds__(CTHREADS) void k_col_cg_step(OpArgs<double> op, Top
         if constexpr (FIN > 0) {
             const double rzn = rs.total(), beta64 = rzn / rz;
             const bool bad = !(rzn > 0.0) || !isfinite(beta64);
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (s.grp == 0 && threadIdx.x == 0) {
                 if (bad) {
                     sc->status = 6;
                     sc->done = 1;
@@ -989,24 +987,24 @@ __global__ __launch_bounds__(CTHREADS) void k_col_rupdate(OpArgs<double> op, Top
     constexpr bool WIDE = std::is_same<TZ, double>::value;
     double *lds = col_lds<double, ZPL, LABEL>();
     __shared__ double red[CWAVES];
-    const Seg<ZPL> s = make_seg<ZPL>(topo, sc);
+    const Seg<ZPL> s = make_seg<ZPL, true, true>(topo, sc);
     if (s.stop || s.hc < 0 || s.hc >= nh) return;
     double alpha = 0.0, rz = 0.0;
     RowSum<FIN> rs;
-    Scal *row = sc + blockIdx.y;
+    Scal *row = sc + s.row;
     if constexpr (FIN > 0) {
         if (s.grp < 0) return;
-        rs.load(fin, topo, ZPL);
+        rs.load(fin, topo, ZPL, s.row);
         rz = rz_next ? row->rzn : row->rz;
     } else {
         alpha = row->alpha;
     }
     // the step size of this search direction, for the update of x at the end of the window
-    if (FIN == 0 && blockIdx.x == 0 && threadIdx.x == 0) ahist[blockIdx.y * nh + s.hc] = alpha;
+    if (FIN == 0 && s.grp == 0 && threadIdx.x == 0) ahist[s.row * nh + s.hc] = alpha;
     if (s.grp < 0) return;
-    const TZ *__restrict__ pv = ph + (long long)s.hc * hs + blockIdx.y * vs;
-    r += blockIdx.y * vs;
-    if (r32) r32 += blockIdx.y * vs;
+    const TZ *__restrict__ pv = ph + (long long)s.hc * hs + s.row * vs;
+    r += s.row * vs;
+    if (r32) r32 += s.row * vs;
     double rr = 0.0;
     if (s.bk >= 0) {
         SegOp<double, ZPL, LABEL> A;
@@ -1023,12 +1021,12 @@ __global__ __launch_bounds__(CTHREADS) void k_col_rupdate(OpArgs<double> op, Top
             const double pq = rs.total();
             alpha = rz / pq;
             const bool bad = !(pq > 0.0) || !isfinite(alpha);
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
+            if (s.grp == 0 && threadIdx.x == 0) {
                 if (bad) {
                     row->status = 6;
                     row->done = 1;
                 } else {
-                    ahist[blockIdx.y * nh + s.hc] = alpha;
+                    ahist[s.row * nh + s.hc] = alpha;
                 }
                 row->pq = pq;
                 row->alpha = bad ? 0.0 : alpha;
@@ -1066,7 +1064,7 @@ __global__ __launch_bounds__(CTHREADS) void k_col_rupdate(OpArgs<double> op, Top
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < CWAVES; ++w) t += red[w];
-        part[(long long)blockIdx.y * ps + s.grp] = t;
+        part[(long long)s.row * ps + s.grp] = t;
     }
 }
 
@@ -1081,13 +1079,13 @@ __global__ __launch_bounds__(CTHREADS) void k_col_resid(OpArgs<double> op, Topo 
 {
     double *lds = col_lds<double, ZPL, LABEL>();
     __shared__ double red[CWAVES];
-    const Seg<ZPL> s = make_seg<ZPL, false>(topo, nullptr);
+    const Seg<ZPL> s = make_seg<ZPL, false, true>(topo, nullptr);
     if (s.grp < 0) return;
     double rr = 0.0;
     if (s.bk >= 0) {
-        b += blockIdx.y * bvs;
-        x += blockIdx.y * vs;
-        if (r) r += blockIdx.y * vs;
+        b += s.row * bvs;
+        x += s.row * vs;
+        if (r) r += s.row * vs;
         SegOp<double, ZPL, LABEL> A;
         A.load(op, s, lds);
         SegVals<double, ZPL> X;
@@ -1115,7 +1113,7 @@ __global__ __launch_bounds__(CTHREADS) void k_col_resid(OpArgs<double> op, Topo 
         double t = 0.0;
 #pragma unroll
         for (int w = 0; w < CWAVES; ++w) t += red[w];
-        part[(long long)blockIdx.y * ps + s.grp] = t;
+        part[(long long)s.row * ps + s.grp] = t;
     }
 }
 
@@ -1170,9 +1168,9 @@ static bool col_args_ok(const Topo &topo, const Scal *sc, bool need_sc = true)
 }
 
 template <int ZPL>
-static dim3 col_grid(int nb, int nbatch)
+static dim3 col_grid(const Topo &topo, int nbatch)
 {
-    return dim3(xcd_grid(col_ngroups<ZPL>(nb)), nbatch);
+    return topo_grid(topo, Seg<ZPL>::BPG, nbatch);
 }
 
 // Coarser structured levels (stored weights) with few bricks (op.short_below,
@@ -1186,7 +1184,7 @@ template <typename T, typename TB, int ZPL, bool LABEL>
 static void cheb_first_z(const OpArgs<T> &op, Topo topo, const TB *b, T *x, T c0, const Scal *sc, const Batch &bt,
                          hipStream_t s)
 {
-    SPFD_LAUNCH((k_col_cheb_first<T, TB, ZPL, LABEL>), col_grid<ZPL>(topo_count(topo), bt.n), dim3(CTHREADS), 0, s, op, topo,
+    SPFD_LAUNCH((k_col_cheb_first<T, TB, ZPL, LABEL>), col_grid<ZPL>(topo, bt.n), dim3(CTHREADS), 0, s, op, topo,
                 b, x, c0, sc, bt.vs);
 }
 
@@ -1214,7 +1212,7 @@ hipError_t launch_cheb_first2(const OpArgs<T> &op, Topo topo, const TB *b, const
     if (!col_args_ok(topo, sc)) return hipErrorInvalidValue;
     if (!dinv && !op.bscale) return hipErrorInvalidValue;
     constexpr int Z = zpl_cycle<T>();
-    const dim3 g = col_grid<Z>(topo_count(topo), bt.n);
+    const dim3 g = col_grid<Z>(topo, bt.n);
 #define SPFD_F2(LB, SB) SPFD_LAUNCH((k_col_cheb_first2<T, TB, Z, LB, SB>), g, dim3(CTHREADS), 0, s, op, topo, b, dinv, \
                                     xout, dout, c0, c1, c2, sc, bt.vs)
     if (op.w) {
@@ -1234,7 +1232,7 @@ static void cheb_step_z(const OpArgs<T> &op, Topo topo, const TB *b, const T *xi
                         int dmode)
 {
     dt.nparts = col_ngroups<ZPL>(topo_count(topo));
-    SPFD_LAUNCH((k_col_cheb_step<T, TB, ZPL, LAB, PRO, DOT>), col_grid<ZPL>(topo_count(topo), bt.n), dim3(CTHREADS), 0, s, op,
+    SPFD_LAUNCH((k_col_cheb_step<T, TB, ZPL, LAB, PRO, DOT>), col_grid<ZPL>(topo, bt.n), dim3(CTHREADS), 0, s, op,
                 topo, b, xin, xout, din, dout, c1, c2, sc, bt.vs, pr, dt, dmode);
 }
 
@@ -1295,10 +1293,10 @@ static void resid_restrict_z(const OpArgs<T> &op, Topo topo, const TB *b, const 
                              const T *dinv_c, T c0)
 {
     if (op.bscale)
-        SPFD_LAUNCH((k_col_resid_restrict<T, TB, ZPL, LABEL, true>), col_grid<ZPL>(topo_count(topo), bt.n),
+        SPFD_LAUNCH((k_col_resid_restrict<T, TB, ZPL, LABEL, true>), col_grid<ZPL>(topo, bt.n),
                     dim3(CTHREADS), 0, s, op, topo, b, x, bc, parent_slot, fcoord, sc, bt.vs, bt.vsc, xc, dinv_c, c0);
     else
-        SPFD_LAUNCH((k_col_resid_restrict<T, TB, ZPL, LABEL, false>), col_grid<ZPL>(topo_count(topo), bt.n),
+        SPFD_LAUNCH((k_col_resid_restrict<T, TB, ZPL, LABEL, false>), col_grid<ZPL>(topo, bt.n),
                     dim3(CTHREADS), 0, s, op, topo, b, x, bc, parent_slot, fcoord, sc, bt.vs, bt.vsc, xc, dinv_c, c0);
 }
 
@@ -1327,7 +1325,7 @@ hipError_t launch_cg_step(const OpArgs<double> &op, Topo topo, const TZ *z, TZ *
     if (topo.nb <= 0) return hipSuccess;
     if (!col_args_ok(topo, sc)) return hipErrorInvalidValue;
     if (!ph || nh < 2 || nh > MAX_PHIST) return hipErrorInvalidValue;
-    const dim3 g = col_grid<ZPL_CG>(topo_count(topo), bt.n);
+    const dim3 g = col_grid<ZPL_CG>(topo, bt.n);
     if (fin.n > FIN_SMALL || (fin.quads && fin.n > FIN_QUADS) || (fin.n > 0 && (first || q || fin.part == part)))
         return hipErrorInvalidValue;
 #define SPFD_CG(LB, F, FN) SPFD_LAUNCH((k_col_cg_step<TZ, ZPL_CG, LB, F, FN>), g, dim3(CTHREADS), 0, s, op, topo, z, \
@@ -1355,7 +1353,7 @@ hipError_t launch_col_rupdate(const OpArgs<double> &op, Topo topo, const TZ *ph,
     if (r32_scaled && !r32) return hipErrorInvalidValue;
     if (!ph || !ahist || nh < 2 || nh > MAX_PHIST) return hipErrorInvalidValue;
     if (fin.n > FIN_SMALL || fin.quads || (fin.n > 0 && fin.part == part)) return hipErrorInvalidValue;
-    const dim3 g = col_grid<ZPL_RU>(topo_count(topo), bt.n);
+    const dim3 g = col_grid<ZPL_RU>(topo, bt.n);
 #define SPFD_RU(LB, FN) SPFD_LAUNCH((k_col_rupdate<TZ, ZPL_RU, LB, FN>), g, dim3(CTHREADS), 0, s, op, topo, ph, hs, nh, \
                                     r, r32, part, sc, bt.vs, bt.ps, r32_scaled, ahist, fin, rz_next)
     if (op.w) {
@@ -1380,7 +1378,7 @@ hipError_t launch_resid(const OpArgs<double> &op, Topo topo, const double *b, co
 {
     if (topo.nb <= 0) return hipSuccess;
     if (!col_args_ok(topo, nullptr, false)) return hipErrorInvalidValue;
-    const dim3 g = col_grid<ZPL_CG>(topo_count(topo), bt.n);
+    const dim3 g = col_grid<ZPL_CG>(topo, bt.n);
     if (op.w)
         SPFD_LAUNCH((k_col_resid<ZPL_CG, false>), g, dim3(CTHREADS), 0, s, op, topo, b, x, r, part, bvs, bt.vs, bt.ps);
     else
@@ -1394,7 +1392,7 @@ hipError_t launch_spmv(const OpArgs<double> &op, Topo topo, const TZ *z, double 
 {
     if (topo.nb <= 0) return hipSuccess;
     if (!col_args_ok(topo, sc)) return hipErrorInvalidValue;
-    const dim3 g = col_grid<ZPL_CG>(topo_count(topo), bt.n);
+    const dim3 g = col_grid<ZPL_CG>(topo, bt.n);
     if (op.w)
         SPFD_LAUNCH((k_col_spmv<TZ, ZPL_CG, false>), g, dim3(CTHREADS), 0, s, op, topo, z, w, sc, bt.vs);
     else
