@@ -223,6 +223,29 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// Wave sums of NV values a lane at once (NV a power of two up to 32): lane l returns that of row l / (64 / NV).  Each
+// step over half the distance also halves the rows a lane keeps (lanes l and l ^ off keep one half each), so 16 rows
+// take 17 cross-lane adds instead of 96, in the order of wave_sum.
+template <int NV>
+__device__ __forceinline__ double wave_rows(double (&acc)[NV])
+{
+    const int lane = threadIdx.x & 63;
+    int off = 32;
+#pragma unroll
+    for (int m = NV / 2; m > 0; m /= 2, off /= 2) {
+        const long long up = lane & off ? -1LL : 0LL;   // (a mask: a choice of elements becomes a search by index)
+#pragma unroll
+        for (int i = 0; i < m; ++i) {
+            const long long lo = __double_as_longlong(acc[i]), hi = __double_as_longlong(acc[i + m]);
+            const double give = __longlong_as_double((lo & up) | (hi & ~up));
+            const double keep = __longlong_as_double((hi & up) | (lo & ~up));
+            acc[i] = keep + __shfl_xor(give, off, 64);
+        }
+    }
+    for (; off > 0; off >>= 1) acc[0] += __shfl_xor(acc[0], off, 64);
+    return acc[0];
+}
+
 // sum over a 512-thread block, valid in thread 0; lds needs 8 doubles
 __device__ __forceinline__ double block_sum(double v, double *lds)
 {

@@ -31,29 +31,16 @@ __device__ __forceinline__ double block_reduce(double v, double *lds)
     return s;
 }
 
-// partials of NV rows at once: row i of the workgroup into part[i*gridDim.x + blockIdx.x], i < nv.  Each step of a
-// wave's sums over half the distance also halves the rows a lane keeps (lanes l and l ^ off keep one half each), so
-// 16 rows take 17 cross-lane adds instead of 96, in the order of wave_sum.  (205 k slots, 9 to 13 rows: k_mdot 14.0 ->
-// 6.5 us, k_mupdate, whose coefficients were also loaded one by one, 14.2 -> 7.4 us.)
+// partials of NV rows at once: row i of the workgroup into part[i*gridDim.x + blockIdx.x], i < nv.  (205 k slots, 9 to
+// 13 rows: k_mdot 14.0 -> 6.5 us with wave_rows, k_mupdate, whose coefficients were also loaded one by one, 14.2 -> 7.4
+// us.)
 template <int NV>
 __device__ __forceinline__ void rows_reduce(double (&acc)[NV], int nv, double *__restrict__ part)
 {
     __shared__ double lds[NV][KT / 64];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int off = 32;
-#pragma unroll
-    for (int m = NV / 2; m > 0; m /= 2, off /= 2) {
-        const long long up = lane & off ? -1LL : 0LL;   // (a mask: a choice of elements becomes a search by index)
-#pragma unroll
-        for (int i = 0; i < m; ++i) {
-            const long long lo = __double_as_longlong(acc[i]), hi = __double_as_longlong(acc[i + m]);
-            const double give = __longlong_as_double((lo & up) | (hi & ~up));
-            const double keep = __longlong_as_double((hi & up) | (lo & ~up));
-            acc[i] = keep + __shfl_xor(give, off, 64);
-        }
-    }
-    for (; off > 0; off >>= 1) acc[0] += __shfl_xor(acc[0], off, 64);
-    if (lane % (64 / NV) == 0) lds[lane / (64 / NV)][wv] = acc[0];
+    const double sum = wave_rows<NV>(acc);
+    if (lane % (64 / NV) == 0) lds[lane / (64 / NV)][wv] = sum;
     __syncthreads();
     if (threadIdx.x < nv) {
         double t = 0.0;
