@@ -93,6 +93,7 @@ struct Ctx {
     int np = 0;
     ModelBoxes mbox{};
     Grid mgrid[MAX_MODELS];
+    ModelOut *d_mout = nullptr;                  // the same for the output kernel
     long long mnodes_off[MAX_MODELS + 1] = {};   // offsets of the models' dense node arrays in psi
     int mfirst[MAX_MODELS] = {}, mcount[MAX_MODELS] = {};   // the models' finest-level bricks (after build)
     int2 *d_mrange = nullptr;                               // the same on the device (first, count)
@@ -1538,6 +1539,11 @@ spfd_status model_ranges(Ctx *c)
     for (int k = 0; k < c->np; ++k) rg[k] = make_int2(c->mfirst[k], c->mcount[k]);
     c->d_mrange = dalloc<int2>(c, c->hier_allocs, 2 * MAX_MODELS);   // (read up to MAX_MODELS from any model's entry)
     HIPCHK(hipMemcpyAsync(c->d_mrange, rg, c->np * sizeof(int2), hipMemcpyHostToDevice, c->stream));
+    ModelOut out[MAX_MODELS];
+    for (int k = 0; k < c->np; ++k)
+        out[k] = ModelOut{c->mgrid[k].Nx, c->mgrid[k].Ny, c->mgrid[k].Nz, c->mbox.zoff[k], c->mnodes_off[k]};
+    c->d_mout = dalloc<ModelOut>(c, c->hier_allocs, MAX_MODELS);
+    HIPCHK(hipMemcpyAsync(c->d_mout, out, c->np * sizeof(ModelOut), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     return SPFD_OK;
 }
@@ -2143,18 +2149,17 @@ spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, int nb
             TScope ts(c, SPFD_K_GAUGE, (double)L0.dofs * 24.0 + c->mnodes_off[c->np] * 8.0);
             HIPCHK(launch_comp_mean(topo, c->d_x, c->d_comp, c->ncomp, c->d_counts, c->d_means, c->d_cpart, c->stream));
         }
-        for (int i = 0; i < nb; ++i) {
-            if (c->np) {
-                HIPCHK(launch_psi_out(c->d_x, c->d_comp, c->d_means, L0.d_slot_of, c->mgrid[i], psi + c->mnodes_off[i],
-                                      c->stream, &c->g, c->mbox.zoff[i]));
-            } else {
-                TScope ts(c, SPFD_K_GAUGE,
-                          (double)L0.dofs * (12.0 * (c->ncomp < 16 ? c->ncomp : 1) + 12.0) + nn * 8.0);
-                HIPCHK(launch_comp_mean(topo, c->d_x + i * n0, c->d_comp, c->ncomp, c->d_counts, c->d_means,
-                                        c->d_cpart, c->stream));
-                HIPCHK(launch_psi_out(c->d_x + i * n0, c->d_comp, c->d_means, L0.d_slot_of, c->g, psi + i * nn,
-                                      c->stream));
-            }
+        if (c->np) {
+            int most = 0;
+            for (int m = 0; m < c->np; ++m) most = std::max(most, psi_groups(c->mgrid[m].Ny, c->mgrid[m].Nz));
+            HIPCHK(launch_psi_out(c->d_x, c->d_comp, c->d_means, L0.d_slot_of, c->g, psi, c->stream, c->d_mout, c->np,
+                                  most));
+        }
+        for (int i = 0; i < nb && !c->np; ++i) {
+            TScope ts(c, SPFD_K_GAUGE, (double)L0.dofs * (12.0 * (c->ncomp < 16 ? c->ncomp : 1) + 12.0) + nn * 8.0);
+            HIPCHK(launch_comp_mean(topo, c->d_x + i * n0, c->d_comp, c->ncomp, c->d_counts, c->d_means, c->d_cpart,
+                                    c->stream));
+            HIPCHK(launch_psi_out(c->d_x + i * n0, c->d_comp, c->d_means, L0.d_slot_of, c->g, psi + i * nn, c->stream));
         }
     };
     for (int pass = 0; pass < 3 && any; ++pass) {

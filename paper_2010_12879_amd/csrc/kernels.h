@@ -366,8 +366,16 @@ hipError_t launch_comp_mean(Topo topo, const double *x, const int *comp, int nco
                             double *means, double *part, hipStream_t s);
 // gbricks (nullable): the grid of the brick layout when it is not g (packed models; the output's model
 // starts at node layer zoff of it)
+struct ModelOut {
+    int Nx, Ny, Nz;   // nodes of a packed model
+    int zoff;         // its first node layer in the packed grid
+    long long at;     // its place in the output
+};
+// workgroups of an output of Ny x Nz node rows (with models: the most of any of them)
+int psi_groups(int Ny, int Nz);
 hipError_t launch_psi_out(const double *x, const int *comp, const double *means, const int *slot_of, const Grid &g,
-                          double *psi, hipStream_t s, const Grid *gbricks = nullptr, int zoff = 0);
+                          double *psi, hipStream_t s, const ModelOut *models = nullptr, int nmodels = 0,
+                          int groups_most = 0);
 // start of a solve from x = 0 for nvec right sides: x = 0, r = b and r32 = (float)b (r32 may be null;
 // dinv given: r32 = (float)(dinv b), the scaled form an FP32 cycle in label form reads)
 hipError_t launch_start(long long n, const double *b, long long bvs, double *x, double *r, float *r32, int nvec,
