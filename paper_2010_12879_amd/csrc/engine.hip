@@ -2733,8 +2733,8 @@ spfd_status spfd_set_source(spfd_handle h, int rhs, const double *a)
             double *part = h->d_part + (long long)rhs * h->pstride;
             {
                 TScope ts(h, SPFD_K_RHS, (double)t.pmax * BS * (24.0 + 8.0 + op_bytes<double>(h, 0)));
-                HIPCHK(launch_rhs(level_op<double>(h, 0), t, L0.d_coord, h->mgrid[rhs], a, h->d_bs, part,
-                                  h->d_scal + rhs, h->stream, h->mbox.zoff[rhs]));
+                HIPCHK(launch_rhs(level_op<double>(h, 0), t, L0.d_coord, h->mgrid[rhs], a, h->d_bs, part, h->stream,
+                                  h->mbox.zoff[rhs]));
             }
             HIPCHK(launch_finish(part, t.pmax, FIN_BB, h->d_scal + rhs, 0, h->stream, nullptr, nullptr, 0, 1, 0,
                                  h->h_ring_dev, nullptr, 0, stamp));
@@ -2742,7 +2742,7 @@ spfd_status spfd_set_source(spfd_handle h, int rhs, const double *a)
             {
                 TScope ts(h, SPFD_K_RHS, (double)L0.dofs * (24.0 + 8.0 + op_bytes<double>(h, 0)));
                 HIPCHK(launch_rhs(level_op<double>(h, 0), L0.topo(), L0.d_coord, h->g, a, h->d_bs + rhs * L0.nodes(),
-                                  h->d_part, h->d_scal + rhs, h->stream));
+                                  h->d_part, h->stream));
             }
             finish(h, L0.nb, FIN_BB, h->d_scal + rhs, 0, 1, h->h_ring_dev, 0, 0, stamp);
         }

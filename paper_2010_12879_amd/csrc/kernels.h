@@ -175,7 +175,7 @@ hipError_t launch_fill(T *x, long long n, T v, hipStream_t s);
 // b = -G^T M a and the ||b||^2 partials (one per brick of the launch row).  Packed models: topo holds one
 // model (np = 1), g is that model's grid and zoff its first node layer in the packed grid.
 hipError_t launch_rhs(const OpArgs<double> &op, Topo topo, const int4 *coord, const Grid &g, const double *a,
-                      double *b, double *part, Scal *sc, hipStream_t s, int zoff = 0);
+                      double *b, double *part, hipStream_t s, int zoff = 0);
 hipError_t launch_scal_init(Scal *sc, double tol, int use_x0, int nbatch, hipStream_t s);
 // fused CG step: p = z + beta p (p = z when first), x += alpha p_old (deferred), q = A p, p.q partials;
 // pin and pout are different buffers (neighbours read p_old)

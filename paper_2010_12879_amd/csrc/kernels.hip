@@ -1205,60 +1205,6 @@ hipError_t launch_finish(const double *part, int n, int mode, Scal *sc, int max_
     return hipGetLastError();
 }
 
-// b = -G^T M a on the unknowns of the finest level (Eq. (3), right side):
-// b_n = sum over edges leaving n of M_e a_e - sum over edges entering n of M_e a_e,
-// and ||b||^2.  a is read only on conducting edges (M_e > 0), which all lie in the grid.
-// With packed models (topo.np > 0, one launch row): g is the model's grid, zoff its first node layer in
-// the packed grid, and the bricks are the model's.
-template <bool LABEL>
-__global__ __launch_bounds__(NT) void k_rhs(OpArgs<double> op, Topo topo, const int4 *__restrict__ coord, Grid g,
-                                            int zoff, const double *__restrict__ a, double *b, double *part)
-{
-    __shared__ double tile[TILE_VOX + 7];
-    __shared__ double red[8];
-    int loc, row;
-    const int bk = topo_brick(topo, loc, row);
-    if (bk < 0) return;
-    int nb[6];
-    brick_nbrs(topo.nbr, bk, nb);
-    const int t = threadIdx.x;
-    int tx, ty, tz;
-    brick_xyz(t, tx, ty, tz);
-    const long long base = (long long)bk * BS;
-    long long I[6];
-    nbr_index(base, t, tx, ty, tz, nb, I);
-    op_stage(op, bk, tile);
-    double W[6];
-    op_weights(op, tile, base, t, tx, ty, tz, I, W);
-    const int4 c = coord[bk];
-    const long long i = c.x * 8 + tx, j = c.y * 8 + ty, k = c.z * 8 + tz - zoff;
-    const long long n = i + (long long)g.Nx * (j + (long long)g.Ny * k);
-    const long long nn = (long long)g.Nx * g.Ny * g.Nz;
-    double s = 0.0;
-    if (W[NPX] != 0.0) s += W[NPX] * a[n];
-    if (W[NMX] != 0.0) s -= W[NMX] * a[n - 1];
-    if (W[NPY] != 0.0) s += W[NPY] * a[nn + n];
-    if (W[NMY] != 0.0) s -= W[NMY] * a[nn + n - g.Nx];
-    if (W[NPZ] != 0.0) s += W[NPZ] * a[2 * nn + n];
-    if (W[NMZ] != 0.0) s -= W[NMZ] * a[2 * nn + n - (long long)g.Nx * g.Ny];
-    b[base + t] = s;
-    const double tot = block_sum(s * s, red);
-    if (t == 0) part[loc] = tot;
-}
-
-hipError_t launch_rhs(const OpArgs<double> &op, Topo topo, const int4 *coord, const Grid &g, const double *a,
-                      double *b, double *part, Scal *sc, hipStream_t s, int zoff)
-{
-    if (topo.nb <= 0) return hipSuccess;
-    if (topo.np > 1) return hipErrorInvalidValue;   // one model per call
-    const dim3 grid = topo_grid(topo, 1, 1);
-    if (op.w)
-        SPFD_LAUNCH(k_rhs<false>, grid, dim3(NT), 0, s, op, topo, coord, g, zoff, a, b, part);
-    else
-        SPFD_LAUNCH(k_rhs<true>, grid, dim3(NT), 0, s, op, topo, coord, g, zoff, a, b, part);
-    return hipGetLastError();
-}
-
 // x += sum_j alpha_j p_j over the search directions kept in the window and not yet added (slots happlied ..
 // hcount-1, filled in step order), in step order: x receives the same sequence of updates as with one
 // update per step, whatever the window length and whenever the updates happen.  k_hist_reset then starts

@@ -1117,6 +1117,85 @@ __global__ __launch_bounds__(CTHREADS) void k_col_resid(OpArgs<double> op, Topo 
     }
 }
 
+// ---------------------------------------------------------------- right side
+// b = -G^T M a on the unknowns of the finest level (Eq. (3), right side):
+// b_n = sum over edges leaving n of M_e a_e - sum over edges entering n of M_e a_e,
+// and the partials of ||b||^2, one per brick (the layers' wave sums in order).  a counts only on conducting edges
+// (M_e > 0), which all lie in the grid; the other values are loaded where they lie in the array, and not used.
+// With packed models (topo.np = 1): g is the model's grid, zoff its first node layer in the packed grid, and the
+// bricks are the model's.  A wave per brick and a lane per node column: the loads of four layers are in flight
+// together, and a layer's lower z edge is the one above the layer before.  (8.9 M unknowns: 156 us with a node per
+// thread and its loads under the tests of its conductances; this form 108 us, of 70 for the bytes at the copy rate.)
+template <bool LABEL>
+__global__ __launch_bounds__(CTHREADS) void k_col_rhs(OpArgs<double> op, Topo topo, const int4 *__restrict__ coord,
+                                                      Grid g, int zoff, const double *__restrict__ a,
+                                                      double *__restrict__ b, double *__restrict__ part)
+{
+    constexpr int ZPL = 8, H = 4;
+    double *lds = col_lds<double, ZPL, LABEL>();
+    const Seg<ZPL> s = make_seg<ZPL, false, true>(topo, nullptr);
+    if (s.bk < 0) return;
+    SegOp<double, ZPL, LABEL> A;
+    A.load(op, s, lds);
+    const int4 c = coord[s.bk];
+    const int i = c.x * 8 + s.tx, j = c.y * 8 + s.ty, k0 = c.z * 8 - zoff;
+    const long long nl = (long long)g.Nx * g.Ny, nn = nl * g.Nz;
+    const bool col = s.active && i < g.Nx && j < g.Ny;
+    const long long n0 = col ? i + (long long)g.Nx * j : 0;
+    const int dx = col && i > 0 ? 1 : 0, dy = col && j > 0 ? g.Nx : 0;
+    double sq[ZPL], low = 0.0;
+    if (col && k0 > 0 && k0 < g.Nz) low = a[2 * nn + n0 + nl * (k0 - 1)];
+#pragma unroll
+    for (int h = 0; h < ZPL; h += H) {
+        double xp[H], xm[H], yp[H], ym[H], zp[H];
+#pragma unroll
+        for (int z = 0; z < H; ++z) {
+            const int k = k0 + h + z;
+            const bool in = col && k < g.Nz;
+            const long long n = in ? n0 + nl * k : 0;
+            xp[z] = a[n];
+            xm[z] = a[in ? n - dx : 0];
+            yp[z] = a[nn + n];
+            ym[z] = a[in ? nn + n - dy : 0];
+            zp[z] = a[2 * nn + n];
+        }
+        if (h == 0) A.stage(op, s);
+#pragma unroll
+        for (int z = 0; z < H; ++z) {
+            double W[6];
+            A.weights(s, h + z, W);
+            double v = 0.0;
+            if (W[NPX] != 0.0) v += W[NPX] * xp[z];
+            if (W[NMX] != 0.0) v -= W[NMX] * xm[z];
+            if (W[NPY] != 0.0) v += W[NPY] * yp[z];
+            if (W[NMY] != 0.0) v -= W[NMY] * ym[z];
+            if (W[NPZ] != 0.0) v += W[NPZ] * zp[z];
+            if (W[NMZ] != 0.0) v -= W[NMZ] * low;
+            low = zp[z];
+            if (s.active) b[s.self + 64 * (h + z)] = v;   // (a column without unknowns holds zeros)
+            sq[h + z] = s.active ? v * v : 0.0;
+        }
+    }
+    const double t = wave_rows<ZPL>(sq);
+    double tot = 0.0;
+#pragma unroll
+    for (int z = 0; z < ZPL; ++z) tot += __shfl(t, 64 / ZPL * z, 64);
+    if (s.lane == 0) part[s.grp * Seg<ZPL>::BPG + (threadIdx.x >> 6)] = tot;
+}
+
+hipError_t launch_rhs(const OpArgs<double> &op, Topo topo, const int4 *coord, const Grid &g, const double *a,
+                      double *b, double *part, hipStream_t s, int zoff)
+{
+    if (topo.nb <= 0) return hipSuccess;
+    if (topo.np > 1 || !topo.cmask) return hipErrorInvalidValue;   // one model per call
+    const dim3 grid = topo_grid(topo, Seg<8>::BPG, 1);
+    if (op.w)
+        SPFD_LAUNCH(k_col_rhs<false>, grid, dim3(CTHREADS), 0, s, op, topo, coord, g, zoff, a, b, part);
+    else
+        SPFD_LAUNCH(k_col_rhs<true>, grid, dim3(CTHREADS), 0, s, op, topo, coord, g, zoff, a, b, part);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- plain operator application
 // w = A z (FP64 operator, z in the cycle's precision): the Krylov vector of
 // the flexible GMRES outer solver
