@@ -1876,6 +1876,9 @@ void pcg_step_enqueue(Ctx *c, Scal *sc, Scal *hsc, int nb, int it, int max_iter,
 // tolerance within a margin), step it+1 is held back until step it is seen:
 // a wrong guess costs the host's round trip, a right one saves a whole step.
 constexpr double HOLD_MARGIN = 4.0;
+// (solve of the body at 2 mm, 177 MB: 9,504 us with early updates, 9,378 without, four sources 29,090 and 28,718; at
+// 3 mm, 65 MB, 7,149 and 7,145)
+constexpr double EARLY_FLUSH_BYTES = 32e6;
 
 void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
 {
@@ -1889,6 +1892,9 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
         stamp[k & 1] = next_stamp(c);
         pcg_step_enqueue(c, sc, ring[k & 1], nb, k, so.max_iter, true, stamp[k & 1]);
     };
+    // An early update of x costs reading and writing x once more (16 B per slot) where the guess was wrong, an idle
+    // GPU about 8 us: worth it up to about as many bytes
+    const bool early = (double)c->lv[0].nodes() * (c->np ? 1 : nb) * 16.0 <= EARLY_FLUSH_BYTES;
     // ||r||^2 after the last two steps seen by the host (< 0: not seen yet)
     std::vector<double> rr1(nb, -1.0), rr2(nb, -1.0), tol2(nb, 0.0);
     std::vector<int> seen_done(nb, 0);
@@ -1913,7 +1919,7 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
         if (it + 1 <= so.max_iter && !likely_last()) {
             enqueue(it + 1);
             queued = it + 1;
-        } else if (queued == it) {
+        } else if (queued == it && early) {
             // step it+1 is held back: the GPU would idle during the host's poll, so x takes the directions
             // kept so far now (the window goes on: they are only marked as added)
             x_flush(c, sc, nb, (it + 1) % c->phist_len, false);
