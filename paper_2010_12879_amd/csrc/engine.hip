@@ -1578,6 +1578,9 @@ spfd_status do_set_num_rhs(Ctx *c, int nrhs)
         HIPCHK(hipHostMalloc((void **)&c->h_ring, sizeof(Scal) * 2 * (nrhs + 1),
                              hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer((void **)&c->h_ring_dev, c->h_ring, 0));
+        // (fresh pinned memory can hold what an earlier handle left there, stamps that this one will wait for too)
+        memset(c->h_scal, 0, sizeof(Scal) * (nrhs + 1));
+        memset(c->h_ring, 0, sizeof(Scal) * 2 * (nrhs + 1));
         c->h_cap = nrhs;
     }
     c->nrhs = nrhs;
