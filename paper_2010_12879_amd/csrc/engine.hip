@@ -142,6 +142,8 @@ struct Ctx {
     Scal *d_nostop = nullptr;     // zeroed scalars (never stopped) for cycles run outside a CG step
     Scal *step_mirror = nullptr;  // where the CG step being enqueued leaves its scalars
     int step_stamp = 0;           // and the stamp it leaves with them (0: none)
+    bool defer_rr = false;        // the step may leave the sum of ||r||^2 to the next step's first kernel (rr_left)
+    RrIn rr_left;                 // (n > 0: left)
     int stamps = 0;               // stamps given so far
     hipEvent_t ev_it[2] = {nullptr, nullptr};
     // adjoint solve
@@ -848,6 +850,10 @@ void brick_leg(Ctx *c, int l, bool up, const T *b, const T *xin, T *xout, const 
     }
     A.part = part;
     A.ps = bt.ps;
+    if (fine && !up) {
+        A.rr = c->rr_left;
+        c->rr_left = RrIn{};
+    }
     // the leg's vectors once: right side, iterates, operator, the coarser level's vectors
     const double per = (fine && !up ? 2.0 : 3.0) * sizeof(T) + op_bytes<T>(c, l);
     TScope ts(c, fine ? (up ? SPFD_K_DOTS : SPFD_K_SMOOTH0) : SPFD_K_COARSE,
@@ -1713,8 +1719,24 @@ void pcg_step(Ctx *c, Scal *sc, int nb, int it, int max_iter)
             HIPCHK(launch_col_rupdate<T>(op, topo, ph, c->phist_stride, nh, c->d_r, r32, c->d_part, sc, bt, c->stream,
                                          r32 && r32_scaled(c), c->d_ahist, alpha_in, beta_in.n > 0));
         }
-        finish(c, rupdate_parts(nmax), FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_RU_GROUPS, 0, c->step_stamp);
+        // On a level that runs legs the sum of few partials is left to the next step: one more workgroup of its first
+        // leg forms it beside the others, and a launch in the chain of the iteration goes (solves of 31^3 FP64
+        // 548 -> 511 us, 96x80x120 697 -> 647, 128x96x256 mixed 924 -> 907).  The caller settles what no next step takes.
+        const int nrr = rupdate_parts(nmax);
+        if (c->defer_rr && !c->np && nrr <= RR_MOST && leg_level(c, 0, nb))
+            c->rr_left = RrIn{c->d_part, nrr, c->pstride, max_iter, sc, c->step_mirror, c->step_stamp};
+        else
+            finish(c, nrr, FIN_RR, sc, max_iter, nb, c->step_mirror, ROWS_RU_GROUPS, 0, c->step_stamp);
     }
+}
+
+// the sum of ||r||^2 that a step left, where no leg has taken it
+void settle_rr(Ctx *c, int nb)
+{
+    if (c->rr_left.n == 0) return;
+    const RrIn in = c->rr_left;
+    c->rr_left = RrIn{};
+    finish(c, in.n, FIN_RR, in.sc, in.max_iter, nb, in.mirror, ROWS_RU_GROUPS, 0, in.stamp);
 }
 
 // x += sum alpha_j p_j over the steps of the window taken and not yet added; full: then an empty window
@@ -1827,7 +1849,10 @@ void pcg_step_enqueue(Ctx *c, Scal *sc, Scal *hsc, int nb, int it, int max_iter,
         c->step_ctx = timed_sample ? 2 : 1;
         pcg_step_any(c, sc, nb, it, max_iter);
         c->step_ctx = 0;
-        if (flush) x_flush(c, sc, nb, c->phist_len);
+        if (flush) {
+            settle_rr(c, nb);
+            x_flush(c, sc, nb, c->phist_len);
+        }
         return;
     }
     if (c->sg_nb != nb || c->sg_sc != sc || c->sg_max_iter != max_iter || c->sg_flexible != (int)c->cg_flexible) {
@@ -1888,12 +1913,18 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
     Scal *ring[2] = {c->h_ring, c->h_ring + nb};
     int stamp[2] = {0, 0};
     c->cg_flexible = so.flexible != 0;
+    struct RrScope {   // what the last queued step left is not needed, and no other cycle may find it
+        Ctx *c;
+        ~RrScope() { c->rr_left = RrIn{}; c->defer_rr = false; }
+    } rrs{c};
     c->step_ctx = 1;
     pcg_begin_any(c, sc, nb);
     c->step_ctx = 0;
     auto enqueue = [&](int k) {
         stamp[k & 1] = next_stamp(c);
+        c->defer_rr = c->tmask == 0;   // (launch timing counts the finisher)
         pcg_step_enqueue(c, sc, ring[k & 1], nb, k, so.max_iter, true, stamp[k & 1]);
+        c->defer_rr = false;
     };
     // An early update of x costs reading and writing x once more (16 B per slot) where the guess was wrong, an idle
     // GPU about 8 us: worth it up to about as many bytes
@@ -1922,10 +1953,11 @@ void pcg_iterations(Ctx *c, Scal *sc, int nb, const spfd_solve_options &so)
         if (it + 1 <= so.max_iter && !likely_last()) {
             enqueue(it + 1);
             queued = it + 1;
-        } else if (queued == it && early) {
+        } else if (queued == it) {
+            settle_rr(c, nb);
             // step it+1 is held back: the GPU would idle during the host's poll, so x takes the directions
             // kept so far now (the window goes on: they are only marked as added)
-            x_flush(c, sc, nb, (it + 1) % c->phist_len, false);
+            if (early) x_flush(c, sc, nb, (it + 1) % c->phist_len, false);
         }
         wait_stamp(c, ring[it & 1], nb, stamp[it & 1]);
         const Scal *hs = ring[it & 1];

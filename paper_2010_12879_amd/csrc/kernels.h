@@ -304,6 +304,13 @@ hipError_t launch_coarse_apply(const TB *bc, T *xc, const double *Ainv, const in
 // ---------------------------------------------------------------- one leg of the cycle per launch (small levels)
 // Operands of launch_brick_leg, on a structured level of nb bricks (vectors [nrhs][vs], the coarser level's
 // [nrhs][vsc]).
+struct RrIn {
+    const double *part = nullptr;
+    int n = 0, ps = 0, max_iter = 0;   // at most RR_MOST partials per right side
+    Scal *sc = nullptr, *mirror = nullptr;
+    int stamp = 0;
+};
+constexpr int RR_MOST = 256;
 template <typename T>
 struct BrickLeg {
     int nb;
@@ -335,6 +342,9 @@ struct BrickLeg {
     T scale;
     T *bc, *xcout;                     // down: P^T (b - A x); its first iterate c0 dinv_c bc (nullable)
     const T *dinv_c;
+    // down on the finest level (rr.n > 0): ||r||^2 of the CG step before from its partials, as launch_finish in mode
+    // FIN_RR, by one more workgroup per right side beside the leg's
+    RrIn rr;
     // up on the finest level (nullable): partials of x.b per column segment, brick_dot_parts<T>(nb) of them in
     // groups of four, the column kernels' partials
     double *part;

@@ -69,6 +69,37 @@ __device__ __forceinline__ int halo_depth(int e)
 
 enum { BR_LABEL = 0, BR_STORED = 1, BR_HALF = 2 };
 
+// ||r||^2 and the stop test of the step before (k_finish, FIN_RR) for up to RR_MOST partials, one a thread; red: LDS
+__device__ __forceinline__ void finish_rr(const RrIn &in, int row, double *red)
+{
+    const int t = threadIdx.x;
+    const double *part = in.part + (long long)row * in.ps;
+    Scal *sc = in.sc + row;
+    const int stopped = sc->done;
+    double a = t < in.n ? part[t] : 0.0;
+    a = wave_sum(a);
+    if ((t & 63) == 0) red[t >> 6] = a;
+    __syncthreads();
+    if (t != 0) return;
+    if (!stopped) {
+        a = 0.0;
+        for (int w = 0; w < RR_MOST / 64; ++w) a += red[w];
+        sc->rr = a;
+        sc->iters += 1;
+        sc->hcount += 1;   // the step's search direction and step size are kept
+        if (a <= sc->tol2) {
+            sc->done = 1;
+        } else if (!isfinite(a)) {
+            sc->status = 6;
+            sc->done = 1;
+        } else if (sc->iters >= in.max_iter) {
+            sc->status = 5;
+            sc->done = 1;
+        }
+    }
+    store_mirror(in.mirror, sc, in.stamp, row);
+}
+
 // OPK: the operator (label form, stored weights, FP16 weights).  FINE: the finest level (down: the first
 // iterate is c0 D^-1 b, formed here; up: the dot products).  UP: the upward leg.  CELL: the coarser level is
 // an ELL level (member table, aggregate map).
@@ -87,6 +118,14 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
     __shared__ T xs[2][G::EC], xe[FINE && !UP ? G::EC : 1];
     __shared__ T sig[NV], tab[LABEL ? MAX_LABELS : 1];
     __shared__ int nslot[27], npar[27];
+    if constexpr (FINE && !UP) {
+        // The right side may turn out to be done here: the leg's own workgroups do not wait for it (they write
+        // nothing but the cycle's vectors), and the kernels behind see the flag.
+        if (A.rr.n > 0 && blockIdx.x == gridDim.x - 1) {
+            finish_rr(A.rr, blockIdx.y, (double *)xs);
+            return;
+        }
+    }
     const int part = xcd_brick(blockIdx.x, A.nb * G::PARTS);
     if (part < 0) return;
     const int b = part / G::PARTS;
@@ -484,7 +523,8 @@ template <typename T, int H, int BX, int BY, int BZ, int OPK, bool FINE, bool CE
 static hipError_t leg_parts(const BrickLeg<T> &A, int up, int n, hipStream_t s)
 {
     using G = BrickGeom<H, BX, BY, BZ>;
-    const dim3 grid(xcd_grid(A.nb * G::PARTS), n), block(G::NTH);
+    const dim3 grid(xcd_grid(A.nb * G::PARTS) + (!up && A.rr.n > 0 ? 1 : 0), n), block(G::NTH);
+    static_assert(G::NTH >= RR_MOST, "one partial a thread");
     if (up)
         SPFD_LAUNCH((k_brick_leg<T, H, BX, BY, BZ, OPK, FINE, true, CELL>), grid, block, 0, s, A);
     else
@@ -509,7 +549,8 @@ hipError_t launch_brick_leg(const BrickLeg<T> &A, int degree, int fine, int up, 
     if (A.nb <= 0 || nrhs <= 0) return hipSuccess;
     if (!A.nbr27 || !A.cmask || !A.coord || !A.sc || !A.b || !A.xout || (!label && !half && !A.w) ||
         (!cell && !A.parent_slot) || (up ? !A.xin || !A.xc : !A.bc || (cell && !A.memb) || (A.xcout && !A.dinv_c)) ||
-        (fine && !up && !A.bscale && !A.dinv) || (!fine && !A.xin) || (label && !fine))
+        (fine && !up && !A.bscale && !A.dinv) || (!fine && !A.xin) || (label && !fine) ||
+        (A.rr.n > 0 && (A.rr.n > RR_MOST || !fine || up || !A.rr.sc || !A.rr.part)))
         return hipErrorInvalidValue;
     if (fine) {
         if (degree != 2 || cell || half) return hipErrorInvalidValue;

@@ -72,3 +72,25 @@ def test_eighths_equal_whole_bricks(opts, prec):
         assert torch.equal(one, many[1])
     s.close()
     assert info["status"] == "OK"
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("window", [0, 2, 4])
+@pytest.mark.parametrize("max_iter", [1, 2, 3, 6, 300])
+def test_residual_sums_left_to_the_next_leg(max_iter, window, prec):
+    """A source alone (the sum of ||r||^2 formed beside the next step's first leg) and in a batch large enough that
+    the finisher forms it: the same iterations, status and bits, stopped by the limit, by the tolerance, and with x
+    updated every second and fourth step."""
+    print(f"case leg residual sums {max_iter} {window} {prec}", flush=True)
+    w = W.random_ellipsoid_phantom(31, 29, 37, seed=11, n_ell=6, semi_range=(4.0, 9.0))
+    s = P.Solver(_dev(w.labels), w.sigma_table, w.h, precision=prec, cg_window=window)
+    a = _dev(w.a)
+    n = 30
+    assert s.info()["n_levels"] > 1 and n * P.spfd_level_info(s.handle, 0)["slots"] // 512 > MOST
+    one, info = s.solve((a * 1.01).contiguous(), tol=1e-9, max_iter=max_iter, check=False)
+    many, infos = s.solve(torch.stack([a * (1.0 + 0.01 * k) for k in range(n)]), tol=1e-9, max_iter=max_iter,
+                          check=False)
+    s.close()
+    assert info["status"] == infos[1]["status"] == ("OK" if max_iter == 300 else "NOT_CONVERGED")
+    assert info["iterations"] == infos[1]["iterations"] and (max_iter == 300 or info["iterations"] == max_iter)
+    assert info["rel_residual"] == infos[1]["rel_residual"] and torch.equal(one, many[1])
