@@ -254,7 +254,7 @@ def scale_1mm(P, torch, args):
         s = P.Solver(lab, w.sigma_table, w.h, precision=prec)
         torch.cuda.synchronize()
         t_build = time.perf_counter() - t
-        s.solve(a, tol=args.tol)                        # warm-up (graph capture)
+        s.solve(a, tol=args.tol)                        # warm-up
         times = []
         for _ in range(2):
             torch.cuda.synchronize()
@@ -323,7 +323,7 @@ def adjoint_block(w, lab, a, P, torch):
     def J_of(emag):
         return torch.linalg.vector_norm(emag.reshape(-1), ord=8)
 
-    # warm-up of the whole timed block (graph capture; the first torch reduction and power load their kernels)
+    # warm-up of the whole timed block (the first torch reduction and power load their kernels)
     p0, _ = s.solve(a, tol=tol)
     e0 = s.efield(a, p0, w.omega)
     J0 = J_of(e0)
@@ -389,7 +389,7 @@ def batch_phantoms(P, torch, args):
     torch.cuda.synchronize()
     t_build_packed = time.perf_counter() - t
     ms.set_sources(srcs)
-    ms.solve(tol=args.tol)                                 # warm-up (graph capture)
+    ms.solve(tol=args.tol)                                 # warm-up
     packed = []
     for _ in range(3):
         torch.cuda.synchronize()

@@ -262,9 +262,10 @@ spfd_status spfd_stream_triad(int device, void *hip_stream, double *a, const dou
  * previous one, so that no brick of the structured multigrid levels and no
  * aggregate spans two models.  One hierarchy serves all of them: every level
  * kernel runs once over all models (the cycle is block-diagonal), and the
- * finest-level CG kernels run one launch row per model over that model's
- * bricks, with the model's own alpha, beta, residual norms and stop test
- * (so each model's iterates are those of its own preconditioned CG).
+ * finest-level CG kernels run once over the bricks of all models, each
+ * workgroup within one model, with the model's own alpha, beta, residual norms
+ * and stop test (so each model's iterates are those of its own preconditioned
+ * CG).
  * n (1..16) models; dims [n][3] (host): nx, ny, nz voxels of model m; labels
  * [n] (host array of device pointers to uint8 [nz][ny][nx] arrays, copied);
  * h as for spfd_set_geometry.  Then spfd_set_sigma_tables, spfd_build (split
@@ -329,9 +330,9 @@ enum {
 };
 /* Enable timing for the classes in the bit mask (1 << class); resets all
  * counters.  While enabled, the launches of such a class in the second CG
- * iteration of every solve (run from the host, not from the captured graph)
- * are bracketed by two HIP events on the handle's stream: a sample of every
- * solve, at the cost of one eagerly launched iteration.  With
+ * iteration of every solve are bracketed by two HIP events on the handle's
+ * stream: a sample of every solve (spfd_solve_many launches that iteration
+ * from the host instead of replaying its graph).  With
  * SPFD_TIMING_COLD in the mask, a kernel that reads and writes a 1 GiB buffer
  * (four times the Infinity Cache) runs before every timed launch, outside
  * its events, so each sample starts from cold caches; the buffer is held
