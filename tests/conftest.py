@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -11,3 +12,10 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (HIP device) and the built HIP library")
     config.addinivalue_line("markers", "slow: takes more than a few seconds on the CPU")
+
+
+def pytest_runtest_setup(item):
+    # An exception caught by pytest.raises(...) as e keeps its test's tensors alive in a reference cycle until the
+    # cyclic collector happens to run; freed inside a later test, they would falsify its count of device memory.
+    if item.get_closest_marker("gpu"):
+        gc.collect()
