@@ -1737,9 +1737,28 @@ hipError_t launch_psi_in(const double *psi, const int *comp, const int4 *coord, 
 // Columns of FCOL layers: the lanes of a workgroup hold consecutive (i, j) of a layer (contiguous loads and
 // stores, one division per thread, no idle lanes at the row ends), each for FCOL layers of z.  What
 // neighbouring layers share (voxel flags, potentials, edge voltages) is read once, and all loads of a thread
-// are in flight together.
+// are in flight together.  A layer has fewer than 2^32 columns (a grid of two node layers has at most 2^33 - 4 nodes),
+// so a column is counted in 32 bits without a sign; the blocks of layers go along the launch's y dimension, in several
+// launches where they are more than it takes.
 constexpr int FCOL = 4;
 constexpr int FCOL_T = 256;
+constexpr int FCOL_Y = 65535;   // most workgroups along y
+
+// LAUNCH(grid, first block of layers) over the columns of an nx x ny layer and the blocks of nz layers
+template <typename F>
+static hipError_t launch_columns(int nx, int ny, int nz, const F &launch)
+{
+    if (nx <= 0 || ny <= 0 || nz <= 0) return hipSuccess;
+    const unsigned long long cols = (unsigned long long)nx * ny;
+    if (cols > 0xffffffffull) return hipErrorInvalidValue;
+    const int blocks = nz / FCOL + (nz % FCOL != 0);
+    for (int b0 = 0; b0 < blocks; b0 += FCOL_Y) {
+        launch(dim3((unsigned)((cols + FCOL_T - 1) / FCOL_T), (unsigned)(blocks - b0 < FCOL_Y ? blocks - b0 : FCOL_Y)),
+               b0);
+        HIP_RETURN_IF(hipGetLastError());
+    }
+    return hipSuccess;
+}
 
 // cond[l]: label l conducts (all threads of the workgroup call this)
 __device__ __forceinline__ void stage_cond(const double *__restrict__ table, bool per_voxel, unsigned char *cond)
@@ -1789,13 +1808,13 @@ __device__ __forceinline__ unsigned col_cond(const uint8_t *__restrict__ labels,
 __global__ __launch_bounds__(FCOL_T) void k_efield(const uint8_t *__restrict__ labels, const double *__restrict__ table,
                                                    const double *__restrict__ sig_vox, Grid g, double hx, double hy,
                                                    double hz, double omega, const double *__restrict__ a,
-                                                   const double *__restrict__ psi, double *__restrict__ emag)
+                                                   const double *__restrict__ psi, double *__restrict__ emag, int b0)
 {
     __shared__ unsigned char cond[MAX_LABELS];
     stage_cond(table, sig_vox != nullptr, cond);
-    const int e = blockIdx.x * FCOL_T + threadIdx.x;
-    if (e >= g.nx * g.ny) return;
-    const int i = e % g.nx, j = e / g.nx, k0 = blockIdx.y * FCOL;
+    const unsigned e = blockIdx.x * FCOL_T + threadIdx.x;
+    if (e >= (unsigned)g.nx * (unsigned)g.ny) return;
+    const int i = (int)(e % (unsigned)g.nx), j = (int)(e / (unsigned)g.nx), k0 = (b0 + (int)blockIdx.y) * FCOL;
     const int nk = g.nz - k0 < FCOL ? g.nz - k0 : FCOL;
     const long long nn = (long long)g.Nx * g.Ny * g.Nz;
     const long long sy = g.Nx, sz = (long long)g.Nx * g.Ny;
@@ -1850,11 +1869,10 @@ hipError_t launch_efield(const uint8_t *labels, const double *table, const doubl
                          const double h[3], double omega, const double *a, const double *psi, double *emag,
                          hipStream_t s)
 {
-    if (g.nx <= 0 || g.ny <= 0 || g.nz <= 0) return hipSuccess;
-    const long long cols = (long long)g.nx * g.ny;
-    SPFD_LAUNCH(k_efield, dim3((unsigned)((cols + FCOL_T - 1) / FCOL_T), (unsigned)((g.nz + FCOL - 1) / FCOL)),
-                dim3(FCOL_T), 0, s, labels, table, sig_vox, g, h[0], h[1], h[2], omega, a, psi, emag);
-    return hipGetLastError();
+    return launch_columns(g.nx, g.ny, g.nz, [&](dim3 grid, int b0) {
+        SPFD_LAUNCH(k_efield, grid, dim3(FCOL_T), 0, s, labels, table, sig_vox, g, h[0], h[1], h[2], omega, a, psi,
+                    emag, b0);
+    });
 }
 
 // u = a + G psi on conducting edges (any of the four voxels around the edge conducts), 0 elsewhere.  Bound by
@@ -1863,13 +1881,13 @@ hipError_t launch_efield(const uint8_t *labels, const double *table, const doubl
 __global__ __launch_bounds__(FCOL_T) void k_uedges(const uint8_t *__restrict__ labels, const double *__restrict__ table,
                                                    const double *__restrict__ sig_vox, Grid g,
                                                    const double *__restrict__ a, const double *__restrict__ psi,
-                                                   double *__restrict__ u)
+                                                   double *__restrict__ u, int b0)
 {
     __shared__ unsigned char cond[MAX_LABELS];
     stage_cond(table, sig_vox != nullptr, cond);
-    const int e = blockIdx.x * FCOL_T + threadIdx.x;
-    if (e >= g.Nx * g.Ny) return;
-    const int i = e % g.Nx, j = e / g.Nx, k0 = blockIdx.y * FCOL;
+    const unsigned e = blockIdx.x * FCOL_T + threadIdx.x;
+    if (e >= (unsigned)g.Nx * (unsigned)g.Ny) return;
+    const int i = (int)(e % (unsigned)g.Nx), j = (int)(e / (unsigned)g.Nx), k0 = (b0 + (int)blockIdx.y) * FCOL;
     const int nk = g.Nz - k0 < FCOL ? g.Nz - k0 : FCOL;
     const long long nn = (long long)g.Nx * g.Ny * g.Nz;
     const long long sy = g.Nx, sz = (long long)g.Nx * g.Ny;
@@ -1919,11 +1937,9 @@ __global__ __launch_bounds__(FCOL_T) void k_uedges(const uint8_t *__restrict__ l
 hipError_t launch_uedges(const uint8_t *labels, const double *table, const double *sig_vox, const Grid &g,
                          const double *a, const double *psi, double *u, hipStream_t s)
 {
-    if (g.Nx <= 0 || g.Ny <= 0 || g.Nz <= 0) return hipSuccess;
-    const long long cols = (long long)g.Nx * g.Ny;
-    SPFD_LAUNCH(k_uedges, dim3((unsigned)((cols + FCOL_T - 1) / FCOL_T), (unsigned)((g.Nz + FCOL - 1) / FCOL)),
-                dim3(FCOL_T), 0, s, labels, table, sig_vox, g, a, psi, u);
-    return hipGetLastError();
+    return launch_columns(g.Nx, g.Ny, g.Nz, [&](dim3 grid, int b0) {
+        SPFD_LAUNCH(k_uedges, grid, dim3(FCOL_T), 0, s, labels, table, sig_vox, g, a, psi, u, b0);
+    });
 }
 
 }  // namespace spfd
