@@ -66,3 +66,34 @@ def test_split_levels(shape, fill, split_level, prec):
     print("row entries", widths, "iterations", info["iterations"], flush=True)
     assert info["status"] == "OK" and min(widths) == 7 and max(widths) >= 9
     assert np.linalg.norm(psi.cpu().numpy() - ref) <= 1e-7 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("shape", [(7, 9, 16), (3, 11, 31), (4, 16, 16), (5, 5, 41), (20, 13, 4), (8, 8, 64),
+                                   (241, 17, 1), (16, 17, 241)], ids=str)
+def test_voxel_flags_at_wave_remainders(shape):
+    """A wave reads 1,024 conductivities: voxel counts one run of 16 or one voxel below and above that, and just it, on
+    a body with a conductor in its first and last voxels.  A value that is not finite or below 0 is refused wherever it
+    is."""
+    n = int(np.prod(shape))
+    print(f"case voxel flags {shape} {n} = {n // 1024} x 1024 + {n % 1024}", flush=True)
+    rng = np.random.default_rng(n)
+    sig = np.where(rng.random(shape) < 0.2, rng.uniform(0.1, 1.0, shape), 0.0)
+    sig.flat[0] = sig.flat[-1] = 0.3
+    h = (2e-3, 2e-3, 2e-3)
+    lab = torch.ones(shape, dtype=torch.uint8, device=DEV)
+    s = P.Solver(lab, torch.from_numpy(sig).to(DEV), h)
+    info = s.info()
+    s.close()
+    touched = np.zeros(tuple(m + 1 for m in shape), bool)
+    for k in (0, 1):
+        for j in (0, 1):
+            for i in (0, 1):
+                touched[k:shape[0] + k, j:shape[1] + j, i:shape[2] + i] |= sig > 0
+    assert info["n_dofs"] == touched.sum()
+    assert info["n_components"] == oracle.components(sig, h)[1]
+    for at in (0, n // 2, n - 1):
+        for bad in (-0.1, np.inf, np.nan):
+            wrong = sig.copy()
+            wrong.flat[at] = bad
+            with pytest.raises(P.SPFDError):
+                P.Solver(lab, torch.from_numpy(wrong).to(DEV), h)
