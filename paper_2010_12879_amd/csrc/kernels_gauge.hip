@@ -53,9 +53,10 @@ __global__ __launch_bounds__(TC_T) void k_tc_plane(const double *__restrict__ fl
 
 __global__ __launch_bounds__(TC_T) void k_tc_columns(const double *__restrict__ flux, double *__restrict__ a, Grid g)
 {
-    const int e = blockIdx.x * TC_T + threadIdx.x;
-    if (e >= g.Nx * g.Ny) return;
-    const int i = e % g.Nx, j = e / g.Nx;
+    // (a layer has fewer than 2^32 columns)
+    const unsigned e = blockIdx.x * TC_T + threadIdx.x;
+    if (e >= (unsigned)g.Nx * (unsigned)g.Ny) return;
+    const int i = (int)(e % (unsigned)g.Nx), j = (int)(e / (unsigned)g.Nx);
     const long long nn = (long long)g.Nx * g.Ny * g.Nz;
     const long long plane = (long long)g.Nx * g.Ny;
     const int d = blockIdx.y;
@@ -96,7 +97,9 @@ __global__ __launch_bounds__(TC_T) void k_tc_columns(const double *__restrict__ 
 hipError_t launch_tree_cotree(const double *flux, double *a, const Grid &g, hipStream_t s)
 {
     SPFD_LAUNCH(k_tc_plane, dim3((g.nx + TC_T - 1) / TC_T), dim3(TC_T), 0, s, flux, a, g);
-    SPFD_LAUNCH(k_tc_columns, dim3((g.Nx * g.Ny + TC_T - 1) / TC_T, 3), dim3(TC_T), 0, s, flux, a, g);
+    const unsigned long long cols = (unsigned long long)g.Nx * g.Ny;
+    if (cols > 0xffffffffull) return hipErrorInvalidValue;
+    SPFD_LAUNCH(k_tc_columns, dim3((unsigned)((cols + TC_T - 1) / TC_T), 3), dim3(TC_T), 0, s, flux, a, g);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""Field and edge voltages on grids whose layers or number of layers exceed what fits a 32-bit product or one launch
+"""Field, edge voltages and edge potentials on grids whose layers or number of layers exceed what fits a 32-bit product or one launch
 dimension."""
 import numpy as np
 import pytest
@@ -75,3 +75,27 @@ def test_layer_of_2e31_voxels():
         del a, emag
         torch.cuda.empty_cache()
     assert lo == hi == 6.0, (lo, hi)
+
+
+def test_edge_potentials_of_a_layer_of_2e31_columns():
+    """The tree-cotree potentials of one flux b_y, at the last edge of a slab of 46,341 x 46,341 node columns: a_x above
+    it is that flux, everything else 0 (207 GB)."""
+    n = 46340
+    nodes = 2 * (n + 1) * (n + 1)
+    _free_for(8 * 6 * nodes + 2 * n * n)
+    print("case edge potentials of 2^31 columns", flush=True)
+    flux = torch.zeros((3, 2, n + 1, n + 1), dtype=torch.float64, device=DEV)
+    a = torch.full((3, 2, n + 1, n + 1), 5.0, dtype=torch.float64, device=DEV)
+    flux[1, 0, n, n - 1] = 2.0
+    hd = P.spfd_create()
+    try:
+        P.spfd_set_geometry(hd, n, n, 1, 1.0, 1.0, 1.0, torch.zeros((1, n, n), dtype=torch.uint8, device=DEV))
+        P.spfd_edge_potentials(hd, flux, a)
+        got = float(a[0, 1, n, n - 1])
+        a[0, 1, n, n - 1] = 0.0
+        lo, hi = float(a.min()), float(a.max())
+    finally:
+        P.spfd_destroy(hd)
+        del a, flux
+        torch.cuda.empty_cache()
+    assert got == 2.0 and lo == hi == 0.0, (got, lo, hi)
