@@ -1417,7 +1417,7 @@ template hipError_t launch_pupdate<float>(Topo, const float *, double *, const S
 // ---------------------------------------------------------------- multigrid level kernels
 __device__ __forceinline__ bool stopped(const Scal *sc)
 {
-    return sc && sc[blockIdx.y].done;   // written by an earlier kernel only: a plain (scalar) load
+    return sc && sc[blockIdx.y].done;   // set by an earlier kernel than the one that asks: a plain (scalar) load
 }
 
 // x += s * P x_c

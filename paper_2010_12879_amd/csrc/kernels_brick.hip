@@ -17,7 +17,7 @@
 // the next; the degree-4 level alone is eight of them per cycle.  The region
 // is 2.7 (H = 2) to 5.2 (H = 4) times the brick, so the leg pays while the
 // workgroups together leave the chip idle, and loses on levels that fill it
-// (brick_leg_max).
+// (leg_max).
 //
 // Every node is computed as the separate kernels compute it, to the last bit,
 // so the choice of the form may depend on the number of right sides and moves
@@ -117,10 +117,11 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
     auto depth_z = [](int e) { return halo_depth<H, BZ>(e); };
     __shared__ T xs[2][G::EC], xe[FINE && !UP ? G::EC : 1];
     __shared__ T sig[NV], tab[LABEL ? MAX_LABELS : 1];
-    __shared__ int nslot[27], npar[27];
+    __shared__ int nslot[27], npar[27], stop;
     if constexpr (FINE && !UP) {
         // The right side may turn out to be done here: the leg's own workgroups do not wait for it (they write
-        // nothing but the cycle's vectors), and the kernels behind see the flag.
+        // nothing but the cycle's vectors, all of them again in the next cycle), and the kernels behind see the flag.
+        // As it may change while they start, one thread of each reads it for its whole workgroup.
         if (A.rr.n > 0 && blockIdx.x == gridDim.x - 1) {
             finish_rr(A.rr, blockIdx.y, (double *)xs);
             return;
@@ -133,7 +134,7 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
     const int ox = part % G::NX * BX, oy = part / G::NX % G::NY * BY, oz = part % G::PARTS / (G::NX * G::NY) * BZ;
     const int rx = ox - H, ry = oy - H, rz = oz - H;
     const int t = threadIdx.x;
-    const int stop = A.sc[blockIdx.y].done;
+    if (t == 0) stop = A.sc[blockIdx.y].done;
     const int4 fc = A.coord[b];
     const unsigned long long cm = A.cmask[b];
     if (t < 27) {
@@ -145,7 +146,6 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
         const T *table = A.models ? A.table + A.models[b * NBR + NTAB] : A.table;
         for (int l = t; l < MAX_LABELS; l += NTH) tab[l] = l < A.nlab ? table[l] : T(0);
     }
-    if (stop) return;   // (uniform)
     const long long vo = blockIdx.y * A.vs;
     // the thread's nodes: region column (ex, ey), layers ez0 .. ez0 + ZS - 1
     const int ex = t % EX, ey = (t / EX) % EY, ez0 = (t / EL) * ZS;
@@ -167,6 +167,7 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
         }
     }
     __syncthreads();
+    if (stop) return;   // (uniform: read once, above)
     auto brick_of = [&](int x, int y, int z) {   // index into nslot / npar of a region coordinate
         return ((x + rx) >> 3) + 1 + 3 * (((y + ry) >> 3) + 1) + 9 * (((z + rz) >> 3) + 1);
     };

@@ -103,8 +103,12 @@ __host__ __device__ __forceinline__ int col_ngroups(int nb)
 // whether a pointer is given, before the others were issued would cost one
 // more memory round trip per wave, a large part of a wave's life in these
 // short kernels.  So the column mask and the scalars are required (launches
-// that never stop pass zeroed scalars).  The stop flag is written only by an
-// earlier kernel of the stream, so a plain load sees it.
+// that never stop pass zeroed scalars).  The stop flag is written by an
+// earlier kernel of the stream, so a plain load sees it; the CG step and the
+// residual update may also set it themselves, on a breakdown that every wave
+// of the row finds from the same sums: one that reads it already set leaves
+// before its loads, the others leave without storing, and none waits for
+// another before that.
 template <int ZPL, bool FLAG = true, bool MODELS = false>
 __device__ __forceinline__ Seg<ZPL> make_seg(const Topo &topo, const Scal *sc)
 {
