@@ -487,7 +487,8 @@ __global__ __launch_bounds__((BrickGeom<H, BX, BY, BZ>::NTH)) void k_brick_leg(B
         sum = (a00 + a10) + (a01 + a11);
     }
     bc[rn] = sum;
-    if (A.xcout) A.xcout[blockIdx.y * A.vsc + rn] = A.c0 * sum * rdc;
+    // (0 at a coarse node without conductance whatever the sum is, as the separate kernel)
+    if (A.xcout) A.xcout[blockIdx.y * A.vsc + rn] = rdc > T(0) ? A.c0 * sum * rdc : T(0);
 }
 
 // the 27 bricks around each brick (index (dx+1) + 3 (dy+1) + 9 (dz+1); -1: absent)

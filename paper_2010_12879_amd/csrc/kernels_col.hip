@@ -800,8 +800,9 @@ __global__ __launch_bounds__(CTHREADS) void k_col_resid_restrict(OpArgs<T> op, T
         if (corner) {
             const long long n = pbase + ox + 8 * oy + 64 * (oz + k);
             bc[n] = a;
-            // the coarse level's first Chebyshev step from zero: x_c = c0 D_c^-1 b_c
-            if (xc) xc[blockIdx.y * vsc + n] = c0 * a * dc[k];
+            // the coarse level's first Chebyshev step from zero: x_c = c0 D_c^-1 b_c; 0 at a node without conductance
+            // whatever b_c is (in a column without unknowns no other kernel writes x_c, and a later solve reads it)
+            if (xc) xc[blockIdx.y * vsc + n] = dc[k] > T(0) ? c0 * a * dc[k] : T(0);
         }
     }
 }
