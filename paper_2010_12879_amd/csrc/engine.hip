@@ -295,7 +295,9 @@ T *dalloc(Ctx *c, std::vector<void *> &owner, size_t count)
     if (!p) {
         hipError_t e = raw_alloc(c, &p, bytes);
         if (e != hipSuccess) {
-            // give the cached buffers back and try once more
+            // give the cached buffers back and try once more (the error is dealt with here: it is not to be found
+            // after the next launch)
+            (void)hipGetLastError();
             for (auto &q : c->pool) {
                 raw_free(c, q.second);
                 for (size_t i = 0; i < c->sizes.size(); ++i)
@@ -306,7 +308,10 @@ T *dalloc(Ctx *c, std::vector<void *> &owner, size_t count)
             }
             c->pool.clear();
             e = raw_alloc(c, &p, bytes);
-            if (e != hipSuccess) throw HipFail{e, "device allocation"};
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                throw HipFail{e, "device allocation"};
+            }
         }
         c->sizes.push_back({p, bytes});
     }
@@ -2988,10 +2993,15 @@ spfd_status spfd_percentile(spfd_handle h, const double *emag, double q, double 
         const int nlab = h->voxel_mode ? MAX_LABELS : h->nlab;
         const int ng = 1 + nlab;
         const long long nvox = (long long)h->g.nx * h->g.ny * h->g.nz;
-        if (!h->d_sel_work) {
-            h->d_sel_cand = dalloc<unsigned long long>(h, h->geo_allocs, (size_t)bin_candidates(nvox));
-            h->d_sel_out = dalloc<double>(h, h->geo_allocs, 2 + MAX_LABELS);
+        if (!h->d_sel_out) h->d_sel_out = dalloc<double>(h, h->geo_allocs, 2 + MAX_LABELS);
+        if (!h->d_sel_work)
             h->d_sel_work = dalloc<uint8_t>(h, h->geo_allocs, std::max(bin_state_bytes(), sel_work_bytes(1 + MAX_LABELS)));
+        if (!h->d_sel_cand) {
+            try {
+                h->d_sel_cand = dalloc<unsigned long long>(h, h->geo_allocs, (size_t)bin_candidates(nvox));
+            } catch (const HipFail &f) {   // no room for the candidates: the radix form, which needs none
+                if (f.e != hipErrorOutOfMemory) throw;
+            }
         }
         const double *sv = h->voxel_mode ? h->d_sigvox : nullptr;
         double out[2 + MAX_LABELS];
@@ -2999,13 +3009,17 @@ spfd_status spfd_percentile(spfd_handle h, const double *emag, double q, double 
             HIPCHK(hipMemcpyAsync(out, h->d_sel_out, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
             HIPCHK(hipStreamSynchronize(h->stream));
         };
-        {
-            TScope ts(h, SPFD_K_EFIELD, 18.0 * nvox);
-            HIPCHK(launch_quantiles_bins(h->d_labels, h->d_table64, sv, nvox, emag, nlab, q, h->d_sel_work,
-                                         h->d_sel_cand, h->d_sel_out, h->stream));
+        bool found = false;
+        if (h->d_sel_cand) {
+            {
+                TScope ts(h, SPFD_K_EFIELD, 18.0 * nvox);
+                HIPCHK(launch_quantiles_bins(h->d_labels, h->d_table64, sv, nvox, emag, nlab, q, h->d_sel_work,
+                                             h->d_sel_cand, h->d_sel_out, h->stream));
+            }
+            fetch(ng + 1);
+            found = out[ng] == 0.0;
         }
-        fetch(ng + 1);
-        if (out[ng] != 0.0) {   // more candidates than the buffer holds: the radix form
+        if (!found) {   // no candidate buffer, or more candidates than it holds: the radix form
             TScope ts(h, SPFD_K_EFIELD, 8.0 * nvox * 9.0);
             HIPCHK(launch_quantiles(h->d_labels, h->d_table64, sv, nvox, emag, ng, q, h->d_sel_work, h->d_sel_out,
                                     h->stream));

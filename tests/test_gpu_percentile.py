@@ -61,3 +61,37 @@ def test_percentile_branches(shape, labels, fill, kind):
                     assert per[t] == ref_per[t] or (np.isnan(per[t]) and np.isnan(ref_per[t])), (q, t, per[t], ref_per[t])
     finally:
         P.spfd_destroy(s)
+
+
+def test_percentile_without_room_for_candidates():
+    """A caller's allocator that has no block of 1 MiB left, as many as the smallest candidate buffer takes: the radix
+    form answers, in the 0.3 MiB it needs, and the two-scan form once there is room again."""
+    print("case percentile without room", flush=True)
+    torch_alloc = P.torch_allocator(DEV)
+    state = {"most": 1 << 40, "refused": 0}
+
+    def alloc(nbytes, user):
+        if nbytes > state["most"]:
+            state["refused"] += 1
+            return None
+        return torch_alloc.alloc(nbytes, user)
+
+    callbacks = P.Allocator(P._ALLOC_FN(alloc), P._FREE_FN(lambda p, user: torch_alloc.free(p, user)), None)
+    rng = np.random.default_rng(5)
+    shape = (40, 37, 43)
+    lab = rng.integers(0, 5, shape).astype(np.uint8)
+    table = np.array([0.0, 0.2, 0.9, 0.0, 0.4])
+    e = _field("plain", shape, rng)
+    s = P.spfd_create(0, None, callbacks)
+    try:
+        P.spfd_set_geometry(s, shape[2], shape[1], shape[0], 1e-3, 1e-3, 1e-3, torch.from_numpy(lab).to(DEV))
+        P.spfd_set_sigma_table(s, table)
+        ref, ref_per = oracle.percentile_nearest_rank(e, lab, table[lab], 0.99, n_labels=5)
+        for most in ((1 << 20) - 1, (1 << 20) - 1, 1 << 40):
+            state["most"] = most
+            body, per = P.spfd_percentile(s, torch.from_numpy(e).to(DEV), 0.99, 5)
+            assert body == ref
+            assert all(a == b or (np.isnan(a) and np.isnan(b)) for a, b in zip(per, ref_per))
+        assert state["refused"] > 0
+    finally:
+        P.spfd_destroy(s)
