@@ -2234,7 +2234,7 @@ spfd_status solve_batch(Ctx *c, const double *b, long long bvs, Scal *sc, int nb
         if (any) {
             resid_b(c, b, bvs, sc, c->d_r, 1, nb);
             HIPCHK(hipMemcpyAsync(again, redo.data(), nb * sizeof(int), hipMemcpyHostToDevice, c->stream));
-            hipLaunchKernelGGL(k_rearm_if, dim3(1), dim3(64), 0, c->stream, sc, so.rel_tol, nb, again);
+            hipLaunchKernelGGL(k_rearm_if, dim3((nb + 63) / 64), dim3(64), 0, c->stream, sc, so.rel_tol, nb, again);
             HIPCHK(hipGetLastError());
         }
     }

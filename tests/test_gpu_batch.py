@@ -226,3 +226,20 @@ def test_packed_models_errors():
         assert e.value.status == 2
     finally:
         P.spfd_destroy(h)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_restarts_of_a_large_batch(prec):
+    """70 right sides, all the same, to a tolerance below what the recursive residual can promise: each restarts from
+    its true residual as one alone does (iterations, status, residual and bits)."""
+    print(f"case restarts {prec}", flush=True)
+    w = W.random_ellipsoid_phantom(20, 18, 24, seed=51, n_ell=6, semi_range=(3.0, 8.0))
+    s = P.Solver(_dev(w.labels), w.sigma_table, w.h, precision=prec)
+    a = _dev(w.a)
+    for tol in (1e-15, 3e-16, 1e-16):
+        one, info = s.solve(a, tol=tol, max_iter=200, check=False)
+        many, infos = s.solve(torch.stack([a] * 70), tol=tol, max_iter=200, check=False)
+        print(tol, info, infos[69], flush=True)
+        for k in range(70):
+            assert infos[k] == info and torch.equal(many[k], one), (k, infos[k], info)
+    s.close()
