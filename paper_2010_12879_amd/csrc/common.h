@@ -4,7 +4,8 @@
 // hold unknowns are stored, brick b occupies elements [b*512, b*512+512) and
 // node (tx,ty,tz) of a brick sits at tx + 8*ty + 64*tz.  A workgroup of 512
 // threads owns one brick, so each wave covers one 8x8 z-slice (512 contiguous
-// bytes in FP64).  Neighbour bricks come from a [nb][6] table (-1 = absent).
+// bytes in FP64).  Neighbour bricks come from a table of [nb][NBR] ints, the first
+// six of a brick's (-1 = absent).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

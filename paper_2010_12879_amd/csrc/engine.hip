@@ -135,10 +135,10 @@ struct Ctx {
     void *d_z = nullptr;
     float *d_r32 = nullptr;
     Scal *d_scal = nullptr;
-    Scal *h_scal = nullptr;   // pinned, one per right side plus one for the adjoint solve
+    Scal *h_scal = nullptr;   // pinned, one per right side (the lockstep solve's copies)
     Scal *h_ring = nullptr;   // pinned, 2 x (nrhs + 1): scalars of the last two enqueued CG steps
     Scal *h_ring_dev = nullptr;   // device address of h_ring (written by the last kernel of a CG step)
-    int h_cap = 0;                // right sides h_scal and h_ring hold (plus one each)
+    int h_cap = 0;                // right sides h_scal and h_ring hold (the ring one more)
     Scal *d_nostop = nullptr;     // zeroed scalars (never stopped) for cycles run outside a CG step
     Scal *step_mirror = nullptr;  // where the CG step being enqueued leaves its scalars
     int step_stamp = 0;           // and the stamp it leaves with them (0: none)
@@ -1576,7 +1576,7 @@ spfd_status do_set_num_rhs(Ctx *c, int nrhs)
     // host time, every rebuild passes here), cleared once the stream is idle (no step writes the ring)
     if (c->h_scal && c->h_ring && c->h_cap >= nrhs) {
         HIPCHK(hipStreamSynchronize(c->stream));
-        memset(c->h_scal, 0, sizeof(Scal) * (c->h_cap + 1));
+        memset(c->h_scal, 0, sizeof(Scal) * c->h_cap);
         memset(c->h_ring, 0, sizeof(Scal) * 2 * (c->h_cap + 1));
     } else {
         if (c->h_scal) (void)hipHostFree(c->h_scal);
@@ -1584,13 +1584,13 @@ spfd_status do_set_num_rhs(Ctx *c, int nrhs)
         if (c->h_ring) (void)hipHostFree(c->h_ring);
         c->h_ring = nullptr;
         c->h_cap = 0;
-        HIPCHK(hipHostMalloc((void **)&c->h_scal, sizeof(Scal) * (nrhs + 1), hipHostMallocDefault));
-        // coherent: the step's last kernel stores the scalars here, the host reads them after an event
+        HIPCHK(hipHostMalloc((void **)&c->h_scal, sizeof(Scal) * nrhs, hipHostMallocDefault));
+        // coherent: the step's last kernel stores the scalars here, and the host watches for its stamp
         HIPCHK(hipHostMalloc((void **)&c->h_ring, sizeof(Scal) * 2 * (nrhs + 1),
                              hipHostMallocMapped | hipHostMallocCoherent));
         HIPCHK(hipHostGetDevicePointer((void **)&c->h_ring_dev, c->h_ring, 0));
         // (fresh pinned memory can hold what an earlier handle left there, stamps that this one will wait for too)
-        memset(c->h_scal, 0, sizeof(Scal) * (nrhs + 1));
+        memset(c->h_scal, 0, sizeof(Scal) * nrhs);
         memset(c->h_ring, 0, sizeof(Scal) * 2 * (nrhs + 1));
         c->h_cap = nrhs;
     }

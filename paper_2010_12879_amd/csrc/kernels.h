@@ -129,7 +129,6 @@ hipError_t launch_coarse_setup(const double *w64, long long stride, Topo topo, i
                                int *adj, int *ndof_dev, int maxdof, hipStream_t s);
 hipError_t launch_coarse_assemble_brick(const double *w64, long long stride, Topo topo, const int *node_of_dof,
                                         const int *adj, int n, double *A, hipStream_t s);
-// dense pseudo-inverse in place; work: 2n ints + n doubles (+1 int of padding)
 // A <- inverse of the regularised coarsest matrix (work: coarse_factor_work_ints(n)
 // ints; dwork: dense_inverse_work_doubles(n) doubles)
 size_t coarse_factor_work_ints(int n);
@@ -259,9 +258,6 @@ hipError_t launch_resid(const OpArgs<double> &op, Topo topo, const double *b, co
 template <typename TZ>
 hipError_t launch_dots(Topo topo, const TZ *z, const double *r, const double *q, double *part, Scal *sc,
                        int first, const Batch &bt, hipStream_t s);
-template <typename TZ>
-hipError_t launch_pupdate(Topo topo, const TZ *z, double *p, const Scal *sc, int first, const Batch &bt,
-                          hipStream_t s);
 
 // multigrid level kernels (T = arithmetic of the cycle, TB = type of the level's right side)
 template <typename T, typename TB>

@@ -885,20 +885,13 @@ __global__ __launch_bounds__(256) void k_coarse_assemble_brick(const double *__r
     }
 }
 
-// Dense pseudo-inverse of the coarsest (singular) operator, in place: A_c +
-// sum over components c of alpha_c 1_c 1_c^T is SPD, and for a right side
-// orthogonal to every 1_c its solution has zero mean per component, i.e.
-// equals A_c^+ r.  One workgroup: components by min-label propagation over
-// the nonzeros, regularisation with alpha_c = mean diagonal / size^2, and
-// Gauss-Jordan inversion (no pivoting needed for an SPD matrix).
-// work: 2n ints + n doubles.
 // Make the coarsest matrix definite: A += sum over its connected components c
 // of (mean diagonal of c / |c|) 1_c 1_c^T.  For right sides with zero sum per
 // component the inverse of the result applies the pseudo-inverse and returns
 // the solution with zero sum per component.  Three kernels: the sparsity
 // pattern as adjacency lists (one wave per row, many workgroups), the
-// components by minimum-label propagation and their diagonal sums (one
-// workgroup), the rank-one updates (many workgroups).
+// components by union-find in LDS and their diagonal sums (one workgroup), the
+// rank-one updates (many workgroups).  The inverse follows (kernels_dense.hip).
 constexpr int CMAXADJ = 64;
 
 struct CoarseWork {
@@ -1385,34 +1378,6 @@ template hipError_t launch_dots<double>(Topo, const double *, const double *, co
                                         const Batch &, hipStream_t);
 template hipError_t launch_dots<float>(Topo, const float *, const double *, const double *, double *, Scal *, int,
                                        const Batch &, hipStream_t);
-
-template <typename TZ>
-__global__ __launch_bounds__(NT) void k_pupdate(Topo topo, const TZ *__restrict__ z, double *__restrict__ p,
-                                                const Scal *sc, int first, long long vs)
-{
-    int loc, row;
-    const int bk = topo_brick(topo, loc, row);
-    if (bk < 0) return;
-    sc += row;
-    if (sc->done) return;
-    z += row * vs;
-    p += row * vs;
-    const long long n = (long long)bk * BS + threadIdx.x;
-    const double zv = (double)z[n];
-    p[n] = first ? zv : zv + sc->beta * p[n];
-}
-
-template <typename TZ>
-hipError_t launch_pupdate(Topo topo, const TZ *z, double *p, const Scal *sc, int first, const Batch &bt,
-                          hipStream_t s)
-{
-    if (topo.nb <= 0) return hipSuccess;
-    SPFD_LAUNCH(k_pupdate<TZ>, topo_grid(topo, 1, bt.n), dim3(NT), 0, s, topo, z, p, sc, first, bt.vs);
-    return hipGetLastError();
-}
-template hipError_t launch_pupdate<double>(Topo, const double *, double *, const Scal *, int, const Batch &,
-                                           hipStream_t);
-template hipError_t launch_pupdate<float>(Topo, const float *, double *, const Scal *, int, const Batch &, hipStream_t);
 
 // ---------------------------------------------------------------- multigrid level kernels
 __device__ __forceinline__ bool stopped(const Scal *sc)
