@@ -480,7 +480,8 @@ EllStat ell_stat(Ctx *c, const EllStat *d_stat)
     return a;
 }
 
-// the finest level's operator is stored (else in label form)
+// the finest level's operator is stored (else in label form: formed where it is read, in the precision of the kernel that
+// reads it, so that an FP32 cycle sums FP32 conductivities; stored FP32 weights are FP64 sums rounded once)
 bool stored_fine(const Ctx *c) { return c->voxel_mode && !c->mlabel; }
 
 template <typename T>

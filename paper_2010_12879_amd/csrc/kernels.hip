@@ -309,7 +309,7 @@ __device__ __forceinline__ void brick_masks(bool unknown, int b, unsigned long l
 // tiles (label form: voxels (8 bx - 1 + a, 8 by - 1 + b, 8 bz - 1 + c), a, b, c in 0..8; outside = air (0)), inverse
 // diagonals, the node columns with unknowns, bit masks of the conducting edges and of the unknowns for the
 // components, and the number of unknowns.  All of it follows from the 9x9x9 voxels, staged in LDS once; as six
-// kernels, of which four read the stored weights again, this was 0.54 ms at 8.9 M unknowns; in one it is 117 us, bound
+// kernels, of which four read the stored weights again, this was 0.54 ms at 8.9 M unknowns; in one it is 95 us, bound
 // by the bytes it writes.
 template <bool VOX>
 __global__ __launch_bounds__(NT) void k_finest_setup(const uint8_t *__restrict__ labels,
@@ -603,7 +603,7 @@ __global__ void k_cc_local(const unsigned long long *__restrict__ emask, int *pa
 // brick-local components as the face edge next to them: a face node whose (own parent, neighbour's parent) pair
 // equals that of the previous node on the face skips its union (same sets, already joined or about to be).
 // (8.9 M unknowns, components of each brick and unions: 271 + 324 us with a workgroup per brick and every edge
-// united, now 75 + 222 us, beside the coarsening.)
+// united, now 76 + 250 us, beside the coarsening.)
 __global__ __launch_bounds__(256) void k_cc_union(const unsigned long long *__restrict__ emask, Topo topo, int *parent)
 {
     const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;

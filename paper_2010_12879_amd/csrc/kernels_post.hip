@@ -149,8 +149,8 @@ hipError_t launch_quantiles(const uint8_t *labels, const double *table, const do
 // times, each wave waiting for label, conductivity and field one after the
 // other: 8 x (150 + 28) us on the 250 x 150 x 900 body.  Here every lane has
 // SCAN_U labels and then SCAN_U fields in flight, conductivity flags and bins
-// are in LDS, and the voxels are read twice (scans of 48 and 38 us, selection
-// 14 us, the rest 25 us): the whole quantile 1,540 -> 130 us.
+// are in LDS, and the voxels are read twice (scans of 53 and 38 us, selection
+// 18 us, the rest 22 us): the kernels of a quantile 1,540 -> 131 us.
 //
 // Bins: 32 octaves of |E| ending one octave above that of a sampled maximum, body
 // 128 bins per octave, each label up to 16; keys beyond either end fall into
